@@ -224,10 +224,10 @@ int oscar_quantize_append(const void *k, const void *v, int32_t T, const int32_t
  * Two launches (split-K partial pass, reduce pass); with a single split the matrix-core kernel
  * writes `out` itself and the reduce launch is left out (same bits: the same sums, divided the
  * same way; the workspace is still required and may then stay untouched).
- * Two kernels sit behind this call: the matrix-core one (fp16 metadata; scale_mode L2 or MAX,
- * i.e. keys scaled into [-1, 1]) and a generic plain-ALU one for every other configuration
- * (fp32 metadata; scale_mode NONE or MEAN_ABS); both are checked against the same
- * oracle.  oscar_debug_force_generic_decode selects the generic kernel for every
+ * Two kernels sit behind this call: the matrix-core one (fp16 or fp32 metadata; scale_mode L2
+ * or MAX, i.e. keys scaled into [-1, 1]; page pools below 2 GiB each) and a generic plain-ALU one
+ * for every other configuration (scale_mode NONE or MEAN_ABS; larger pools); both are checked
+ * against the same oracle.  oscar_debug_force_generic_decode selects the generic kernel for every
  * configuration; it exists for tests and profiling. */
 int oscar_decode_attn(const void *q, const oscar_cache *cache, void *out, int32_t out_dtype,
                       float softmax_scale, int32_t max_seq_len_hint, int32_t num_splits,

@@ -24,6 +24,8 @@ SOURCES = {
     "oscar_decode.hip": [],
     "oscar_decode_mfma.hip": [],
     "oscar_decode_mfma_zpmin.hip": [],
+    "oscar_decode_mfma_meta32.hip": [],
+    "oscar_decode_mfma_meta32_zpmin.hip": [],
     "oscar_bf16_decode.hip": [],
     "oscar_probe.hip": [],
 }

@@ -37,12 +37,17 @@
 
 #include "oscar_decode_common.h"
 
-// This file is compiled twice: as it stands for the integer zero-point of Eq. 3-4, and through
+// This file is compiled four times: as it stands for the integer zero-point of Eq. 3-4, and through
 // oscar_decode_mfma_zpmin.hip with OSCAR_MFMA_ZPMIN = 1 for the float zero-point form; the
 // zero-point form is a compile-time constant of the kernel (no branches in the page loop), and
 // the two sets of variants compile side by side.
 #ifndef OSCAR_MFMA_ZPMIN
 #define OSCAR_MFMA_ZPMIN 0
+#endif
+// and both forms once more with OSCAR_MFMA_META32 = 1: step sizes, zero-points and norms stored
+// as fp32 (oscar_decode_mfma_meta32.hip, oscar_decode_mfma_meta32_zpmin.hip).
+#ifndef OSCAR_MFMA_META32
+#define OSCAR_MFMA_META32 0
 #endif
 #include "oscar_rowops.h"
 
@@ -207,6 +212,34 @@ __device__ __forceinline__ uint4 scale_halves(const uint4& y, half2v k) {
   for (int i = 0; i < 4; ++i) r[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, c[i]) * k);
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
+// Two fp16 limbs of t[i], |t[i]| < 2^13 * u[i] with u a power of two per slot, on a common grid:
+// hi[i] is t rounded to the grid 4 * u[i] (adding and subtracting 1.5 * 2^23 grids rounds to nearest
+// even), lo[i] what is left of it, the pair 2^-24 of the range off at most.  g and r are the two
+// limbs widened, for the sums that have to cancel the limbs' own.
+__device__ __forceinline__ void grid_limbs(const float (&t)[8], const float (&u)[8], float (&g)[8],
+                                           float (&r)[8], uint4& hi, uint4& lo) {
+#pragma clang fp contract(off)
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  constexpr float magic = 12582912.0f * 4.0f;
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float m = u[i] * magic;
+    g[i] = (t[i] + m) - m;
+    r[i] = t[i] - g[i];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x2 gv = {g[2 * i], g[2 * i + 1]}, rv = {r[2 * i], r[2 * i + 1]};
+    const half2v lv = __builtin_convertvector(rv, half2v);
+    h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(gv, half2v));
+    l[i] = __builtin_bit_cast(uint32_t, lv);
+    r[2 * i] = (float)lv[0];
+    r[2 * i + 1] = (float)lv[1];
+  }
+  hi = make_uint4(h[0], h[1], h[2], h[3]);
+  lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
 __device__ __forceinline__ void mul_limbs_packed(const uint4& xh, const uint4& xl, const uint4& y,
                                                  uint4& hi, uint4& lo) {
   const uint32_t a[4] = {xh.x, xh.y, xh.z, xh.w}, b[4] = {xl.x, xl.y, xl.z, xl.w};
@@ -331,6 +364,49 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, int off, u
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, (int)soff, 2));
 }
 
+// Eight consecutive metadata values (element `elem` of the resource onwards), held as stored.
+template <bool M32> struct Meta8;
+template <> struct Meta8<false> {
+  uint4 a;
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int elem, uint32_t so) {
+    a = buf_load16(r, elem * 2, so);
+  }
+};
+template <> struct Meta8<true> {
+  uint4 a, b;
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int elem, uint32_t so) {
+    a = buf_load16(r, elem * 4, so);
+    b = buf_load16(r, elem * 4 + 16, so);
+  }
+  __device__ __forceinline__ void floats(float (&x)[8]) const {
+    x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y);
+    x[2] = __uint_as_float(a.z); x[3] = __uint_as_float(a.w);
+    x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
+    x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
+  }
+};
+// What one unit of the other operand takes off per element: Delta*z, or -zero when the zero-point
+// is the float group minimum (x = Delta*c + zero).
+template <bool ZPMIN>
+__device__ __forceinline__ void zero_terms(const Meta8<true>& d, const Meta8<true>& z, float (&dz)[8]) {
+  float zf[8];
+  z.floats(zf);
+  if constexpr (ZPMIN) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dz[i] = -zf[i];
+  } else {
+    float df[8];
+    d.floats(df);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dz[i] = df[i] * zf[i];
+  }
+}
+template <bool ZPMIN>
+__device__ __forceinline__ void zero_terms(const Meta8<false>& d, const Meta8<false>& z, float (&dz)[8]) {
+  if constexpr (ZPMIN) neg_widen8(z.a, dz);
+  else mix_mul8(d.a, z.a, dz);
+}
+
 // A lane's two chunks of a tile pair: 16 bytes (2-bit) or 32 bytes (4-bit).
 template <int BITS> struct TilePair;
 template <> struct TilePair<2> {
@@ -395,20 +471,20 @@ struct PageRsrc {
 // What one wave needs of one page, in registers, single-buffered: every register is
 // reloaded for the wave's next page right after its last use for the current one, so each
 // load has a whole iteration to arrive and only one copy of a page is ever live.
-template <int BITS, int NGK> struct KeyRegs {
+template <int BITS, int NGK, bool M32> struct KeyRegs {
   static constexpr int PB = 2 * chunk_bytes(BITS);  // bytes of a lane's tile pair
   TilePair<BITS> kc[4];
-  uint4 kd[NGK], kz[NGK];  // key Delta / zero of positions 8n..8n+7 (operand order)
-  uint4 nr;                // norms of tokens 16*T+n, T = 0..7
+  Meta8<M32> kd[NGK], kz[NGK];  // key Delta / zero of positions 8n..8n+7 (operand order)
+  Meta8<M32> nr;                // norms of tokens 16*T+n, T = 0..7
   __device__ __forceinline__ void load_codes(const PageRsrc& r, int tp, int lane) {
     kc[tp].load(r.kcodes, (tp * 64 + (lane & 15) * 4 + (lane >> 4)) * PB, r.o_kcodes);
   }
   __device__ __forceinline__ void load_meta(const PageRsrc& r, int g, int lane) {
-    kd[g] = buf_load16(r.kmeta, (g * D + 8 * (lane & 15)) * 2, r.o_kmeta);
-    kz[g] = buf_load16(r.kmeta, ((NGK + g) * D + 8 * (lane & 15)) * 2, r.o_kmeta);
+    kd[g].load(r.kmeta, g * D + 8 * (lane & 15), r.o_kmeta);
+    kz[g].load(r.kmeta, (NGK + g) * D + 8 * (lane & 15), r.o_kmeta);
   }
   __device__ __forceinline__ void load_norm(const PageRsrc& r, int lane) {
-    nr = buf_load16(r.knorm, 8 * (lane & 15) * 2, r.o_knorm);
+    nr.load(r.knorm, 8 * (lane & 15), r.o_knorm);
   }
   __device__ __forceinline__ void load(const PageRsrc& r, int lane) {
 #pragma unroll
@@ -418,18 +494,18 @@ template <int BITS, int NGK> struct KeyRegs {
     load_norm(r, lane);
   }
 };
-template <int BITS, int NGV> struct ValRegs {
+template <int BITS, int NGV, bool M32> struct ValRegs {
   static constexpr int PB = 2 * chunk_bytes(BITS);
   TilePair<BITS> vc[4];
-  uint4 vd[NGV], vz[NGV];  // value Delta / zero of tokens 16*T+n
+  Meta8<M32> vd[NGV], vz[NGV];  // value Delta / zero of tokens 16*T+n
   __device__ __forceinline__ void load_codes(const PageRsrc& r, int tp, int lane) {
     vc[tp].load(r.vcodes, (tp * 64 + (lane & 15) * 4 + (lane >> 4)) * PB, r.o_vcodes);
   }
   __device__ __forceinline__ void load_delta(const PageRsrc& r, int g, int lane) {
-    vd[g] = buf_load16(r.vmeta, (g * R + 8 * (lane & 15)) * 2, r.o_vmeta);
+    vd[g].load(r.vmeta, g * R + 8 * (lane & 15), r.o_vmeta);
   }
   __device__ __forceinline__ void load_zero(const PageRsrc& r, int g, int lane) {
-    vz[g] = buf_load16(r.vmeta, ((NGV + g) * R + 8 * (lane & 15)) * 2, r.o_vmeta);
+    vz[g].load(r.vmeta, (NGV + g) * R + 8 * (lane & 15), r.o_vmeta);
   }
   __device__ __forceinline__ void load(const PageRsrc& r, int lane) {
 #pragma unroll
@@ -484,16 +560,16 @@ struct Raw8rt {
 };
 
 // The residual window of one (sequence, kv head) as buffer resources: K_u (fp16), V (caller's
-// dtype), token norms (fp16 here: this kernel requires fp16 metadata); void when the wave has
-// no residual token.
-struct ResRsrc {
+// dtype), token norms (metadata type); void when the wave has no residual token.
+template <bool M32> struct ResRsrc {
+  static constexpr int MB = M32 ? 4 : 2;
   __amdgpu_buffer_rsrc_t k, n;
   IoRsrc v;
   __device__ __forceinline__ void make(const DecodeParams& P, size_t rb, bool valid) {
     uint8_t* kp = const_cast<uint8_t*>(static_cast<const uint8_t*>(P.c.res_k)) + rb * D * 2;
-    uint8_t* np = const_cast<uint8_t*>(static_cast<const uint8_t*>(P.c.res_norm)) + rb * 2;
+    uint8_t* np = const_cast<uint8_t*>(static_cast<const uint8_t*>(P.c.res_norm)) + rb * MB;
     k = __builtin_amdgcn_make_buffer_rsrc(kp, 0, valid ? R * D * 2 : 0, 0x00020000);
-    n = __builtin_amdgcn_make_buffer_rsrc(np, 0, valid ? R * 2 : 0, 0x00020000);
+    n = __builtin_amdgcn_make_buffer_rsrc(np, 0, valid ? R * MB : 0, 0x00020000);
     v.make(P.c.res_v, rb * D, R * D, P.c.cfg.io_dtype, valid);
   }
 };
@@ -501,14 +577,18 @@ struct ResRsrc {
 // One residual token's share for a lane: 8 channels (channel group cg) of K_u (fp16) and of
 // V (caller's dtype), and the token norm, held raw until the query rotation is done.
 // `tok` is the token's slot in the window, clamped by the caller to a slot that exists.
-struct ResTok {
+template <bool M32> struct ResTok {
   uint4 k;
   Raw8rt v;
   uint32_t nrm;
-  __device__ __forceinline__ void load(const ResRsrc& r, int tok, int cg) {
+  __device__ __forceinline__ void load(const ResRsrc<M32>& r, int tok, int cg) {
     k = buf_load16(r.k, (tok * D + 8 * cg) * 2);
     v.load(r.v, tok * D + 8 * cg);
-    nrm = (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r.n, tok * 2, 0, 0);
+    if constexpr (M32) nrm = __builtin_amdgcn_raw_buffer_load_b32(r.n, tok * 4, 0, 0);
+    else nrm = (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r.n, tok * 2, 0, 0);
+  }
+  __device__ __forceinline__ float norm() const {
+    return M32 ? __uint_as_float(nrm) : __half2float(__ushort_as_half((unsigned short)nrm));
   }
 };
 // Step sizes are non-negative fp16 numbers, which order like their bit patterns: packed
@@ -533,12 +613,23 @@ __device__ __forceinline__ int row_hi(int h) { return 4 * (h & 3) + 2 * (h >> 2)
 // rest run one workgroup per CU and their overflow lives in accumulation registers
 // (measured: 4-bit, G_k = 32 took 188 us with 65 spilled registers at two per CU, 76 us at
 // one).
-__host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv) {
-  return oscar_decode_mfma_wgs_per_cu(bits, hp, ngk, ngv);
+//
+// fp32 metadata takes up to 68 registers more for the same page, the exact page sums fewer than the
+// running ones.  Measured at one / two per CU (attention alone, us, batch 4 x 8K, 8 x 16K and
+// 1 x 1K; the plain-ALU kernel these variants replaced: 54, 210 and 59 at GQA 4, 80, 186 and 85 at
+// GQA 7): (2,1,1,4) 13.4 / 13.0, 28.8 / 27.5, 14.9 / 14.7; (2,1,4,4) 13.9 / 17.0, 38.0 / 37.0,
+// 16.1 / 18.5; (2,2,1,4) 15.1 / 14.6, 33.0 / 24.2, 20.2 / 19.6; (2,2,4,1) 14.9 / 14.6, 31.8 / 23.7,
+// 19.8 / 29.3; (4,1,1,4) 14.6 / 15.1, 41.6 / 39.2, 15.4 / 15.4; (4,1,2,4) 15.1 / 16.7, 43.6 / 42.2,
+// 15.8 / 16.5; (4,1,4,1) 14.3 / 14.2, 40.9 / 38.7, 15.4 / 22.6; (4,2,1,4) 16.2 / 22.5, 25.6 / 38.5,
+// 20.5 / 24.3; (4,2,1,1) 13.6 / 14.1, 29.6 / 25.9, 18.1 / 22.5.  Two per CU where no size pays for it.
+__host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv, bool m32) {
+  if (!m32) return oscar_decode_mfma_wgs_per_cu(bits, hp, ngk, ngv);
+  if (bits == 2) return (hp == 1 ? ngk < 4 || ngv < 4 : ngk < 4) ? 2 : 1;
+  return hp == 1 && (ngk == 1 || (ngk == 2 && ngv <= 2)) ? 2 : 1;
 }
 
-template <int BITS, int HP, int NGK, int NGV, bool ZPMIN>
-__global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV))
+template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32>
+__global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
 void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr int TPG = 8 / NGK;  // token tiles per key group
   constexpr int CPG = 8 / NGV;  // channel tiles per value group
@@ -615,19 +706,19 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // over them then runs while the page is still on its way.  Waves without residual tokens skip
   // their loads (a void load still takes its turn in the CU's address unit, and at kernel start
   // all eight waves of a CU queue there). ----
-  ResRsrc rres;
+  ResRsrc<M32> rres;
   rres.make(P, ((size_t)b * Hkv + kvh) * R, wave_res);
   // slot of the wave's token i of pass p0, clamped to the slice (masked where it is used)
   auto res_slot = [&](int p0, int i) { return t_lo + max(0, min(p0 + 4 * wave + i, rcount - 1)); };
-  ResTok rt_first[4];   // the wave's four tokens of the first residual pass
+  ResTok<M32> rt_first[4];   // the wave's four tokens of the first residual pass
   if (wave_res) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) rt_first[i].load(rres, res_slot(0, i), cg);
   }
   PoolBases pools;
   pools.make(P, kvh);
-  KeyRegs<BITS, NGK> kr;
-  ValRegs<BITS, NGV> vr;
+  KeyRegs<BITS, NGK, M32> kr;
+  ValRegs<BITS, NGV, M32> vr;
   PageRsrc first;
   first.make(pools, P, (uint32_t)__builtin_amdgcn_readlane(tab, 0), pg_first < n_pages);
   kr.load(first, lane);
@@ -667,6 +758,12 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   for (int ct = 0; ct < 8; ++ct) O[ct] = (float4v){0.0f, 0.0f, 0.0f, 0.0f};
   // accumulator scale: O holds out * 2^-(24 - xv_cur - offset); this start value makes it 1
   int xv_cur = 24 - slot_bitpos_min(BITS);
+  // (M32) the output itself, see the value side of the page loop
+  [[maybe_unused]] float om[HP][8];
+#pragma unroll
+  for (int s = 0; s < HP; ++s)
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct) om[s][ct] = 0.0f;
 
   // ---- residual tokens: plain-ALU attention over fp16 K_u and raw V, wave-local.  Row q4
   // works for head q4 (+4) on all four tokens of the wave's pass, a lane on its 8 channels:
@@ -686,7 +783,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rt_first[i].nrm));
     // one pass: the wave's four tokens of slots p0 .. p0 + 15 of the slice, from registers
-    auto pass = [&](const ResTok (&rt)[4], int p0) {
+    auto pass = [&](const ResTok<M32> (&rt)[4], int p0) {
       float sc[HP][4], vv[4][8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -694,7 +791,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         float kv[8];
         halves_to_f32(rt[i].k, kv);
         rt[i].v.widen(vv[i], P.c.cfg.io_dtype);
-        const float nrm = __half2float(__ushort_as_half((unsigned short)rt[i].nrm));
+        const float nrm = rt[i].norm();
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
           float acc = qh[s][0] * kv[0];
@@ -726,7 +823,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     // walks the whole window, up to eight passes, in every workgroup: batch 64 x 8K, attention
     // alone, 127 residual tokens 73.4 -> 68.4 us against 60.3 with none; batch 1 x 1K, 104 residual
     // tokens 14.7 -> 13.9.  A third set does not fit the registers of any variant.)
-    ResTok rt_other[4];
+    ResTok<M32> rt_other[4];
     for (int p0 = 0;; p0 += 32) {
       const bool second = p0 + 16 + 4 * wave < rcount;
       if (second) {
@@ -761,7 +858,11 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         m_run[s] = mw[s];
         l_run[s] = (n == 0) ? lw[s] : 0.0f;   // l_run is summed over the 16 lanes at the end
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) O[ct][2 * s] = s_o[wave][h][16 * ct + n];
+        for (int ct = 0; ct < 8; ++ct) {
+          const float x = s_o[wave][h][16 * ct + n];
+          if constexpr (M32) om[s][ct] = x;
+          else O[ct][2 * s] = x;
+        }
       }
     }
     wave_lds_fence();
@@ -789,7 +890,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // writer role for the key operand: positions 8n..8n+7 of heads q4 (+4)
   float qr[HP][8], qs[HP][8], ps[HP];
 #if OSCAR_LIMBS_PACKED
-  uint4 qsh[HP], qsl[HP];   // qs as fp16 limbs
+  [[maybe_unused]] uint4 qsh[HP], qsl[HP];   // qs as fp16 limbs
 #endif
 #pragma unroll
   for (int s = 0; s < HP; ++s) {
@@ -811,7 +912,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     for (int i = 0; i < 8; ++i) qs[s][i] = ldexpf(qr[s][i], xh - slot_bitpos(BITS, n & 3, i));
     ps[s] = ldexpf(1.0f, 24 - xh);
 #if OSCAR_LIMBS_PACKED
-    split_to_halves(qs[s], qsh[s], qsl[s]);
+    if constexpr (!M32) split_to_halves(qs[s], qsh[s], qsl[s]);
 #endif
     if constexpr (HP == 2) {
       s_qr[wave][s][0][lane] = make_float4(qr[s][0], qr[s][1], qr[s][2], qr[s][3]);
@@ -823,6 +924,10 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #pragma unroll
   for (int T = 0; T < 8; ++T)
     vsc0[T] = ldexpf(1.0f, slot_bitpos_min(BITS) - slot_bitpos(BITS, n >> 2, T));
+
+  [[maybe_unused]] float vup[8];   // 1 / vsc0
+#pragma unroll
+  for (int T = 0; T < 8; ++T) vup[T] = ldexpf(1.0f, slot_bitpos(BITS, n >> 2, T) - slot_bitpos_min(BITS));
 
   Masks<BITS> masks;
   masks.init();
@@ -869,14 +974,16 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     // ---- q K^T ----
     float S[HP][8];
     {
-      const uint32_t nt[4] = {kr.nr.x, kr.nr.y, kr.nr.z, kr.nr.w};
+      [[maybe_unused]] const uint32_t nt[4] = {kr.nr.a.x, kr.nr.a.y, kr.nr.a.z, kr.nr.a.w};
+      [[maybe_unused]] float ntf[8];
+      if constexpr (M32) kr.nr.floats(ntf);
 #pragma unroll
       for (int g = 0; g < NGK; ++g) {
-        // per channel, what one unit of Q_h takes off the logit: Delta*z, or -zero when the
-        // zero-point is the float group minimum (x = Delta*c + zero)
+        // per channel, what one unit of Q_h takes off the logit
         float dz[8];
-        if constexpr (zp_min) neg_widen8(kr.kz[g], dz);
-        else mix_mul8(kr.kd[g], kr.kz[g], dz);
+        zero_terms<zp_min>(kr.kd[g], kr.kz[g], dz);
+        [[maybe_unused]] float kdf[8];
+        if constexpr (M32) kr.kd[g].floats(kdf);
         float bias[HP];
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
@@ -892,10 +999,16 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
           }
           bias[s] = row16_sum(bp);
           uint4 hi, lo;
+          if constexpr (M32) {
+            float t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = qs[s][i] * kdf[i];
+            split_to_halves(t, hi, lo);
+          }
 #if OSCAR_LIMBS_PACKED
-          mul_limbs_packed(qsh[s], qsl[s], kr.kd[g], hi, lo);
+          else mul_limbs_packed(qsh[s], qsl[s], kr.kd[g].a, hi, lo);
 #else
-          mul_split_hi_lo(qs[s], kr.kd[g], hi, lo);
+          else mul_split_hi_lo(qs[s], kr.kd[g].a, hi, lo);
 #endif
           // (rows of heads past the group hold zeros either way: their queries are zero)
           const int h = q4 + 4 * s;
@@ -915,8 +1028,15 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #pragma unroll
           for (int s = 0; s < HP; ++s) {
             // T is even: tokens T, T+1 are the two halves of norm word T/2
-            S[s][T] = mix_scale<0>(fmaf(a0[2 * s] + a0[2 * s + 1], ps[s], -bias[s]), nt[T >> 1]);
-            S[s][T + 1] = mix_scale<1>(fmaf(a1[2 * s] + a1[2 * s + 1], ps[s], -bias[s]), nt[T >> 1]);
+            const float l0 = fmaf(a0[2 * s] + a0[2 * s + 1], ps[s], -bias[s]);
+            const float l1 = fmaf(a1[2 * s] + a1[2 * s + 1], ps[s], -bias[s]);
+            if constexpr (M32) {
+              S[s][T] = l0 * ntf[T];
+              S[s][T + 1] = l1 * ntf[T + 1];
+            } else {
+              S[s][T] = mix_scale<0>(l0, nt[T >> 1]);
+              S[s][T + 1] = mix_scale<1>(l1, nt[T >> 1]);
+            }
           }
           keep_tuple(a0);
           keep_tuple(a1);
@@ -989,117 +1109,222 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
       l_run[s] = l_run[s] * alpha[s] + sum;
     }
 
-    // ---- scale of the value operand for this page: Delta_v * 2^xv < 2^13 ----
-    uint4 dm = vr.vd[0];
+    if constexpr (M32) {
+      // ---- fp32 metadata: P V of this page on its own, exactly, then added to the output ----
+      // sum p*Delta*c and sum p*Delta*z are each many times their difference, the page's share of
+      // the output (c is near z for most channels of a group that holds an outlier), and the
+      // plain-ALU kernel takes the difference code by code.  To lose no more than it does, the
+      // page's sums start from zero accumulators and both come from the same limbs on one grid
+      // (grid_limbs): the high limbs' sums are then exact, in the matrix core as in the vector unit,
+      // and so is their difference.  Limbs rounded to their own exponents lost the low bits of every
+      // small product beside a large one (a matrix instruction aligns its products to the largest
+      // nominal exponent, for codes held as subnormals up to 2^10 above their value): 3e-6 of
+      // sum p*Delta*z where the softmax is peaked, eight times this form's error in the output.
+      // (positive fp32 numbers order like their bit patterns; the exponent field E bounds the
+      // largest step size by 2^(E - 126))
+      uint32_t dm = 0;
 #pragma unroll
-    for (int g = 1; g < NGV; ++g) dm = pk_max4(dm, vr.vd[g]);
-    // Step sizes are non-negative fp16 numbers: the largest has the largest bit pattern, and its
-    // exponent field E bounds it by 2^(E - 14) (2^-14 for E = 0: zero or subnormal steps)
-    const uint32_t dm2 = pk_max_u16(pk_max_u16(dm.x, dm.y), pk_max_u16(dm.z, dm.w));
-    const uint32_t dbits = row16_max_u32(max(dm2 & 0xffffu, dm2 >> 16));  // the 16 lanes of a head group cover all 128 tokens
-    const int xv = 27 - (int)(dbits >> 10);
-    rescale |= (xv != xv_cur);
-    if (__any(rescale)) {
-      float f[HP];
+      for (int g = 0; g < NGV; ++g) {
+        const uint4 da = vr.vd[g].a, db = vr.vd[g].b;
+        dm = max(max(max(dm, max(da.x, da.y)), max(da.z, da.w)), max(max(db.x, db.y), max(db.z, db.w)));
+      }
+      const int xv = min(139 - (int)(row16_max_u32(dm) >> 23), 126);   // Delta_v * 2^xv < 2^13
+      const float pscale = ldexpf(1.0f, xv);
+      const int unscale_exp = 24 - slot_bitpos_min(BITS) - xv;
+      constexpr float kz = 1.0f / (float)(1 << (24 - slot_bitpos_min(BITS)));   // limbs -> accumulator
+      if (__any(rescale)) {
 #pragma unroll
-      for (int s = 0; s < HP; ++s) f[s] = ldexpf(alpha[s], xv - xv_cur);
+        for (int s = 0; s < HP; ++s)
 #pragma unroll
-      for (int ct = 0; ct < 8; ++ct) {
+          for (int ct = 0; ct < 8; ++ct) om[s][ct] *= alpha[s];
+      }
+#pragma unroll
+      for (int g = 0; g < NGV; ++g) {
+        float vdf[8], vzf[8];
+        vr.vd[g].floats(vdf);
+        vr.vz[g].floats(vzf);
+        // integer zero-point: the limbs carry the slots' weights, the zero-points take them back;
+        // float zero-point: the terms p * zero go on the grid themselves
+#pragma unroll
+        for (int T = 0; T < 8; ++T) {
+          vdf[T] = (vdf[T] * pscale) * vsc0[T];
+          vzf[T] = zp_min ? vzf[T] * pscale : vzf[T] * vup[T];
+        }
+        float zh[HP], zl[HP];
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
-          O[ct][2 * s] *= f[s];
-          O[ct][2 * s + 1] *= f[s];
+          float t[8], gr[8], re[8];
+          uint4 hi, lo;
+#pragma unroll
+          for (int T = 0; T < 8; ++T) t[T] = S[s][T] * vdf[T];
+          grid_limbs(t, vsc0, gr, re, hi, lo);
+          const int h = q4 + 4 * s;
+          *reinterpret_cast<uint4*>(&P_tab[row_hi(h)][8 * n]) = hi;
+          *reinterpret_cast<uint4*>(&P_tab[row_hi(h) + 1][8 * n]) = lo;
+          float sh = 0.0f, sl = 0.0f;
+          if constexpr (zp_min) {
+#pragma clang fp contract(off)
+            constexpr float magic = 12582912.0f * 4.0f;
+#pragma unroll
+            for (int T = 0; T < 8; ++T) {
+              const float tz = S[s][T] * vzf[T];
+              const float gz = (tz + magic) - magic;
+              sh -= gz;
+              sl -= tz - gz;
+            }
+          } else {
+#pragma unroll
+            for (int T = 0; T < 8; ++T) {
+              sh = fmaf(gr[T], vzf[T], sh);
+              sl = fmaf(re[T], vzf[T], sl);
+            }
+          }
+          zh[s] = row16_sum(sh) * kz;
+          zl[s] = row16_sum(sl) * kz;
         }
+        vr.load_delta(nx, g, lane);
+        wave_lds_fence();
+        half8 preg[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          preg[kk] = *reinterpret_cast<const half8*>(&P_tab[n][8 * (4 * kk + q4)]);
+        wave_lds_fence();
+        auto add_tile = [&](int ct, const float4v& a) {
+#pragma unroll
+          for (int s = 0; s < HP; ++s)
+            om[s][ct] += ldexpf((a[2 * s] - zh[s]) + (a[2 * s + 1] - zl[s]), unscale_exp);
+          keep_tuple(a);
+        };
+        float4v prev = (float4v){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int cc = 0; cc < CPG; ++cc) {
+          const int ct = g * CPG + cc;
+          u32x4 b0[4];
+          vr.vc[ct >> 1].chunk(ct & 1).operands(b0, masks);
+          OSCAR_PREFETCH_FENCE();
+          if (ct & 1) vr.load_codes(nx, ct >> 1, lane);
+          float4v acc = (float4v){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                preg[kk], __builtin_bit_cast(half8, b0[kk]), acc, 0, 0, 0);
+          if (cc > 0) add_tile(ct - 1, prev);   // one tile late: its result has left the matrix pipe
+          prev = acc;
+        }
+        add_tile(g * CPG + CPG - 1, prev);
       }
+    } else {
+      // ---- scale of the value operand for this page: Delta_v * 2^xv < 2^13 ----
+      uint4 dm = vr.vd[0].a;
+#pragma unroll
+      for (int g = 1; g < NGV; ++g) dm = pk_max4(dm, vr.vd[g].a);
+      // Step sizes are non-negative fp16 numbers: the largest has the largest bit pattern, and its
+      // exponent field E bounds it by 2^(E - 14) (2^-14 for E = 0: zero or subnormal steps)
+      const uint32_t dm2 = pk_max_u16(pk_max_u16(dm.x, dm.y), pk_max_u16(dm.z, dm.w));
+      const uint32_t dbits = row16_max_u32(max(dm2 & 0xffffu, dm2 >> 16));  // the 16 lanes of a head group cover all 128 tokens
+      const int xv = 27 - (int)(dbits >> 10);
+      rescale |= (xv != xv_cur);
+      if (__any(rescale)) {
+        float f[HP];
+#pragma unroll
+        for (int s = 0; s < HP; ++s) f[s] = ldexpf(alpha[s], xv - xv_cur);
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) {
+#pragma unroll
+          for (int s = 0; s < HP; ++s) {
+            O[ct][2 * s] *= f[s];
+            O[ct][2 * s + 1] *= f[s];
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < HP; ++s)
+#pragma unroll
+          for (int g = 0; g < NGV; ++g) bv[s][g] *= alpha[s];
+      }
+      xv_cur = xv;
+
+      // ---- P V, one value group at a time through the wave's LDS table ----
+      [[maybe_unused]] const float pscale = ldexpf(1.0f, xv);
+      float pc[HP][8];   // p * 2^(xv - slot offset): the value operand before Delta_v
 #pragma unroll
       for (int s = 0; s < HP; ++s)
 #pragma unroll
-        for (int g = 0; g < NGV; ++g) bv[s][g] *= alpha[s];
-    }
-    xv_cur = xv;
-
-    // ---- P V, one value group at a time through the wave's LDS table ----
-    [[maybe_unused]] const float pscale = ldexpf(1.0f, xv);
-    float pc[HP][8];   // p * 2^(xv - slot offset): the value operand before Delta_v
-#pragma unroll
-    for (int s = 0; s < HP; ++s)
-#pragma unroll
-      for (int T = 0; T < 8; ++T)
-        pc[s][T] = S[s][T] * (vsc0[T] * (OSCAR_LIMBS_PACKED ? 16384.0f : pscale));
+        for (int T = 0; T < 8; ++T)
+          pc[s][T] = S[s][T] * (vsc0[T] * (OSCAR_LIMBS_PACKED ? 16384.0f : pscale));
 #if OSCAR_LIMBS_PACKED
-    // The probabilities are split as p * 2^14 (at most 2^14, whatever the page's step sizes
-    // are); the rest of the page's power of two goes to the step sizes, whose largest then
-    // sits in [2^-2, 2^-1): an exact scaling unless a step size is 2^12 times smaller than
-    // the page's largest.
-    uint4 pch[HP], pcl[HP];
+      // The probabilities are split as p * 2^14 (at most 2^14, whatever the page's step sizes
+      // are); the rest of the page's power of two goes to the step sizes, whose largest then
+      // sits in [2^-2, 2^-1): an exact scaling unless a step size is 2^12 times smaller than
+      // the page's largest.
+      uint4 pch[HP], pcl[HP];
 #pragma unroll
-    for (int s = 0; s < HP; ++s) split_to_halves(pc[s], pch[s], pcl[s]);
-    const _Float16 ysc = (_Float16)ldexpf(1.0f, xv - 14);
-    const half2v ysc2 = {ysc, ysc};
+      for (int s = 0; s < HP; ++s) split_to_halves(pc[s], pch[s], pcl[s]);
+      const _Float16 ysc = (_Float16)ldexpf(1.0f, xv - 14);
+      const half2v ysc2 = {ysc, ysc};
 #endif
 #pragma unroll
-    for (int g = 0; g < NGV; ++g) {
-      float dz[8];
-      if constexpr (zp_min) neg_widen8(vr.vz[g], dz);
-      else mix_mul8(vr.vd[g], vr.vz[g], dz);
+      for (int g = 0; g < NGV; ++g) {
+        float dz[8];
+        zero_terms<zp_min>(vr.vd[g], vr.vz[g], dz);
 #if OSCAR_LIMBS_PACKED
-      const uint4 yd = scale_halves(vr.vd[g], ysc2);
+        const uint4 yd = scale_halves(vr.vd[g].a, ysc2);
 #endif
 #pragma unroll
-      for (int s = 0; s < HP; ++s) {
-        float acc_b = 0.0f;
+        for (int s = 0; s < HP; ++s) {
+          float acc_b = 0.0f;
 #pragma unroll
-        for (int T = 0; T < 8; ++T) acc_b = fmaf(S[s][T], dz[T], acc_b);
-        bv[s][g] += acc_b;
-        uint4 hi, lo;
+          for (int T = 0; T < 8; ++T) acc_b = fmaf(S[s][T], dz[T], acc_b);
+          bv[s][g] += acc_b;
+          uint4 hi, lo;
 #if OSCAR_LIMBS_PACKED
-        mul_limbs_packed(pch[s], pcl[s], yd, hi, lo);
+          mul_limbs_packed(pch[s], pcl[s], yd, hi, lo);
 #else
-        mul_split_hi_lo(pc[s], vr.vd[g], hi, lo);
+          mul_split_hi_lo(pc[s], vr.vd[g].a, hi, lo);
 #endif
-        // (heads past the group produce finite values in rows nobody reads back)
-        const int h = q4 + 4 * s;
-        *reinterpret_cast<uint4*>(&P_tab[row_hi(h)][8 * n]) = hi;
-        *reinterpret_cast<uint4*>(&P_tab[row_hi(h) + 1][8 * n]) = lo;
-      }
-      vr.load_delta(nx, g, lane);
-      wave_lds_fence();
-      half8 preg[4];
+          // (heads past the group produce finite values in rows nobody reads back)
+          const int h = q4 + 4 * s;
+          *reinterpret_cast<uint4*>(&P_tab[row_hi(h)][8 * n]) = hi;
+          *reinterpret_cast<uint4*>(&P_tab[row_hi(h) + 1][8 * n]) = lo;
+        }
+        vr.load_delta(nx, g, lane);
+        wave_lds_fence();
+        half8 preg[4];
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        preg[kk] = *reinterpret_cast<const half8*>(&P_tab[n][8 * (4 * kk + q4)]);
-      wave_lds_fence();
+        for (int kk = 0; kk < 4; ++kk)
+          preg[kk] = *reinterpret_cast<const half8*>(&P_tab[n][8 * (4 * kk + q4)]);
+        wave_lds_fence();
 #pragma unroll
-      for (int cc = 0; cc < CPG; cc += 2) {
-        const int ct = g * CPG + cc;
-        if constexpr (!ONE_TILE) {
-          u32x4 b0[4], b1[4];
-          vr.vc[ct >> 1].chunk(0).operands(b0, masks);
-          vr.vc[ct >> 1].chunk(1).operands(b1, masks);
-          OSCAR_PREFETCH_FENCE();
-          vr.load_codes(nx, ct >> 1, lane);
+        for (int cc = 0; cc < CPG; cc += 2) {
+          const int ct = g * CPG + cc;
+          if constexpr (!ONE_TILE) {
+            u32x4 b0[4], b1[4];
+            vr.vc[ct >> 1].chunk(0).operands(b0, masks);
+            vr.vc[ct >> 1].chunk(1).operands(b1, masks);
+            OSCAR_PREFETCH_FENCE();
+            vr.load_codes(nx, ct >> 1, lane);
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            O[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct], 0, 0, 0);
-            O[ct + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                preg[kk], __builtin_bit_cast(half8, b1[kk]), O[ct + 1], 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk) {
+              O[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct], 0, 0, 0);
+              O[ct + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  preg[kk], __builtin_bit_cast(half8, b1[kk]), O[ct + 1], 0, 0, 0);
+            }
+          } else {
+            u32x4 b0[4];
+            vr.vc[ct >> 1].chunk(0).operands(b0, masks);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+              O[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct], 0, 0, 0);
+            asm volatile("" ::: "memory");
+            vr.vc[ct >> 1].chunk(1).operands(b0, masks);
+            OSCAR_PREFETCH_FENCE();
+            vr.load_codes(nx, ct >> 1, lane);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+              O[ct + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct + 1], 0, 0, 0);
           }
-        } else {
-          u32x4 b0[4];
-          vr.vc[ct >> 1].chunk(0).operands(b0, masks);
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            O[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct], 0, 0, 0);
-          asm volatile("" ::: "memory");
-          vr.vc[ct >> 1].chunk(1).operands(b0, masks);
-          OSCAR_PREFETCH_FENCE();
-          vr.load_codes(nx, ct >> 1, lane);
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            O[ct + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                preg[kk], __builtin_bit_cast(half8, b0[kk]), O[ct + 1], 0, 0, 0);
         }
       }
     }
@@ -1118,7 +1343,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   if (OSCAR_DECODE_PRIORITY) __builtin_amdgcn_s_setprio(0);
   // ---- wave results -> LDS ----
   {
-    const float unscale = ldexpf(1.0f, 24 - xv_cur - slot_bitpos_min(BITS));
+    [[maybe_unused]] const float unscale = ldexpf(1.0f, 24 - xv_cur - slot_bitpos_min(BITS));
 #pragma unroll
     for (int s = 0; s < HP; ++s) {
       const int h = q4 + 4 * s;
@@ -1129,7 +1354,8 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
       if (h < gq) {
 #pragma unroll
         for (int ct = 0; ct < 8; ++ct)
-          s_o[wave][h][16 * ct + n] = (O[ct][2 * s] + O[ct][2 * s + 1]) * unscale - bvt[ct / CPG];
+          s_o[wave][h][16 * ct + n] =
+              M32 ? om[s][ct] : (O[ct][2 * s] + O[ct][2 * s + 1]) * unscale - bvt[ct / CPG];
         if (n == 0) {
           s_wm[wave][h] = m_run[s];
           s_wl[wave][h] = l_tot;
@@ -1206,16 +1432,16 @@ template <int BITS, int HP>
 int launch_groups(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, hipEvent_t e0,
                   hipEvent_t e1) {
   const int ngk = P.g.ngk, ngv = P.g.ngv;
-  constexpr bool ZPM = OSCAR_MFMA_ZPMIN != 0;
+  constexpr bool ZPM = OSCAR_MFMA_ZPMIN != 0, M32 = OSCAR_MFMA_META32 != 0;
   // the event-carrying launch only when a timer asked for it: the plain launch is what a
   // stream capture records
 #define OSCAR_MFMA_CASE(NK, NV)                                                            \
   if (ngk == NK && ngv == NV) {                                                            \
     if (e0 || e1)                                                                          \
-      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM>), grid,       \
+      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32>), grid,       \
                             dim3(256), 0, st, e0, e1, 0, P, gq);                           \
     else                                                                                   \
-      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM>), grid,          \
+      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32>), grid,          \
                          dim3(256), 0, st, P, gq);                                         \
     return OSCAR_OK;                                                                       \
   }
@@ -1244,14 +1470,23 @@ int launch_this_form(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, h
 
 }  // namespace
 
-#if OSCAR_MFMA_ZPMIN
-
-int oscar_launch_decode_mfma_zpmin(const void* params, int gq, dim3 grid, hipStream_t st,
-                                   hipEvent_t e0, hipEvent_t e1) {
-  return launch_this_form(*reinterpret_cast<const DecodeParams*>(params), gq, grid, st, e0, e1);
-}
-
+// the other three translation units' entries
+#define OSCAR_MFMA_FORM(NAME) \
+  int NAME(const void* params, int gq, dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
+#define OSCAR_MFMA_FORM_DEFINE(NAME)                                                             \
+  OSCAR_MFMA_FORM(NAME) {                                                                        \
+    return launch_this_form(*reinterpret_cast<const DecodeParams*>(params), gq, grid, st, e0, e1); \
+  }
+#if OSCAR_MFMA_META32 && OSCAR_MFMA_ZPMIN
+OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_meta32_zpmin)
+#elif OSCAR_MFMA_META32
+OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_meta32)
+#elif OSCAR_MFMA_ZPMIN
+OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_zpmin)
 #else
+OSCAR_MFMA_FORM(oscar_launch_decode_mfma_zpmin);
+OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32);
+OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32_zpmin);
 
 #ifdef OSCAR_DECODE_STAMPS
 // [8 workgroup slots][4 waves][32 stamps] of the last stamped launch (integer zero-point variants)
@@ -1260,9 +1495,6 @@ extern "C" int oscar_debug_read_stamps(void* dst, size_t bytes) {
   return hipMemcpyFromSymbol(dst, HIP_SYMBOL(g_stamps), sizeof(g_stamps)) == hipSuccess ? OSCAR_OK : OSCAR_ERR_HIP;
 }
 #endif
-
-int oscar_launch_decode_mfma_zpmin(const void* params, int gq, dim3 grid, hipStream_t st,
-                                   hipEvent_t e0, hipEvent_t e1);
 
 // Test / profiling switch of oscar_debug_force_generic_decode: the only process-wide state of
 // the library besides the cached device properties, one relaxed atomic flag read per launch.
@@ -1273,12 +1505,11 @@ extern "C" int oscar_debug_force_generic_decode(int32_t on) {
 }
 
 // Launches the matrix-core partial pass when the configuration is one it is built for
-// (fp16 metadata; group sizes 32, 64 or 128 on either side; keys scaled into [-1, 1]; page pools
-// below 2 GiB each); OSCAR_ERR_UNSUPPORTED tells the caller to use the generic kernel.
+// (fp16 or fp32 metadata; group sizes 32, 64 or 128 on either side; keys scaled into [-1, 1];
+// page pools below 2 GiB each); OSCAR_ERR_UNSUPPORTED tells the caller to use the generic kernel.
 int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
                              hipEvent_t e0, hipEvent_t e1) {
   const DecodeParams& P = *reinterpret_cast<const DecodeParams*>(params);
-  if (P.c.cfg.meta_dtype != OSCAR_F16) return OSCAR_ERR_UNSUPPORTED;
   // the key operand's fixed exponent assumes Delta_k <= 1, which holds when |K_u| <= 1 (L2 or
   // maximum scaling); the un-scaled and mean-absolute-value ablations go to the generic kernel
   if (P.c.cfg.scale_mode != OSCAR_SCALE_L2 && P.c.cfg.scale_mode != OSCAR_SCALE_MAX)
@@ -1286,9 +1517,14 @@ int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t 
   if (g_force_generic.load(std::memory_order_relaxed)) return OSCAR_ERR_UNSUPPORTED;
   // a page is addressed as a 32-bit scalar offset into its pool
   const unsigned long long units = (unsigned long long)P.c.num_pages * (unsigned long long)P.c.cfg.n_kv_heads;
-  const int biggest = P.g.k_codes_bytes > P.g.v_meta_bytes ? P.g.k_codes_bytes : P.g.v_meta_bytes;
+  int biggest = P.g.k_codes_bytes > P.g.v_meta_bytes ? P.g.k_codes_bytes : P.g.v_meta_bytes;
+  if (P.g.k_meta_bytes > biggest) biggest = P.g.k_meta_bytes;
   if (units * (unsigned long long)biggest > 0x7FFFFFFFull) return OSCAR_ERR_UNSUPPORTED;
-  if (P.c.cfg.zp_mode == OSCAR_ZP_MIN) return oscar_launch_decode_mfma_zpmin(params, gq, grid, st, e0, e1);
+  const bool zpm = P.c.cfg.zp_mode == OSCAR_ZP_MIN;
+  if (P.c.cfg.meta_dtype == OSCAR_F32)
+    return zpm ? oscar_launch_decode_mfma_meta32_zpmin(params, gq, grid, st, e0, e1)
+               : oscar_launch_decode_mfma_meta32(params, gq, grid, st, e0, e1);
+  if (zpm) return oscar_launch_decode_mfma_zpmin(params, gq, grid, st, e0, e1);
   return launch_this_form(P, gq, grid, st, e0, e1);
 }
 

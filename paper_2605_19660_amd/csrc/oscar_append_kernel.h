@@ -475,18 +475,24 @@ __device__ __forceinline__ void key_codes(const uint4& ku, const float (&rd)[8],
   }
 }
 
-template <typename IO, typename META, int BITS, int KG, int XF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF == 2 ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
+// NP = tokens per thread.  8: 256 threads a workgroup, four workgroups a CU, the form for launches
+// that fill the chip.  4: 512 threads, half the work per thread, for launches that do not (see
+// launch_kg): there a workgroup's own latency is the time, and it is issue-bound at one wave a SIMD.
+// A thread of the 512 takes every second pass: thread group 0 the even ones, group 1 the odd ones,
+// which are the two halves of a packed value piece.
+template <typename IO, typename META, int BITS, int KG, int XF, int NP>
+__global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF == 2 ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
   constexpr bool NORM_ALL = XF == XF_ALL_HEADS;
   constexpr int NGK = R / KG;        // key groups per page
-  constexpr int PPG = KG / 16;       // passes per key group
+  constexpr int RPG = KG / 16 * NP / 8;   // registers (a thread's tokens) per key group
+  constexpr int NT = 2048 / NP, NW = NT / 64, ROWS = NT / 16;   // threads, waves, token rows
   constexpr float QMAX = (float)((1 << BITS) - 1);
   constexpr int IMG = R * D * BITS / 8;   // bytes of one code image
 
   struct MinMax {
     uint4 mn, mx;   // packed fp16, the 8 channels of a channel group
   };
-  __shared__ __align__(16) MinMax s_red[NGK][4][16];   // [group][wave][channel group]
+  __shared__ __align__(16) MinMax s_red[NGK][NW][16];   // [group][wave][channel group]
   // per channel: 1/Delta, -z, qmax-z, z*place; channel 8*cg + e sits at slot 16*e + cg, so the
   // 16 lanes of a row (cg = 0..15) read 256 consecutive bytes (channel order would put them
   // 128 bytes apart: an 8-way bank conflict on every read)
@@ -502,7 +508,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
   // kv head fastest: the workgroups that share a token block's rows in memory run together
   const int b = blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int slot = tid >> 4;                            // token of a pass
+  const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;  // token of a pass
+  const int grp = NP == 8 ? 0 : tid >> 8;               // thread group
+  // register i of a thread holds token 16 * pass(i) + slot of the block
+  auto pass = [&](int i) { return NP == 8 ? i : 2 * i + grp; };
   const int cg = channel_group_of_row_lane(tid & 15);   // channels 8*cg .. 8*cg+7
   const int Hkv = P.c.cfg.n_kv_heads;
   const bool zp_min = P.c.cfg.zp_mode == OSCAR_ZP_MIN;
@@ -534,10 +543,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
 
   // ---- phase 1: gather the block (old residual tokens first, then new tokens) and
   // transform the new keys; keys end up as packed fp16 K_u, values stay raw ----
-  uint4 ku[8];
-  Raw8<IO> vraw[8];
-  float nrm[8];
-  // batched_norms (uniform over the workgroup): the norms of tokens 16*(4*hb + j) + slot sit in
+  uint4 ku[NP];
+  Raw8<IO> vraw[NP];
+  float nrm[NP];
+  // batched_norms (uniform over the workgroup): the norms of tokens 16*pass(4*hb + j) + slot sit in
   // nrm_q[hb] of the lanes whose position in their quad is j, and nrm[] is unused
   bool batched_norms = false;
   float nrm_q[2] = {0.0f, 0.0f};
@@ -551,58 +560,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
   }
   if (do_block && blk * R >= sp.r0) {
     // the whole block is new tokens (every block of a prefill): straight-line loads
-    Raw8<IO> kraw[8];
-    const size_t tok0 = (size_t)b * P.T + (size_t)(blk * R - sp.r0 + slot);
+    Raw8<IO> kraw[NP];
+    const size_t tok0 = (size_t)b * P.T + (size_t)(blk * R - sp.r0 + slot + 16 * grp);
     const IO* kp = knew + (tok0 * Hkv + kvh) * D + cg * 8;
     const IO* vp = vnew + (tok0 * Hkv + kvh) * D + cg * 8;
-    const size_t pstride = (size_t)16 * Hkv * D;
+    const size_t pstride = (size_t)(16 * (8 / NP)) * Hkv * D;
 #pragma unroll
-    for (int p = 0; p < 8; ++p) kraw[p].load(kp + p * pstride);
+    for (int p = 0; p < NP; ++p) kraw[p].load(kp + p * pstride);
     // The values are not needed before the key codes are done: their loads go out behind the
     // first half of the key transform (held there by the fences), which keeps their 32
     // registers free while the transform is at its widest and spreads the workgroup's requests.
+    // (Half the tokens per thread leave room for them from the start.)
     auto load_values = [&]() {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int p = 0; p < 8; ++p) vraw[p].load(vp + p * pstride);
+      for (int p = 0; p < NP; ++p) vraw[p].load(vp + p * pstride);
       __builtin_amdgcn_sched_barrier(0);
     };
+    if (NP == 4) load_values();
     if (NORM_ALL) {
 #pragma unroll
-      for (int p = 0; p < 8; ++p) nrm[p] = to_f32<META>(pre_norm[tok_meta_pos(p * 16 + slot)]);
+      for (int p = 0; p < NP; ++p) nrm[p] = to_f32<META>(pre_norm[tok_meta_pos(pass(p) * 16 + slot)]);
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
+      for (int p = 0; p < NP; ++p) {
         float x[8];
         kraw[p].widen(x);
         ku[p] = key_transform8_given<META>(x, sgn, nrm[p], xf.rotate);
-        if (p == 3) load_values();
+        if (NP == 8 && p == 3) load_values();
       }
     } else if (XF == XF_PUBLISHED) {
       // the method as published: four tokens at a time, one square root and one reciprocal
       // per lane instead of four (key_transform_4tokens)
       batched_norms = true;
 #pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
+      for (int hb = 0; hb < NP / 4; ++hb) {
         float x[4][8];
 #pragma unroll
         for (int j = 0; j < 4; ++j) kraw[4 * hb + j].widen(x[j]);
         key_transform_4tokens<META>(x, sgn, tid & 3, nrm_q[hb], &ku[4 * hb]);
-        if (hb == 0) load_values();
+        if (NP == 8 && hb == 0) load_values();
       }
     } else {
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
+      for (int p = 0; p < NP; ++p) {
         float x[8];
         kraw[p].widen(x);
         ku[p] = key_transform8<META>(x, sgn, nrm[p], xf);
-        if (p == 3) load_values();
+        if (NP == 8 && p == 3) load_values();
       }
     }
   } else if (do_block) {
-    Raw8<IO> kraw[8];
+    Raw8<IO> kraw[NP];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int pi = blk * R + p * 16 + slot;  // index among pending tokens
+    for (int p = 0; p < NP; ++p) {
+      const int pi = blk * R + pass(p) * 16 + slot;  // index among pending tokens
       if (pi < sp.r0) {
         kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
         nrm[p] = to_f32<META>(res_norm[pi]);
@@ -617,24 +628,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     }
     // the branch above is uniform per 16-lane token row; every row runs the transform (its
     // result is dropped for tokens that came from the residual, which are K_u already)
+    if (NP == 4 && XF == XF_PUBLISHED) {
+      float x[4][8], nq;
+      uint4 nu[4];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int pi = blk * R + p * 16 + slot;
-      const bool old = pi < sp.r0;
-      float x[8], nn;
-      kraw[p].widen(x);
-      uint4 nu;
-      if (NORM_ALL) {   // (rows that came from the residual drop the result)
-        nn = to_f32<META>(pre_norm[tok_meta_pos(p * 16 + slot)]);
-        nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
-      } else {
-        nu = key_transform8<META>(x, sgn, nn, xf);
+      for (int j = 0; j < 4; ++j) kraw[j].widen(x[j]);
+      key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool old = blk * R + pass(j) * 16 + slot < sp.r0;
+        const float nn = quad_bcast(nq, j);
+        ku[j].x = old ? kraw[j].a.x : nu[j].x;
+        ku[j].y = old ? kraw[j].a.y : nu[j].y;
+        ku[j].z = old ? kraw[j].a.z : nu[j].z;
+        ku[j].w = old ? kraw[j].a.w : nu[j].w;
+        nrm[j] = old ? nrm[j] : nn;
       }
-      ku[p].x = old ? kraw[p].a.x : nu.x;
-      ku[p].y = old ? kraw[p].a.y : nu.y;
-      ku[p].z = old ? kraw[p].a.z : nu.z;
-      ku[p].w = old ? kraw[p].a.w : nu.w;
-      nrm[p] = old ? nrm[p] : nn;
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const int pi = blk * R + pass(p) * 16 + slot;
+        const bool old = pi < sp.r0;
+        float x[8], nn;
+        kraw[p].widen(x);
+        uint4 nu;
+        if (NORM_ALL) {   // (rows that came from the residual drop the result)
+          nn = to_f32<META>(pre_norm[tok_meta_pos(pass(p) * 16 + slot)]);
+          nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
+        } else {
+          nu = key_transform8<META>(x, sgn, nn, xf);
+        }
+        ku[p].x = old ? kraw[p].a.x : nu.x;
+        ku[p].y = old ? kraw[p].a.y : nu.y;
+        ku[p].z = old ? kraw[p].a.z : nu.z;
+        ku[p].w = old ? kraw[p].a.w : nu.w;
+        nrm[p] = old ? nrm[p] : nn;
+      }
     }
   }
   __syncthreads();  // every read of the old residual precedes the tail write below
@@ -644,27 +673,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     const int src0 = (sp.nq == 0) ? 0 : sp.nq * R - sp.r0;  // first new token of the tail
     const int dst0 = (sp.nq == 0) ? sp.r0 : 0;              // its residual slot
     const int cnt = sp.n - src0;                            // new tokens going to the residual
-    for (int i0 = 0; i0 < cnt; i0 += 16) {
-      const int i = i0 + slot;
-      const int ic = i < cnt ? i : cnt - 1;
-      const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
-      Raw8<IO> kin, vin;
-      kin.load(knew + off);
-      vin.load(vnew + off);
-      float x[8], nn;
-      kin.widen(x);
-      uint4 nu;
-      if (NORM_ALL) {
-        nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
-        nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
-      } else {
-        nu = key_transform8<META>(x, sgn, nn, xf);
+    const int row = tid >> 4;
+    // In the 512-thread form a tail of more than one token per row goes in one batch, four tokens a
+    // row, their loads together and one square root and reciprocal a lane (key_transform_4tokens).
+    // One token after the other, each behind its own loads, it was the longest part of a launch of
+    // few workgroups: 500 new tokens took 4 us more than 512.  (The 256-thread form has no registers
+    // for it.)
+    constexpr bool BATCHED_TAIL = NP == 4 && XF == XF_PUBLISHED;
+    if (BATCHED_TAIL && cnt > ROWS) {   // (at most 128 = 4 * ROWS tokens)
+      Raw8<IO> kin4[4], vin4[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = j * ROWS + row, ic = i < cnt ? i : cnt - 1;
+        const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
+        kin4[j].load(knew + off);
+        vin4[j].load(vnew + off);
       }
-      if (i < cnt) {
-        const int ds = dst0 + i;
-        *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
-        vin.store(res_v + (size_t)ds * D + cg * 8);
-        if (cg == 0) res_norm[ds] = from_f32<META>(nn);
+      float x[4][8], nq;
+      uint4 nu[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
+      key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = j * ROWS + row;
+        if (i < cnt) {
+          const int ds = dst0 + i;
+          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
+          vin4[j].store(res_v + (size_t)ds * D + cg * 8);
+          if ((tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
+        }
+      }
+    } else {
+      for (int i0 = 0; i0 < cnt; i0 += ROWS) {
+        const int i = i0 + row;
+        const int ic = i < cnt ? i : cnt - 1;
+        const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
+        Raw8<IO> kin, vin;
+        kin.load(knew + off);
+        vin.load(vnew + off);
+        float x[8], nn;
+        kin.widen(x);
+        uint4 nu;
+        if (NORM_ALL) {
+          nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
+          nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
+        } else {
+          nu = key_transform8<META>(x, sgn, nn, xf);
+        }
+        if (i < cnt) {
+          const int ds = dst0 + i;
+          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
+          vin.store(res_v + (size_t)ds * D + cg * 8);
+          if (cg == 0) res_norm[ds] = from_f32<META>(nn);
+        }
       }
     }
   }
@@ -682,11 +744,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
   // of the wave, then (through LDS) the 4 waves
 #pragma unroll
   for (int gk = 0; gk < NGK; ++gk) {
-    uint32_t mn[4] = {ku[gk * PPG].x, ku[gk * PPG].y, ku[gk * PPG].z, ku[gk * PPG].w};
+    uint32_t mn[4] = {ku[gk * RPG].x, ku[gk * RPG].y, ku[gk * RPG].z, ku[gk * RPG].w};
     uint32_t mx[4] = {mn[0], mn[1], mn[2], mn[3]};
 #pragma unroll
-    for (int p = 1; p < PPG; ++p) {
-      const uint4 q = ku[gk * PPG + p];
+    for (int p = 1; p < RPG; ++p) {
+      const uint4 q = ku[gk * RPG + p];
       const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -707,27 +769,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     }
   }
   if (batched_norms) {
-    if ((tid & 15) < 4) {   // first quad of the token row: lane j holds the norms of passes j, 4 + j
+    if ((tid & 15) < 4) {   // first quad of the token row: lane j holds the norms of registers j, 4 + j
 #pragma unroll
-      for (int hb = 0; hb < 2; ++hb)
-        s_norm[tok_meta_pos((4 * hb + (tid & 3)) * 16 + slot)] = from_f32<META>(nrm_q[hb]);
+      for (int hb = 0; hb < NP / 4; ++hb)
+        s_norm[tok_meta_pos(pass(4 * hb + (tid & 3)) * 16 + slot)] = from_f32<META>(nrm_q[hb]);
     }
   } else if (cg == 0) {
 #pragma unroll
-    for (int p = 0; p < 8; ++p) s_norm[tok_meta_pos(p * 16 + slot)] = from_f32<META>(nrm[p]);
+    for (int p = 0; p < NP; ++p) s_norm[tok_meta_pos(pass(p) * 16 + slot)] = from_f32<META>(nrm[p]);
   }
   __syncthreads();
 
   // Eq. 3-4 parameters, once per channel and group: thread (slot < 8, cg) takes channel
   // 8*cg + slot, stores Delta and z (operand order, see kmeta_pos_of_chan) and leaves what
   // the coders need in LDS
-  if (slot < 8) {
+  if (tid < D) {
     const int e = slot, c = 8 * cg + e;
 #pragma unroll
     for (int gk = 0; gk < NGK; ++gk) {
       uint32_t mnw = 0, mxw = 0;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NW; ++w) {
         const uint32_t* rp = reinterpret_cast<const uint32_t*>(&s_red[gk][w][cg]);
         const uint32_t a = rp[e >> 1], bb = rp[4 + (e >> 1)];
         mnw = w == 0 ? a : pk_min_f16(mnw, a);
@@ -762,8 +824,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     }
     if (zp_min) {
 #pragma unroll
-      for (int p = gk * PPG; p < (gk + 1) * PPG; ++p)
-        key_codes<true, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, p * 16 + slot, cg);
+      for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+        key_codes<true, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
     } else {
       // a nearly constant channel far from zero has a huge integer zero-point: the wave then
       // packs from the codes themselves (rare; the choice is uniform over the wave)
@@ -772,12 +834,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
       for (int e = 0; e < 8; ++e) big |= fabsf(lo[e]) > kZeroPointFastBound;
       if (__any(big)) {
 #pragma unroll
-        for (int p = gk * PPG; p < (gk + 1) * PPG; ++p)
-          key_codes<false, BITS, true>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, p * 16 + slot, cg);
+        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+          key_codes<false, BITS, true>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
       } else {
 #pragma unroll
-        for (int p = gk * PPG; p < (gk + 1) * PPG; ++p)
-          key_codes<false, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, p * 16 + slot, cg);
+        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+          key_codes<false, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
       }
     }
   }
@@ -791,7 +853,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     const uint4* ksrc = reinterpret_cast<const uint4*>(&s_kimg[0]);
     uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
 #pragma unroll
-    for (int i = tid; i < NV; i += 256) kdst[i] = ksrc[i];
+    for (int i = tid; i < NV; i += NT) kdst[i] = ksrc[i];
   }
 #endif
 
@@ -801,9 +863,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
   // passes fill one byte (2-bit) / half-word (4-bit) of the piece, odd passes the other.
   {
     const int L = P.g.v_group / 8;  // lanes per value group: 4, 8 or 16
-    float vmn[8], vmx[8];
+    float vmn[NP], vmx[NP];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
+    for (int p = 0; p < NP; ++p) {
       float v[8];
       vraw[p].widen(v);
       const float mn = min_finite(min3_finite(min3_finite(v[0], v[1], v[2]), v[3], v[4]),
@@ -817,19 +879,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
       vmx[p] = rmx;
     }
     // The 4 lanes of a quad always share a value group: lane j of the quad works out the
-    // Eq. 3-4 parameters of passes 2j and 2j+1 and the quad reads them back by broadcast.
+    // Eq. 3-4 parameters of its share of the registers (2j and 2j+1 of 8, j of 4) and the quad
+    // reads them back by broadcast.
+    constexpr int PQ = NP / 4;
     const int qj = tid & 3;
-    float prd[2], plo[2], phi[2], pz[2];
+    float prd[PQ], plo[PQ], phi[PQ], pz[PQ];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float mn = qj == 0 ? vmn[i] : qj == 1 ? vmn[2 + i] : qj == 2 ? vmn[4 + i] : vmn[6 + i];
-      const float mx = qj == 0 ? vmx[i] : qj == 1 ? vmx[2 + i] : qj == 2 ? vmx[4 + i] : vmx[6 + i];
+    for (int i = 0; i < PQ; ++i) {
+      const float mn = qj == 0 ? vmn[i] : qj == 1 ? vmn[PQ + i] : qj == 2 ? vmn[2 * PQ + i] : vmn[3 * PQ + i];
+      const float mx = qj == 0 ? vmx[i] : qj == 1 ? vmx[PQ + i] : qj == 2 ? vmx[2 * PQ + i] : vmx[3 * PQ + i];
       float df;
       quant_params<META, BITS>(mn, mx, zp_min, df, prd[i], pz[i]);
       plo[i] = zp_min ? pz[i] : -pz[i];
       phi[i] = QMAX - pz[i];
       if ((cg & (L - 1) & ~3) == 0) {   // first quad of its value group stores the metadata
-        const int tok = (2 * qj + i) * 16 + slot, gv = cg >> (L == 4 ? 2 : L == 8 ? 3 : 4);
+        const int tok = pass(PQ * qj + i) * 16 + slot, gv = cg >> (L == 4 ? 2 : L == 8 ? 3 : 4);
         s_vmeta[0][gv][tok_meta_pos(tok)] = from_f32<META>(df);
         s_vmeta[1][gv][tok_meta_pos(tok)] = from_f32<META>(pz[i]);
       }
@@ -842,21 +906,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     auto code_values = [&](auto mode_tag) {
       constexpr int MODE = decltype(mode_tag)::value;
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
+      for (int p = 0; p < NP; ++p) {
         float v[8];
         vraw[p].widen(v);
-        const float rd = quad_bcast(prd[p & 1], p >> 1);
-        const float lo = quad_bcast(plo[p & 1], p >> 1);
-        const float hi = quad_bcast(phi[p & 1], p >> 1);
-        const float z = MODE == 0 ? quad_bcast(pz[p & 1], p >> 1) : 0.0f;
-        const float pl = place_value<BITS>(p >> 1);
+        const float rd = quad_bcast(prd[p % PQ], p / PQ);
+        const float lo = quad_bcast(plo[p % PQ], p / PQ);
+        const float hi = quad_bcast(phi[p % PQ], p / PQ);
+        const float z = MODE == 0 ? quad_bcast(pz[p % PQ], p / PQ) : 0.0f;
+        const float pl = place_value<BITS>(NP == 8 ? p >> 1 : p);
         float t[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           t[e] = MODE == 1   ? code_term<true, BITS>(v[e], rd, lo, hi)
                  : MODE == 2 ? code_exact<BITS>(v[e], rd, lo)
                              : code_term<false, BITS>(v[e], rd, lo, hi);
-        if ((p & 1) == 0) {
+        if (NP == 4 || (p & 1) == 0) {   // (NP = 4: wv0 is the thread group's half)
 #pragma unroll
           for (int e = 0; e < 8; ++e) wv0[e] = fmaf(t[e], pl, wv0[e]);
           zv0 = fmaf(z, pl, zv0);
@@ -869,7 +933,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     };
     if (zp_min) {
       code_values(std::integral_constant<int, 1>());
-    } else if (__any(fabsf(pz[0]) > kZeroPointFastBound || fabsf(pz[1]) > kZeroPointFastBound)) {
+    } else if (__any(fabsf(pz[0]) > kZeroPointFastBound || fabsf(pz[PQ - 1]) > kZeroPointFastBound)) {
       code_values(std::integral_constant<int, 2>());
     } else {
       code_values(std::integral_constant<int, 0>());
@@ -881,7 +945,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
       const uint32_t ev = (uint32_t)(wv0[e] + zv0), od = (uint32_t)(wv1[e] + zv1);
       const int lin = chunk_offset(BITS, c / 16, c % 16, q4);
       const int base = lin + (lin / (IMG / 8)) * 64;
-      if (BITS == 2) {
+      if (NP == 4) {
+        if (BITS == 2) s_vimg[base + (kk >> 1) * 4 + 2 * grp + (kk & 1)] = (uint8_t)ev;
+        else *reinterpret_cast<uint16_t*>(&s_vimg[base + kk * 4 + 2 * grp]) = (uint16_t)ev;
+      } else if (BITS == 2) {
         s_vimg[base + (kk >> 1) * 4 + (kk & 1)] = (uint8_t)ev;
         s_vimg[base + (kk >> 1) * 4 + 2 + (kk & 1)] = (uint8_t)od;
       } else {
@@ -899,7 +966,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
     uint4* vdst = reinterpret_cast<uint4*>(o_vcodes);
 #pragma unroll
-    for (int i = tid; i < NV; i += 256) {
+    for (int i = tid; i < NV; i += NT) {
 #if !OSCAR_ENC_EARLY_K
       kdst[i] = ksrc[i];
 #endif
@@ -934,7 +1001,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(IO) 
     }
     __syncthreads();
     if (s_last) {
-      for (int bb = tid; bb < P.c.batch; bb += 256) {
+      for (int bb = tid; bb < P.c.batch; bb += NT) {
         const SeqPlan q = plan_sequence(P, bb);
         if (q.n > 0 && q.ok) {
           P.c.seq_lens[bb] += q.n;
@@ -956,15 +1023,34 @@ __global__ void oscar_update_lens_kernel(AppendParams P) {
   P.c.res_lens[b] = sp.tail_len;
 }
 
-template <typename IO, typename META, int BITS, int XF>
-int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
+// Largest launch that takes the 512-thread form: what is resident at once on 256 CUs, two workgroups
+// a CU for the 16-bit input types and one for fp32 (registers).  Measured, the whole call in us, 256 / 512
+// threads: 2 sequences x 8 heads bf16 INT2, 500 new tokens behind 116 old ones (64 workgroups)
+// 11.4 / 9.1 (13.0 before the batched tail), 3072 tokens (400) 10.9 / 10.8, 4096 (528) 12.9 / 12.6,
+// 6144 (784) 17.0 / 19.2; 8 sequences INT4 G_k = 32, 500 tokens (256) 14.2 / 11.7, 2048 (1088)
+// 22.7 / 28.4; fp32, 2048 tokens (272) 13.1 / 9.8, 3072 (400) 14.3 / 19.4.
+template <typename IO> constexpr size_t small_grid_workgroups() { return sizeof(IO) == 4 ? 256 : 512; }
+
+template <typename IO, typename META, int BITS, int XF, int NP>
+int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
+  const dim3 block(2048 / NP);
   switch (P.g.k_group) {
-    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF>), grid, dim3(256), 0, st, P); break;
-    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF>), grid, dim3(256), 0, st, P); break;
-    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF>), grid, dim3(256), 0, st, P); break;
+    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF, NP>), grid, block, 0, st, P); break;
+    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF, NP>), grid, block, 0, st, P); break;
+    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF, NP>), grid, block, 0, st, P); break;
     default: return OSCAR_ERR_UNSUPPORTED;
   }
   return OSCAR_OK;
+}
+template <typename IO, typename META, int BITS, int XF>
+int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
+  // (the ablation switches keep the one form)
+  if constexpr (XF != XF_SWITCHED) {
+    // (a one-token append moves a page once in 128 calls; the rest of the time it is one token row)
+    if (P.T > 1 && (size_t)grid.x * grid.y * grid.z <= small_grid_workgroups<IO>())
+      return launch_np<IO, META, BITS, XF, 4>(P, grid, st);
+  }
+  return launch_np<IO, META, BITS, XF, 8>(P, grid, st);
 }
 
 template <typename IO, typename META, int XF>

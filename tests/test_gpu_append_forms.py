@@ -1,0 +1,48 @@
+"""Multi-token appends in the 512-thread form (small launches) and the 256-thread form of the
+encoder: block edges, tails, and blocks that mix the residual window with new tokens, bit for bit
+against the oracle, at launch sizes on both sides of the choice."""
+import numpy as np
+import pytest
+
+from paper_2605_19660_amd import synth
+from test_gpu_parity import _ob, make_pair, to_dev, assert_cache_equal
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("norm_all", [False, True])
+@pytest.mark.parametrize("zp", [0, 1])
+@pytest.mark.parametrize("io,meta,bits,kg,vg", [
+    ("bf16", "f16", 2, 128, 32), ("f16", "f16", 4, 32, 64), ("f32", "f32", 2, 64, 128),
+    ("f32", "f16", 4, 128, 32), ("bf16", "f32", 2, 32, 128), ("f16", "f32", 4, 64, 32),
+])
+def test_pieces_at_block_edges(io, meta, bits, kg, vg, zp, norm_all):
+    pieces = [2, 31, 33, 62, 127, 128, 129, 1, 160, 255, 257, 500, 3]
+    total = sum(pieces)
+    w = synth.LLAMA8B_32K.replace(batch=2, n_q_heads=4, n_kv_heads=2, context=total, io_dtype=io,
+                                  meta_dtype=meta, bits=bits, k_group=kg, v_group=vg)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, total // 128 + 2, zp_mode=zp, norm_scope=1 if norm_all else 0)
+    ob = _ob()
+    at = 0
+    for n in pieces:
+        kp, vp = np.ascontiguousarray(k[:, at:at + n]), np.ascontiguousarray(v[:, at:at + n])
+        ob.quantize_append(g, to_dev(kp, io), to_dev(vp, io), eager=True, max_seq_len_hint=at)
+        o.append(kp, vp, eager=True)
+        assert_cache_equal(g, o, w)
+        at += n
+    assert int(g.dev_status.item()) == 0
+
+
+@pytest.mark.parametrize("context", [128 * 3 + 70, 128 * 4])   # 32 x 4 and 32 x 5 x batch 4: 512, 640 workgroups
+def test_the_two_forms_meet_at_the_launch_size(context):
+    import torch
+    w = synth.LLAMA8B_32K.replace(batch=4, n_q_heads=32, n_kv_heads=32, context=context)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, 6)
+    lens = np.array([context, 127, 128, 300], np.int32)
+    ob = _ob()
+    ob.quantize_append(g, to_dev(k, w.io_dtype), to_dev(v, w.io_dtype), eager=True, max_seq_len_hint=0,
+                       new_lens=torch.from_numpy(lens).cuda())
+    o.append(k, v, eager=True, new_lens=lens)
+    assert_cache_equal(g, o, w)

@@ -26,6 +26,8 @@ SOURCES = {
     "oscar_decode_mfma_zpmin.hip": [],
     "oscar_decode_mfma_meta32.hip": [],
     "oscar_decode_mfma_meta32_zpmin.hip": [],
+    "oscar_decode_step.hip": [],
+    "oscar_decode_step_zpmin.hip": [],
     "oscar_bf16_decode.hip": [],
     "oscar_probe.hip": [],
 }

@@ -35,7 +35,7 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ("oscar_decode_mfma.hip", "oscar_decode_mfma_zpmin.hip", "oscar_decode_mfma_meta32.hip",
-           "oscar_decode_mfma_meta32_zpmin.hip")
+           "oscar_decode_mfma_meta32_zpmin.hip", "oscar_decode_step.hip", "oscar_decode_step_zpmin.hip")
 DPP_SOURCES = SOURCES + ("oscar_quantize.hip",)    # the encoder and the stand-alone rotations
 
 

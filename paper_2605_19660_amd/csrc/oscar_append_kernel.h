@@ -60,10 +60,11 @@ constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2;
 int oscar_launch_append_switched(const AppendParams& P, dim3 grid, hipStream_t st);
 int oscar_launch_append_all_heads(const AppendParams& P, dim3 grid, hipStream_t st);
 
-namespace {
+// (for the one user that is not compiled with -ffp-contract=off, the fused decode step; it switches
+// contraction back on behind this header)
+#pragma clang fp contract(off)
 
-constexpr int D = OSCAR_D;
-constexpr int R = OSCAR_R;
+namespace {
 
 // 16 bytes of the caller's K / V, which this launch reads exactly once: a non-temporal load
 // (measured on a kernel that only moves the encoder's bytes in the encoder's pattern: 223 us
@@ -475,6 +476,296 @@ __device__ __forceinline__ void key_codes(const uint4& ku, const float (&rd)[8],
   }
 }
 
+// What a workgroup of the encoder keeps in LDS.
+template <typename META, int BITS, int KG, int NP> struct EncoderLds {
+  static constexpr int NGK = R / KG, NW = 2048 / NP / 64, IMG = R * D * BITS / 8;
+  struct MinMax {
+    uint4 mn, mx;   // packed fp16, the 8 channels of a channel group
+  };
+  alignas(16) MinMax red[NGK][NW][16];   // [group][wave][channel group]
+  // per channel: 1/Delta, -z, qmax-z, z*place; channel 8*cg + e sits at slot 16*e + cg, so the
+  // 16 lanes of a row (cg = 0..15) read 256 consecutive bytes (channel order would put them
+  // 128 bytes apart: an 8-way bank conflict on every read)
+  alignas(16) float4 par[NGK][D];
+  alignas(16) uint8_t kimg[IMG];        // key-code page image
+  // value-code page image, staged with 64 bytes of padding after every eighth of the image:
+  // the lanes of a wave write pieces that are 1/8, 1/4 and 1/2 image apart, which would
+  // otherwise all fall into the same 8 LDS banks
+  alignas(16) uint8_t vimg[IMG + 8 * 64];
+  alignas(16) META vmeta[2][4][R];
+  alignas(16) META norm[R];
+};
+
+// Phases 3 and 4 of the encoder: the block of 128 tokens held in registers (keys as packed fp16 K_u,
+// values raw; register i of a thread is token 16 * pass(i) + slot) goes into page `pg` of the pools
+// (physical page * kv heads + kv head).  The whole workgroup of 2048 / NP threads takes part.
+template <typename META, int BITS, int KG, int NP, typename VRAW>
+__device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s, const uint4 (&ku)[NP],
+                                               const VRAW (&vraw)[NP], bool batched_norms, const float (&nrm)[NP],
+                                               const float (&nrm_q)[NP / 4], const oscar_cache& c, const PageGeom& g,
+                                               size_t pg, bool zp_min, int tid, int cg) {
+  constexpr int NGK = R / KG;             // key groups per page
+  constexpr int RPG = KG / 16 * NP / 8;   // registers (a thread's tokens) per key group
+  constexpr int NT = 2048 / NP, NW = NT / 64;
+  constexpr float QMAX = (float)((1 << BITS) - 1);
+  constexpr int IMG = R * D * BITS / 8;   // bytes of one code image
+  const int wave = tid >> 6, lane = tid & 63;
+  const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;
+  const int grp = NP == 8 ? 0 : tid >> 8;
+  auto pass = [&](int i) { return NP == 8 ? i : 2 * i + grp; };
+  uint8_t* o_kcodes = reinterpret_cast<uint8_t*>(c.k_codes) + pg * g.k_codes_bytes;
+  META* o_kmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.k_meta) + pg * g.k_meta_bytes);
+  META* o_knorm = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.k_norms) + pg * g.k_norms_bytes);
+  uint8_t* o_vcodes = reinterpret_cast<uint8_t*>(c.v_codes) + pg * g.v_codes_bytes;
+  META* o_vmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.v_meta) + pg * g.v_meta_bytes);
+
+  // keys: per-channel min/max over the tokens of each group: passes, then the 4 token rows
+  // of the wave, then (through LDS) the 4 waves
+#pragma unroll
+  for (int gk = 0; gk < NGK; ++gk) {
+    uint32_t mn[4] = {ku[gk * RPG].x, ku[gk * RPG].y, ku[gk * RPG].z, ku[gk * RPG].w};
+    uint32_t mx[4] = {mn[0], mn[1], mn[2], mn[3]};
+#pragma unroll
+    for (int p = 1; p < RPG; ++p) {
+      const uint4 q = ku[gk * RPG + p];
+      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        mn[j] = pk_min_f16(mn[j], w[j]);
+        mx[j] = pk_max_f16(mx[j], w[j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 16, 64));
+      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 16, 64));
+      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 32, 64));
+      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 32, 64));
+    }
+    if (lane < 16) {
+      s.red[gk][wave][cg].mn = make_uint4(mn[0], mn[1], mn[2], mn[3]);
+      s.red[gk][wave][cg].mx = make_uint4(mx[0], mx[1], mx[2], mx[3]);
+    }
+  }
+  if (batched_norms) {
+    if ((tid & 15) < 4) {   // first quad of the token row: lane j holds the norms of registers j, 4 + j
+#pragma unroll
+      for (int hb = 0; hb < NP / 4; ++hb)
+        s.norm[tok_meta_pos(pass(4 * hb + (tid & 3)) * 16 + slot)] = from_f32<META>(nrm_q[hb]);
+    }
+  } else if (cg == 0) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) s.norm[tok_meta_pos(pass(p) * 16 + slot)] = from_f32<META>(nrm[p]);
+  }
+  __syncthreads();
+
+  // Eq. 3-4 parameters, once per channel and group: thread (slot < 8, cg) takes channel
+  // 8*cg + slot, stores Delta and z (operand order, see kmeta_pos_of_chan) and leaves what
+  // the coders need in LDS
+  if (tid < D) {
+    const int e = slot, ch = 8 * cg + e;
+#pragma unroll
+    for (int gk = 0; gk < NGK; ++gk) {
+      uint32_t mnw = 0, mxw = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t* rp = reinterpret_cast<const uint32_t*>(&s.red[gk][w][cg]);
+        const uint32_t a = rp[e >> 1], bb = rp[4 + (e >> 1)];
+        mnw = w == 0 ? a : pk_min_f16(mnw, a);
+        mxw = w == 0 ? bb : pk_max_f16(mxw, bb);
+      }
+      float df, rd, z;
+      quant_params<META, BITS>(half_of(mnw, e & 1), half_of(mxw, e & 1), zp_min, df, rd, z);
+      // place value of this channel's code inside its packed word (4-bit: two 16-bit halves)
+      const float place = ldexpf(1.0f, BITS * ((BITS == 2) ? e : (e & 3)));
+      s.par[gk][16 * e + cg] = zp_min ? make_float4(rd, z, 0.0f, 0.0f)
+                            : make_float4(rd, -z, QMAX - z, z * place);
+      const int pos = kmeta_pos_of_chan(BITS, ch);
+      o_kmeta[(size_t)gk * D + pos] = from_f32<META>(df);
+      o_kmeta[(size_t)(NGK + gk) * D + pos] = from_f32<META>(z);
+    }
+  }
+  __syncthreads();
+
+  // key codes: a token's 8 codes of this channel group form one 16-bit (2-bit codes) or
+  // 32-bit (4-bit codes) piece of chunk (tile = tok/16, n = tok%16, q4 = cg/4)
+#pragma unroll
+  for (int gk = 0; gk < NGK; ++gk) {
+    float rd[8], lo[8], hi[8], zs0 = 0.0f, zs1 = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float4 q = s.par[gk][16 * e + cg];
+      rd[e] = q.x;
+      lo[e] = q.y;
+      hi[e] = q.z;
+      if (BITS == 2 || e < 4) zs0 += q.w;
+      else zs1 += q.w;
+    }
+    if (zp_min) {
+#pragma unroll
+      for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+        key_codes<true, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s.kimg, pass(p) * 16 + slot, cg);
+    } else {
+      // a nearly constant channel far from zero has a huge integer zero-point: the wave then
+      // packs from the codes themselves (rare; the choice is uniform over the wave)
+      bool big = false;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) big |= fabsf(lo[e]) > kZeroPointFastBound;
+      if (__any(big)) {
+#pragma unroll
+        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+          key_codes<false, BITS, true>(ku[p], rd, lo, hi, zs0, zs1, s.kimg, pass(p) * 16 + slot, cg);
+      } else {
+#pragma unroll
+        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
+          key_codes<false, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s.kimg, pass(p) * 16 + slot, cg);
+      }
+    }
+  }
+
+#if OSCAR_ENC_EARLY_K
+  // the key-code image is complete: it leaves now, under the value phase, instead of with
+  // everything else at the end of the workgroup (one more barrier)
+  __syncthreads();
+  {
+    constexpr int NV = IMG / 16;
+    const uint4* ksrc = reinterpret_cast<const uint4*>(&s.kimg[0]);
+    uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
+#pragma unroll
+    for (int i = tid; i < NV; i += NT) kdst[i] = ksrc[i];
+  }
+#endif
+
+  // values: per-token min/max over each group of v_group channels (8 registers, then the
+  // 4 | 8 | 16 lanes of the group).  The thread's 8 tokens of one channel are the elements
+  // e = pass of k-step kk = slot/4 in chunk (tile = c/16, n = c%16, q4 = slot%4): even
+  // passes fill one byte (2-bit) / half-word (4-bit) of the piece, odd passes the other.
+  {
+    const int L = g.v_group / 8;  // lanes per value group: 4, 8 or 16
+    float vmn[NP], vmx[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      float v[8];
+      vraw[p].widen(v);
+      const float mn = min_finite(min3_finite(min3_finite(v[0], v[1], v[2]), v[3], v[4]),
+                                  min3_finite(v[5], v[6], v[7]));
+      const float mx = max_finite(max3_finite(max3_finite(v[0], v[1], v[2]), v[3], v[4]),
+                                  max3_finite(v[5], v[6], v[7]));
+      float rmn = partner_min<1>(partner_min<0>(mn)), rmx = partner_max<1>(partner_max<0>(mx));
+      if (L > 4) { rmn = partner_min<2>(rmn); rmx = partner_max<2>(rmx); }
+      if (L > 8) { rmn = partner_min<3>(rmn); rmx = partner_max<3>(rmx); }
+      vmn[p] = rmn;
+      vmx[p] = rmx;
+    }
+    // The 4 lanes of a quad always share a value group: lane j of the quad works out the
+    // Eq. 3-4 parameters of its share of the registers (2j and 2j+1 of 8, j of 4) and the quad
+    // reads them back by broadcast.
+    constexpr int PQ = NP / 4;
+    const int qj = tid & 3;
+    float prd[PQ], plo[PQ], phi[PQ], pz[PQ];
+#pragma unroll
+    for (int i = 0; i < PQ; ++i) {
+      const float mn = qj == 0 ? vmn[i] : qj == 1 ? vmn[PQ + i] : qj == 2 ? vmn[2 * PQ + i] : vmn[3 * PQ + i];
+      const float mx = qj == 0 ? vmx[i] : qj == 1 ? vmx[PQ + i] : qj == 2 ? vmx[2 * PQ + i] : vmx[3 * PQ + i];
+      float df;
+      quant_params<META, BITS>(mn, mx, zp_min, df, prd[i], pz[i]);
+      plo[i] = zp_min ? pz[i] : -pz[i];
+      phi[i] = QMAX - pz[i];
+      if ((cg & (L - 1) & ~3) == 0) {   // first quad of its value group stores the metadata
+        const int tok = pass(PQ * qj + i) * 16 + slot, gv = cg >> (L == 4 ? 2 : L == 8 ? 3 : 4);
+        s.vmeta[0][gv][tok_meta_pos(tok)] = from_f32<META>(df);
+        s.vmeta[1][gv][tok_meta_pos(tok)] = from_f32<META>(pz[i]);
+      }
+    }
+    float wv0[8], wv1[8], zv0 = 0.0f, zv1 = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) wv0[e] = wv1[e] = 0.0f;
+    // mode 0: integer zero-point, (code - z) form; 1: float zero-point; 2: integer zero-point
+    // past kZeroPointFastBound somewhere in the wave, the codes themselves
+    auto code_values = [&](auto mode_tag) {
+      constexpr int MODE = decltype(mode_tag)::value;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        float v[8];
+        vraw[p].widen(v);
+        const float rd = quad_bcast(prd[p % PQ], p / PQ);
+        const float lo = quad_bcast(plo[p % PQ], p / PQ);
+        const float hi = quad_bcast(phi[p % PQ], p / PQ);
+        const float z = MODE == 0 ? quad_bcast(pz[p % PQ], p / PQ) : 0.0f;
+        const float pl = place_value<BITS>(NP == 8 ? p >> 1 : p);
+        float t[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          t[e] = MODE == 1   ? code_term<true, BITS>(v[e], rd, lo, hi)
+                 : MODE == 2 ? code_exact<BITS>(v[e], rd, lo)
+                             : code_term<false, BITS>(v[e], rd, lo, hi);
+        if (NP == 4 || (p & 1) == 0) {   // (NP = 4: wv0 is the thread group's half)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) wv0[e] = fmaf(t[e], pl, wv0[e]);
+          zv0 = fmaf(z, pl, zv0);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) wv1[e] = fmaf(t[e], pl, wv1[e]);
+          zv1 = fmaf(z, pl, zv1);
+        }
+      }
+    };
+    if (zp_min) {
+      code_values(std::integral_constant<int, 1>());
+    } else if (__any(fabsf(pz[0]) > kZeroPointFastBound || fabsf(pz[PQ - 1]) > kZeroPointFastBound)) {
+      code_values(std::integral_constant<int, 2>());
+    } else {
+      code_values(std::integral_constant<int, 0>());
+    }
+    const int kk = slot >> 2, q4 = slot & 3;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int ch = 8 * cg + e;
+      const uint32_t ev = (uint32_t)(wv0[e] + zv0), od = (uint32_t)(wv1[e] + zv1);
+      const int lin = chunk_offset(BITS, ch / 16, ch % 16, q4);
+      const int base = lin + (lin / (IMG / 8)) * 64;
+      if (NP == 4) {
+        if (BITS == 2) s.vimg[base + (kk >> 1) * 4 + 2 * grp + (kk & 1)] = (uint8_t)ev;
+        else *reinterpret_cast<uint16_t*>(&s.vimg[base + kk * 4 + 2 * grp]) = (uint16_t)ev;
+      } else if (BITS == 2) {
+        s.vimg[base + (kk >> 1) * 4 + (kk & 1)] = (uint8_t)ev;
+        s.vimg[base + (kk >> 1) * 4 + 2 + (kk & 1)] = (uint8_t)od;
+      } else {
+        *reinterpret_cast<uint32_t*>(&s.vimg[base + kk * 4]) = ev | (od << 16);
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- phase 4: coalesced page stores ----
+  {
+    constexpr int NV = IMG / 16;  // uint4 count: 256 (2-bit) or 512 (4-bit)
+    const uint4* ksrc = reinterpret_cast<const uint4*>(&s.kimg[0]);
+    const uint4* vsrc = reinterpret_cast<const uint4*>(&s.vimg[0]);
+    uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
+    uint4* vdst = reinterpret_cast<uint4*>(o_vcodes);
+#pragma unroll
+    for (int i = tid; i < NV; i += NT) {
+#if !OSCAR_ENC_EARLY_K
+      kdst[i] = ksrc[i];
+#endif
+      vdst[i] = vsrc[i + (i / (NV / 8)) * 4];   // un-pad: 4 x 16 bytes per eighth
+    }
+  }
+  {
+    // value metadata image: Delta[ngv][R] then zero[ngv][R], 16 bytes per thread (each plane of
+    // the staging array holds 4 groups, of which the first ngv are in use)
+    const int per16 = g.ngv * R * (int)sizeof(META) / 16;   // 16-byte pieces of a plane: <= 128
+    if (tid < 2 * per16) {
+      const int plane = tid >= per16 ? 1 : 0, idx = tid - plane * per16;
+      reinterpret_cast<uint4*>(o_vmeta)[plane * per16 + idx] =
+          reinterpret_cast<const uint4*>(&s.vmeta[plane][0][0])[idx];
+    }
+    if (tid < R * (int)sizeof(META) / 16)
+      reinterpret_cast<uint4*>(o_knorm)[tid] = reinterpret_cast<const uint4*>(&s.norm[0])[tid];
+  }
+}
+
 // NP = tokens per thread.  8: 256 threads a workgroup, four workgroups a CU, the form for launches
 // that fill the chip.  4: 512 threads, half the work per thread, for launches that do not (see
 // launch_kg): there a workgroup's own latency is the time, and it is issue-bound at one wave a SIMD.
@@ -483,31 +774,12 @@ __device__ __forceinline__ void key_codes(const uint4& ku, const float (&rd)[8],
 template <typename IO, typename META, int BITS, int KG, int XF, int NP>
 __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF == 2 ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
   constexpr bool NORM_ALL = XF == XF_ALL_HEADS;
-  constexpr int NGK = R / KG;        // key groups per page
-  constexpr int RPG = KG / 16 * NP / 8;   // registers (a thread's tokens) per key group
-  constexpr int NT = 2048 / NP, NW = NT / 64, ROWS = NT / 16;   // threads, waves, token rows
-  constexpr float QMAX = (float)((1 << BITS) - 1);
-  constexpr int IMG = R * D * BITS / 8;   // bytes of one code image
-
-  struct MinMax {
-    uint4 mn, mx;   // packed fp16, the 8 channels of a channel group
-  };
-  __shared__ __align__(16) MinMax s_red[NGK][NW][16];   // [group][wave][channel group]
-  // per channel: 1/Delta, -z, qmax-z, z*place; channel 8*cg + e sits at slot 16*e + cg, so the
-  // 16 lanes of a row (cg = 0..15) read 256 consecutive bytes (channel order would put them
-  // 128 bytes apart: an 8-way bank conflict on every read)
-  __shared__ __align__(16) float4 s_par[NGK][D];
-  __shared__ __align__(16) uint8_t s_kimg[IMG];        // key-code page image
-  // value-code page image, staged with 64 bytes of padding after every eighth of the image:
-  // the lanes of a wave write pieces that are 1/8, 1/4 and 1/2 image apart, which would
-  // otherwise all fall into the same 8 LDS banks
-  __shared__ __align__(16) uint8_t s_vimg[IMG + 8 * 64];
-  __shared__ __align__(16) META s_vmeta[2][4][R];
-  __shared__ __align__(16) META s_norm[R];
+  constexpr int NT = 2048 / NP, ROWS = NT / 16;   // threads, token rows
+  __shared__ EncoderLds<META, BITS, KG, NP> s;
 
   // kv head fastest: the workgroups that share a token block's rows in memory run together
   const int b = blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x;
   const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;  // token of a pass
   const int grp = NP == 8 ? 0 : tid >> 8;               // thread group
   // register i of a thread holds token 16 * pass(i) + slot of the block
@@ -549,7 +821,7 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   // batched_norms (uniform over the workgroup): the norms of tokens 16*pass(4*hb + j) + slot sit in
   // nrm_q[hb] of the lanes whose position in their quad is j, and nrm[] is unused
   bool batched_norms = false;
-  float nrm_q[2] = {0.0f, 0.0f};
+  float nrm_q[NP / 4] = {};
   // NORM_ALL: the norms of new tokens that end up in a page were written into that page's
   // norm slots (of every head) by oscar_token_norm_kernel, launched just before this kernel
   const META* pre_norm = nullptr;
@@ -732,259 +1004,8 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   }
   if (!do_block) break;
 
-  // ---- phase 3: quantize the block held in registers ----
-  const size_t pg = (size_t)phys * Hkv + kvh;
-  uint8_t* o_kcodes = reinterpret_cast<uint8_t*>(P.c.k_codes) + pg * P.g.k_codes_bytes;
-  META* o_kmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(P.c.k_meta) + pg * P.g.k_meta_bytes);
-  META* o_knorm = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(P.c.k_norms) + pg * P.g.k_norms_bytes);
-  uint8_t* o_vcodes = reinterpret_cast<uint8_t*>(P.c.v_codes) + pg * P.g.v_codes_bytes;
-  META* o_vmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(P.c.v_meta) + pg * P.g.v_meta_bytes);
-
-  // keys: per-channel min/max over the tokens of each group: passes, then the 4 token rows
-  // of the wave, then (through LDS) the 4 waves
-#pragma unroll
-  for (int gk = 0; gk < NGK; ++gk) {
-    uint32_t mn[4] = {ku[gk * RPG].x, ku[gk * RPG].y, ku[gk * RPG].z, ku[gk * RPG].w};
-    uint32_t mx[4] = {mn[0], mn[1], mn[2], mn[3]};
-#pragma unroll
-    for (int p = 1; p < RPG; ++p) {
-      const uint4 q = ku[gk * RPG + p];
-      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        mn[j] = pk_min_f16(mn[j], w[j]);
-        mx[j] = pk_max_f16(mx[j], w[j]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 16, 64));
-      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 16, 64));
-      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 32, 64));
-      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 32, 64));
-    }
-    if (lane < 16) {
-      s_red[gk][wave][cg].mn = make_uint4(mn[0], mn[1], mn[2], mn[3]);
-      s_red[gk][wave][cg].mx = make_uint4(mx[0], mx[1], mx[2], mx[3]);
-    }
-  }
-  if (batched_norms) {
-    if ((tid & 15) < 4) {   // first quad of the token row: lane j holds the norms of registers j, 4 + j
-#pragma unroll
-      for (int hb = 0; hb < NP / 4; ++hb)
-        s_norm[tok_meta_pos(pass(4 * hb + (tid & 3)) * 16 + slot)] = from_f32<META>(nrm_q[hb]);
-    }
-  } else if (cg == 0) {
-#pragma unroll
-    for (int p = 0; p < NP; ++p) s_norm[tok_meta_pos(pass(p) * 16 + slot)] = from_f32<META>(nrm[p]);
-  }
-  __syncthreads();
-
-  // Eq. 3-4 parameters, once per channel and group: thread (slot < 8, cg) takes channel
-  // 8*cg + slot, stores Delta and z (operand order, see kmeta_pos_of_chan) and leaves what
-  // the coders need in LDS
-  if (tid < D) {
-    const int e = slot, c = 8 * cg + e;
-#pragma unroll
-    for (int gk = 0; gk < NGK; ++gk) {
-      uint32_t mnw = 0, mxw = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const uint32_t* rp = reinterpret_cast<const uint32_t*>(&s_red[gk][w][cg]);
-        const uint32_t a = rp[e >> 1], bb = rp[4 + (e >> 1)];
-        mnw = w == 0 ? a : pk_min_f16(mnw, a);
-        mxw = w == 0 ? bb : pk_max_f16(mxw, bb);
-      }
-      float df, rd, z;
-      quant_params<META, BITS>(half_of(mnw, e & 1), half_of(mxw, e & 1), zp_min, df, rd, z);
-      // place value of this channel's code inside its packed word (4-bit: two 16-bit halves)
-      const float place = ldexpf(1.0f, BITS * ((BITS == 2) ? e : (e & 3)));
-      s_par[gk][16 * e + cg] = zp_min ? make_float4(rd, z, 0.0f, 0.0f)
-                            : make_float4(rd, -z, QMAX - z, z * place);
-      const int pos = kmeta_pos_of_chan(BITS, c);
-      o_kmeta[(size_t)gk * D + pos] = from_f32<META>(df);
-      o_kmeta[(size_t)(NGK + gk) * D + pos] = from_f32<META>(z);
-    }
-  }
-  __syncthreads();
-
-  // key codes: a token's 8 codes of this channel group form one 16-bit (2-bit codes) or
-  // 32-bit (4-bit codes) piece of chunk (tile = tok/16, n = tok%16, q4 = cg/4)
-#pragma unroll
-  for (int gk = 0; gk < NGK; ++gk) {
-    float rd[8], lo[8], hi[8], zs0 = 0.0f, zs1 = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float4 q = s_par[gk][16 * e + cg];
-      rd[e] = q.x;
-      lo[e] = q.y;
-      hi[e] = q.z;
-      if (BITS == 2 || e < 4) zs0 += q.w;
-      else zs1 += q.w;
-    }
-    if (zp_min) {
-#pragma unroll
-      for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
-        key_codes<true, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
-    } else {
-      // a nearly constant channel far from zero has a huge integer zero-point: the wave then
-      // packs from the codes themselves (rare; the choice is uniform over the wave)
-      bool big = false;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) big |= fabsf(lo[e]) > kZeroPointFastBound;
-      if (__any(big)) {
-#pragma unroll
-        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
-          key_codes<false, BITS, true>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
-      } else {
-#pragma unroll
-        for (int p = gk * RPG; p < (gk + 1) * RPG; ++p)
-          key_codes<false, BITS, false>(ku[p], rd, lo, hi, zs0, zs1, s_kimg, pass(p) * 16 + slot, cg);
-      }
-    }
-  }
-
-#if OSCAR_ENC_EARLY_K
-  // the key-code image is complete: it leaves now, under the value phase, instead of with
-  // everything else at the end of the workgroup (one more barrier)
-  __syncthreads();
-  {
-    constexpr int NV = IMG / 16;
-    const uint4* ksrc = reinterpret_cast<const uint4*>(&s_kimg[0]);
-    uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
-#pragma unroll
-    for (int i = tid; i < NV; i += NT) kdst[i] = ksrc[i];
-  }
-#endif
-
-  // values: per-token min/max over each group of v_group channels (8 registers, then the
-  // 4 | 8 | 16 lanes of the group).  The thread's 8 tokens of one channel are the elements
-  // e = pass of k-step kk = slot/4 in chunk (tile = c/16, n = c%16, q4 = slot%4): even
-  // passes fill one byte (2-bit) / half-word (4-bit) of the piece, odd passes the other.
-  {
-    const int L = P.g.v_group / 8;  // lanes per value group: 4, 8 or 16
-    float vmn[NP], vmx[NP];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      float v[8];
-      vraw[p].widen(v);
-      const float mn = min_finite(min3_finite(min3_finite(v[0], v[1], v[2]), v[3], v[4]),
-                                  min3_finite(v[5], v[6], v[7]));
-      const float mx = max_finite(max3_finite(max3_finite(v[0], v[1], v[2]), v[3], v[4]),
-                                  max3_finite(v[5], v[6], v[7]));
-      float rmn = partner_min<1>(partner_min<0>(mn)), rmx = partner_max<1>(partner_max<0>(mx));
-      if (L > 4) { rmn = partner_min<2>(rmn); rmx = partner_max<2>(rmx); }
-      if (L > 8) { rmn = partner_min<3>(rmn); rmx = partner_max<3>(rmx); }
-      vmn[p] = rmn;
-      vmx[p] = rmx;
-    }
-    // The 4 lanes of a quad always share a value group: lane j of the quad works out the
-    // Eq. 3-4 parameters of its share of the registers (2j and 2j+1 of 8, j of 4) and the quad
-    // reads them back by broadcast.
-    constexpr int PQ = NP / 4;
-    const int qj = tid & 3;
-    float prd[PQ], plo[PQ], phi[PQ], pz[PQ];
-#pragma unroll
-    for (int i = 0; i < PQ; ++i) {
-      const float mn = qj == 0 ? vmn[i] : qj == 1 ? vmn[PQ + i] : qj == 2 ? vmn[2 * PQ + i] : vmn[3 * PQ + i];
-      const float mx = qj == 0 ? vmx[i] : qj == 1 ? vmx[PQ + i] : qj == 2 ? vmx[2 * PQ + i] : vmx[3 * PQ + i];
-      float df;
-      quant_params<META, BITS>(mn, mx, zp_min, df, prd[i], pz[i]);
-      plo[i] = zp_min ? pz[i] : -pz[i];
-      phi[i] = QMAX - pz[i];
-      if ((cg & (L - 1) & ~3) == 0) {   // first quad of its value group stores the metadata
-        const int tok = pass(PQ * qj + i) * 16 + slot, gv = cg >> (L == 4 ? 2 : L == 8 ? 3 : 4);
-        s_vmeta[0][gv][tok_meta_pos(tok)] = from_f32<META>(df);
-        s_vmeta[1][gv][tok_meta_pos(tok)] = from_f32<META>(pz[i]);
-      }
-    }
-    float wv0[8], wv1[8], zv0 = 0.0f, zv1 = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) wv0[e] = wv1[e] = 0.0f;
-    // mode 0: integer zero-point, (code - z) form; 1: float zero-point; 2: integer zero-point
-    // past kZeroPointFastBound somewhere in the wave, the codes themselves
-    auto code_values = [&](auto mode_tag) {
-      constexpr int MODE = decltype(mode_tag)::value;
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        float v[8];
-        vraw[p].widen(v);
-        const float rd = quad_bcast(prd[p % PQ], p / PQ);
-        const float lo = quad_bcast(plo[p % PQ], p / PQ);
-        const float hi = quad_bcast(phi[p % PQ], p / PQ);
-        const float z = MODE == 0 ? quad_bcast(pz[p % PQ], p / PQ) : 0.0f;
-        const float pl = place_value<BITS>(NP == 8 ? p >> 1 : p);
-        float t[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          t[e] = MODE == 1   ? code_term<true, BITS>(v[e], rd, lo, hi)
-                 : MODE == 2 ? code_exact<BITS>(v[e], rd, lo)
-                             : code_term<false, BITS>(v[e], rd, lo, hi);
-        if (NP == 4 || (p & 1) == 0) {   // (NP = 4: wv0 is the thread group's half)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) wv0[e] = fmaf(t[e], pl, wv0[e]);
-          zv0 = fmaf(z, pl, zv0);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) wv1[e] = fmaf(t[e], pl, wv1[e]);
-          zv1 = fmaf(z, pl, zv1);
-        }
-      }
-    };
-    if (zp_min) {
-      code_values(std::integral_constant<int, 1>());
-    } else if (__any(fabsf(pz[0]) > kZeroPointFastBound || fabsf(pz[PQ - 1]) > kZeroPointFastBound)) {
-      code_values(std::integral_constant<int, 2>());
-    } else {
-      code_values(std::integral_constant<int, 0>());
-    }
-    const int kk = slot >> 2, q4 = slot & 3;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int c = 8 * cg + e;
-      const uint32_t ev = (uint32_t)(wv0[e] + zv0), od = (uint32_t)(wv1[e] + zv1);
-      const int lin = chunk_offset(BITS, c / 16, c % 16, q4);
-      const int base = lin + (lin / (IMG / 8)) * 64;
-      if (NP == 4) {
-        if (BITS == 2) s_vimg[base + (kk >> 1) * 4 + 2 * grp + (kk & 1)] = (uint8_t)ev;
-        else *reinterpret_cast<uint16_t*>(&s_vimg[base + kk * 4 + 2 * grp]) = (uint16_t)ev;
-      } else if (BITS == 2) {
-        s_vimg[base + (kk >> 1) * 4 + (kk & 1)] = (uint8_t)ev;
-        s_vimg[base + (kk >> 1) * 4 + 2 + (kk & 1)] = (uint8_t)od;
-      } else {
-        *reinterpret_cast<uint32_t*>(&s_vimg[base + kk * 4]) = ev | (od << 16);
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- phase 4: coalesced page stores ----
-  {
-    constexpr int NV = IMG / 16;  // uint4 count: 256 (2-bit) or 512 (4-bit)
-    const uint4* ksrc = reinterpret_cast<const uint4*>(&s_kimg[0]);
-    const uint4* vsrc = reinterpret_cast<const uint4*>(&s_vimg[0]);
-    uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
-    uint4* vdst = reinterpret_cast<uint4*>(o_vcodes);
-#pragma unroll
-    for (int i = tid; i < NV; i += NT) {
-#if !OSCAR_ENC_EARLY_K
-      kdst[i] = ksrc[i];
-#endif
-      vdst[i] = vsrc[i + (i / (NV / 8)) * 4];   // un-pad: 4 x 16 bytes per eighth
-    }
-  }
-  {
-    // value metadata image: Delta[ngv][R] then zero[ngv][R], 16 bytes per thread (each plane of
-    // the staging array holds 4 groups, of which the first ngv are in use)
-    const int per16 = P.g.ngv * R * (int)sizeof(META) / 16;   // 16-byte pieces of a plane: <= 128
-    if (tid < 2 * per16) {
-      const int plane = tid >= per16 ? 1 : 0, idx = tid - plane * per16;
-      reinterpret_cast<uint4*>(o_vmeta)[plane * per16 + idx] =
-          reinterpret_cast<const uint4*>(&s_vmeta[plane][0][0])[idx];
-    }
-    if (tid < R * (int)sizeof(META) / 16)
-      reinterpret_cast<uint4*>(o_knorm)[tid] = reinterpret_cast<const uint4*>(&s_norm[0])[tid];
-  }
+  quantize_block<META, BITS, KG, NP>(s, ku, vraw, batched_norms, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
+                                     zp_min, tid, cg);
   } while (false);
 
   // ---- length update, folded in: the last workgroup to finish advances the lengths of all

@@ -21,8 +21,6 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-
-constexpr int D = OSCAR_D;
 constexpr int WS_STRIDE = D + 2;
 constexpr int TOK_STEP = 4;   // tokens per row and step
 

@@ -14,6 +14,11 @@
 #define OSCAR_R 128   // page size / residual length built
 #define OSCAR_MAX_GQA 8
 
+namespace {
+constexpr int D = OSCAR_D;
+constexpr int R = OSCAR_R;
+}  // namespace
+
 // ---- page geometry (bytes per page of one kv head) -------------------------
 struct PageGeom {
   int bits, k_group, v_group, meta_bytes;
@@ -148,8 +153,17 @@ struct oscar_timer {
 };
 
 // Reduce pass of split-K decode (defined with the decode kernels).
+// lens: the lengths a fused decode step still has to advance (none by default).
+struct StepLens {
+  int32_t *seq_lens = nullptr, *res_lens = nullptr;
+  int max_pages_per_seq = 0;
+};
 void oscar_launch_decode_reduce(const float* ws, void* out, int num_splits, int out_dtype,
-                                int n_q_heads, int batch, hipStream_t st);
+                                int n_q_heads, int batch, hipStream_t st, StepLens lens = StepLens());
+
+// The argument checks of oscar_quantize_append.
+int oscar_check_append(const void* k, const void* v, int32_t T, const oscar_cache* cache,
+                       int32_t max_seq_len_hint, uint32_t flags);
 
 // Matrix-core partial pass (params = the decode parameter block); returns
 // OSCAR_ERR_UNSUPPORTED when the configuration must take the generic kernel.
@@ -165,6 +179,9 @@ __host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp,
 }
 int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
                              hipEvent_t e0, hipEvent_t e1);
+// The same with the step's new token appended on the way (params->k_new, v_new).
+int oscar_launch_decode_step_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
+                                  hipEvent_t e0, hipEvent_t e1);
 
 #define OSCAR_HIP_CHECK(expr)                 \
   do {                                        \

@@ -307,8 +307,12 @@ __global__ __launch_bounds__(256) void oscar_decode_partial_kernel(DecodeParams 
 // (o_s, m_s, l_s) with M = max m_s, out = sum o_s 2^(m_s-M) / sum l_s 2^(m_s-M).
 // One block of 128 threads per (sequence, query head); the split statistics are fetched
 // by one thread each, so no thread walks a chain of dependent loads.
-__global__ __launch_bounds__(128) void oscar_decode_reduce_kernel(const float* ws, void* out,
-                                                                  int num_splits, int out_dtype) {
+// lens: of a fused decode step, whose lengths one thread per sequence advances here, where nothing
+// else reads them (null pointers otherwise).
+__global__ __launch_bounds__(128) void oscar_decode_reduce_kernel(const float* ws, void* out, int num_splits,
+                                                                  int out_dtype, StepLens lens) {
+  if (lens.seq_lens && blockIdx.x == 0 && threadIdx.x == 0)
+    advance_lengths(lens.seq_lens, lens.res_lens, blockIdx.y, lens.max_pages_per_seq);
   __shared__ float s_w[512];   // weight of each split (num_splits <= 512)
   __shared__ float s_red[4];
   const size_t unit = (size_t)blockIdx.y * gridDim.x + blockIdx.x;  // b * Hq + h
@@ -386,8 +390,10 @@ __global__ __launch_bounds__(128) void oscar_decode_reduce_kernel(const float* w
 // then walks the partials four at a time, three rounds of memory latency for what takes one here
 // (in the trace: 64 splits x 32 heads 6.2 -> 4.0 us, 32 splits x 112 heads 5.1 -> 4.0, most of it
 // the launch).
-__global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float* ws, void* out,
-                                                                    int num_splits, int out_dtype) {
+__global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float* ws, void* out, int num_splits,
+                                                                    int out_dtype, StepLens lens) {
+  if (lens.seq_lens && blockIdx.x == 0 && threadIdx.x == 0)
+    advance_lengths(lens.seq_lens, lens.res_lens, blockIdx.y, lens.max_pages_per_seq);
   __shared__ __align__(16) float2 s_acc[4][64];
   const size_t unit = (size_t)blockIdx.y * gridDim.x + blockIdx.x;  // b * Hq + h
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -425,14 +431,14 @@ __global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float*
 
 // Host launcher of the reduce pass (also used by the 16-bit comparator).
 void oscar_launch_decode_reduce(const float* ws, void* out, int num_splits, int out_dtype,
-                                int n_q_heads, int batch, hipStream_t st) {
+                                int n_q_heads, int batch, hipStream_t st, StepLens lens) {
   // (the records are read in pairs of floats there: a workspace that is only 4-byte aligned is not)
   if (num_splits > 16 && num_splits <= 64 && reinterpret_cast<uintptr_t>(ws) % 8 == 0)
     hipLaunchKernelGGL(oscar_decode_reduce64_kernel, dim3(n_q_heads, batch), dim3(256), 0, st, ws, out,
-                       num_splits, out_dtype);
+                       num_splits, out_dtype, lens);
   else
     hipLaunchKernelGGL(oscar_decode_reduce_kernel, dim3(n_q_heads, batch), dim3(128), 0, st, ws, out,
-                       num_splits, out_dtype);
+                       num_splits, out_dtype, lens);
 }
 
 namespace {
@@ -476,7 +482,8 @@ static int check_decode_cache(const oscar_cache* cache) {
 static int launch_partial(const void* q, const oscar_cache* cache, void* out, int32_t out_dtype,
                           float softmax_scale, int32_t num_splits, void* workspace,
                           size_t workspace_bytes, void* stream, oscar_timer* timer,
-                          int* wrote_out = nullptr) {
+                          int* wrote_out = nullptr, const void* k_new = nullptr,
+                          const void* v_new = nullptr) {
   int rc = check_decode_cache(cache);
   if (rc != OSCAR_OK) return rc;
   if (!q || num_splits <= 0 || num_splits > 512) return OSCAR_ERR_INVALID_ARG;
@@ -493,13 +500,17 @@ static int launch_partial(const void* q, const oscar_cache* cache, void* out, in
   const float scale = softmax_scale > 0.0f ? softmax_scale : 0.08838834764831845f;
   P.qk_scale_log2 = scale * 1.4426950408889634f;
   P.out_dtype = out_dtype;
+  P.k_new = k_new;
+  P.v_new = v_new;
   const int gq = cache->cfg.n_q_heads / cache->cfg.n_kv_heads;
   dim3 grid(num_splits, cache->cfg.n_kv_heads, cache->batch);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (out && num_splits != 1) return OSCAR_ERR_INVALID_ARG;
   if (wrote_out) *wrote_out = 0;
-  rc = oscar_launch_decode_mfma(&P, gq, grid, st, e0, e1);
+  rc = k_new ? oscar_launch_decode_step_mfma(&P, gq, grid, st, e0, e1)
+             : oscar_launch_decode_mfma(&P, gq, grid, st, e0, e1);
   if (rc == OSCAR_OK && out && wrote_out) *wrote_out = 1;
+  if (k_new && rc != OSCAR_OK) return rc;   // nothing enqueued: the caller takes the two calls
   if (rc == OSCAR_ERR_UNSUPPORTED) {
     P.out = nullptr;
     rc = (cache->cfg.bits == 2) ? launch_gq<2>(P, gq, grid, st, e0, e1)
@@ -615,9 +626,27 @@ extern "C" int oscar_decode_step(const void* k_new, const void* v_new, const voi
   // every argument of the attention is checked before the append is enqueued
   const size_t need = oscar_decode_workspace_bytes(&cache->cfg, cache->batch, num_splits);
   if (!workspace || workspace_bytes < need) return OSCAR_ERR_WORKSPACE;
-  rc = oscar_quantize_append(k_new, v_new, 1, nullptr, cache, max_seq_len_hint - 1, 0u, stream);
+  // The token joins the cache inside the attention kernel where that is the matrix-core one and the
+  // encoder's published form would run (oscar_launch_decode_step_mfma decides): one launch and its
+  // 4 us less.  With several splits the reduce pass advances the lengths, with one the kernel itself,
+  // through the cache's ticket.
+  rc = oscar_check_append(k_new, v_new, 1, cache, max_seq_len_hint - 1, 0u);
   if (rc != OSCAR_OK) return rc;
   int wrote_out = 0;
+  if (cache->cfg.norm_scope == OSCAR_NORM_PER_HEAD && cache->cfg.rotation == OSCAR_ROTATION_ON &&
+      cache->cfg.scale_mode == OSCAR_SCALE_L2 && (num_splits > 1 || cache->tickets)) {
+    rc = launch_partial(q, cache, num_splits == 1 ? out : nullptr, out_dtype, softmax_scale, num_splits,
+                        workspace, workspace_bytes, stream, partial_timer, &wrote_out, k_new, v_new);
+    if (rc == OSCAR_OK && !wrote_out) {
+      oscar_launch_decode_reduce(reinterpret_cast<const float*>(workspace), out, num_splits, out_dtype,
+                                 cache->cfg.n_q_heads, cache->batch, reinterpret_cast<hipStream_t>(stream),
+                                 StepLens{cache->seq_lens, cache->res_lens, cache->max_pages_per_seq});
+      if (hipGetLastError() != hipSuccess) return OSCAR_ERR_HIP;
+    }
+    if (rc != OSCAR_ERR_UNSUPPORTED) return rc;
+  }
+  rc = oscar_quantize_append(k_new, v_new, 1, nullptr, cache, max_seq_len_hint - 1, 0u, stream);
+  if (rc != OSCAR_OK) return rc;
   rc = launch_partial(q, cache, num_splits == 1 ? out : nullptr, out_dtype, softmax_scale,
                       num_splits, workspace, workspace_bytes, stream, partial_timer, &wrote_out);
   if (rc != OSCAR_OK || wrote_out) return rc;

@@ -5,8 +5,6 @@
 
 namespace {
 
-constexpr int D = OSCAR_D;
-constexpr int R = OSCAR_R;
 constexpr int WS_STRIDE = D + 2;  // partial record: o[128], m, l
 
 struct DecodeParams {
@@ -18,7 +16,29 @@ struct DecodeParams {
   int num_splits;
   float qk_scale_log2;  // softmax scale * log2(e)
   int out_dtype;
+  const void *k_new, *v_new;   // fused decode step: the new token of every sequence
 };
+
+// Where a one-token append under the decode rule puts its token (the plan of plan_sequence for T = 1):
+// a full window is flushed to page `packed` first and the token starts the next window, otherwise it
+// joins the window; a sequence whose page table is full stays as it is.
+struct StepPlan {
+  int packed;   // pages before the step
+  bool flush, ok;
+  __device__ __forceinline__ StepPlan(int seq_len, int res_len, int max_pages_per_seq) {
+    packed = (seq_len - res_len) / R;
+    flush = res_len == R;
+    ok = packed + (flush ? 1 : 0) <= max_pages_per_seq;
+  }
+};
+// the lengths behind the step (one thread per sequence)
+__device__ __forceinline__ void advance_lengths(int32_t* seq_lens, int32_t* res_lens, int b, int max_pages_per_seq) {
+  const int n = seq_lens[b], r = res_lens[b];
+  const StepPlan p(n, r, max_pages_per_seq);
+  if (!p.ok) return;
+  seq_lens[b] = n + 1;
+  res_lens[b] = p.flush ? 1 : r + 1;
+}
 
 __device__ __forceinline__ float load_io(const void* p, size_t idx, int dt) {
   if (dt == OSCAR_F32) return reinterpret_cast<const float*>(p)[idx];

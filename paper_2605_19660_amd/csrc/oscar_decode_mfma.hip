@@ -49,7 +49,16 @@
 #ifndef OSCAR_MFMA_META32
 #define OSCAR_MFMA_META32 0
 #endif
+// OSCAR_MFMA_STEP = 1 (oscar_decode_step.hip, oscar_decode_step_zpmin.hip): the decode step's kernel,
+// which appends the step's new token on the way (fp16 metadata).
+#ifndef OSCAR_MFMA_STEP
+#define OSCAR_MFMA_STEP 0
+#endif
 #include "oscar_rowops.h"
+#if OSCAR_MFMA_STEP
+#include "oscar_append_kernel.h"
+#pragma clang fp contract(fast)
+#endif
 
 // A prefetch that refills registers in place must not be moved, by the instruction scheduler,
 // above the last read of the registers' old contents: the arriving data then lands in other
@@ -628,7 +637,85 @@ __host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int n
   return hp == 1 && (ngk == 1 || (ngk == 2 && ngv <= 2)) ? 2 : 1;
 }
 
-template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32>
+#if OSCAR_MFMA_STEP
+// values of the residual window as the encoder's block quantizer takes them
+struct WindowValues {
+  Raw8rt raw;
+  int dt;
+  __device__ __forceinline__ void widen(float (&x)[8]) const { raw.widen(x, dt); }
+};
+
+// One lane's 8 channels of a token into slot `at` of the residual window.
+__device__ __forceinline__ void store_new_token(const DecodeParams& P, size_t at, const uint4& k, const Raw8rt& v,
+                                                uint32_t nrm, int cg) {
+  *reinterpret_cast<uint4*>(reinterpret_cast<__half*>(P.c.res_k) + at * D + 8 * cg) = k;
+  if (P.c.cfg.io_dtype == OSCAR_F32) {
+    uint4* o = reinterpret_cast<uint4*>(reinterpret_cast<float*>(P.c.res_v) + at * D + 8 * cg);
+    o[0] = v.a;
+    o[1] = v.b;
+  } else {
+    *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(P.c.res_v) + at * D + 8 * cg) = v.a;
+  }
+  if (cg == 0) reinterpret_cast<uint16_t*>(P.c.res_norm)[at] = (uint16_t)nrm;
+}
+
+// The full window of (b, kvh) into page `page` of the sequence, then the new token into slot 0: what
+// oscar_append_kernel does for this call, by one workgroup.
+template <int BITS, int KG>
+__device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& lds, const DecodeParams& P, int b, int kvh,
+                                             int page, int tid, int cg) {
+  const int Hkv = P.c.cfg.n_kv_heads, slot = tid >> 4;
+  const size_t rb = ((size_t)b * Hkv + kvh) * R;
+  const int phys = P.c.block_table[(size_t)b * P.c.max_pages_per_seq + page];
+  const __half* res_norm = reinterpret_cast<const __half*>(P.c.res_norm) + rb;
+  ResRsrc<false> win;
+  win.make(P, rb, true);
+  uint4 ku[8];
+  WindowValues vw[8];
+  float nrm[8];
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    const int t = 16 * p + slot;
+    ku[p] = buf_load16(win.k, (t * D + 8 * cg) * 2);
+    vw[p].raw.load(win.v, t * D + 8 * cg);
+    vw[p].dt = P.c.cfg.io_dtype;
+    nrm[p] = __half2float(res_norm[t]);
+  }
+  IoRsrc kn, vn;
+  const size_t e0 = ((size_t)b * Hkv + kvh) * D;
+  kn.make(P.k_new, e0, D, P.c.cfg.io_dtype, true);
+  vn.make(P.v_new, e0, D, P.c.cfg.io_dtype, true);
+  Raw8rt kraw, vraw;
+  kraw.load(kn, 8 * cg);
+  vraw.load(vn, 8 * cg);
+  float x[8], nf;
+  kraw.widen(x, P.c.cfg.io_dtype);
+  uint32_t sg[4];
+  butterfly_signs(cg, sg);
+  const uint4 k = key_transform8<__half>(x, sg, nf);
+  // every read of the old window has returned before slot 0 is written
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (slot == 0) store_new_token(P, rb, k, vraw, half_bits(nf), cg);
+  const float nrm_q[2] = {0.0f, 0.0f};
+  quantize_block<__half, BITS, KG, 8>(lds, ku, vw, false, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
+                                      OSCAR_MFMA_ZPMIN != 0, tid, cg);
+}
+#endif
+
+// STEP: the launch is a whole decode step under the decode rule of oscar_quantize_append (one token per
+// sequence, rotation on, L2 norm per head), then the attention over the cache that results.  As launches
+// of their own the append cost 4 .. 9 us of a step for a token row per sequence and kv head.
+//  * Every workgroup that owns part of the residual window transforms the new token itself (the 16
+//    lanes of a row hold it exactly as they hold a token of the window); the wave whose token it is
+//    writes it to its slot.
+//  * A full window goes to its page first: by the workgroup whose wave will attend to that page, before
+//    anything else, with the encoder's own block quantizer (once in 128 steps of a sequence); it also
+//    writes the new token to slot 0 then, behind its reads of the old window, which nobody else reads.
+//  * The lengths are advanced by the reduce pass.  With a single split there is none: every workgroup
+//    draws the cache's ticket as soon as it has the lengths, so that whoever draws the last one knows
+//    that all have read them, and advances them at its end.
+template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32, bool STEP>
 __global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
 void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr int TPG = 8 / NGK;  // token tiles per key group
@@ -639,9 +726,23 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr bool ONE_TILE = (HP == 2) || (NGK == 4);
 
   // rows padded by 16 bytes: the 16-byte operand reads of lanes n = 0..7 hit 8 different banks
+#if OSCAR_MFMA_STEP
+  struct Tables {
+    alignas(16) _Float16 A[4][16][TABW], P[4][16][TABW];
+    alignas(16) float o[4][OSCAR_MAX_GQA][D];
+  };
+  __shared__ union {   // (the flush is over before the tables are touched)
+    Tables t;
+    EncoderLds<__half, BITS, R / NGK, 8> enc;
+  } s_u;
+  auto& s_A = s_u.t.A;
+  auto& s_P = s_u.t.P;
+  auto& s_o = s_u.t.o;
+#else
   __shared__ __align__(16) _Float16 s_A[4][16][TABW];   // per wave: (Q_h Delta_k) hi/lo rows
   __shared__ __align__(16) _Float16 s_P[4][16][TABW];   // per wave: (p Delta_v) hi/lo rows
   __shared__ __align__(16) float s_o[4][OSCAR_MAX_GQA][D];  // wave results for the merge
+#endif
   __shared__ float s_wm[4][OSCAR_MAX_GQA], s_wl[4][OSCAR_MAX_GQA];
   // two head slots: the rotated queries in operand order wait in LDS between pages instead of
   // registers (16 registers that the second slot's softmax state needs)
@@ -692,8 +793,28 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   }
 
   const int seq_len = P.c.seq_lens[b];
-  const int r = P.c.res_lens[b];
-  const int n_pages = (seq_len - r) / R;
+  int r = P.c.res_lens[b];
+  int n_pages = (seq_len - r) / R;
+  [[maybe_unused]] bool step_ok = false, step_flush = false;
+  [[maybe_unused]] int my_ticket = -1;
+#if OSCAR_MFMA_STEP
+  {
+    const StepPlan plan(seq_len, r, P.c.max_pages_per_seq);
+    step_ok = plan.ok;
+    step_flush = plan.ok && plan.flush;
+    if (!plan.ok && tid == 0 && split == 0 && kvh == 0 && P.c.dev_status) *P.c.dev_status = OSCAR_ERR_CAPACITY;
+    if (step_flush && split == (plan.packed >> 2) % P.num_splits) {
+      flush_window(s_u.enc, P, b, kvh, plan.packed, tid, cg);
+      // the page's stores have reached memory before any wave of this workgroup reads it
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    if (step_ok) {
+      r = step_flush ? 1 : r + 1;
+      n_pages += step_flush ? 1 : 0;
+    }
+  }
+#endif
   // Residual slice of this split: rs tokens per split (a multiple of 16), handed out from
   // the last split backwards; inside the workgroup, wave w takes tokens 16*pass + 4*w + j.
   const int rs = 16 * ((((r + 15) >> 4) + P.num_splits - 1) / P.num_splits);
@@ -710,6 +831,30 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   rres.make(P, ((size_t)b * Hkv + kvh) * R, wave_res);
   // slot of the wave's token i of pass p0, clamped to the slice (masked where it is used)
   auto res_slot = [&](int p0, int i) { return t_lo + max(0, min(p0 + 4 * wave + i, rcount - 1)); };
+#if OSCAR_MFMA_STEP
+  // the new token is the window's last; every wave of the workgroup that owns it has it in registers
+  // (slot numbers past a wave's tokens are clamped to the slice's last one, which it then is)
+  const bool has_new = step_ok && rcount > 0 && t_lo + rcount == r;
+  ResTok<M32> tok_new;
+  if (has_new && wave_res) {
+    IoRsrc kn, vn;
+    const size_t e0 = ((size_t)b * Hkv + kvh) * D;
+    kn.make(P.k_new, e0, D, P.c.cfg.io_dtype, true);
+    vn.make(P.v_new, e0, D, P.c.cfg.io_dtype, true);
+    Raw8rt kraw;
+    kraw.load(kn, 8 * cg);
+    tok_new.v.load(vn, 8 * cg);
+    float x[8], nf;
+    kraw.widen(x, P.c.cfg.io_dtype);
+    uint32_t sg[4];
+    butterfly_signs(cg, sg);
+    tok_new.k = key_transform8<__half>(x, sg, nf);
+    tok_new.nrm = half_bits(nf);
+    if (!step_flush && q4 == 0 && wave == (((r - 1 - t_lo) & 15) >> 2))
+      store_new_token(P, ((size_t)b * Hkv + kvh) * R + r - 1, tok_new.k, tok_new.v, tok_new.nrm, cg);
+  }
+  auto is_new = [&](int p0, int i) { return has_new && res_slot(p0, i) == r - 1; };
+#endif
   ResTok<M32> rt_first[4];   // the wave's four tokens of the first residual pass
   if (wave_res) {
 #pragma unroll
@@ -723,6 +868,17 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   first.make(pools, P, (uint32_t)__builtin_amdgcn_readlane(tab, 0), pg_first < n_pages);
   kr.load(first, lane);
   __builtin_amdgcn_sched_barrier(0);
+#if OSCAR_MFMA_STEP
+  // All four waves have the lengths in registers (the loads above have waited for them) before the
+  // workgroup draws its ticket; the answer is needed at the very end only, by when it has long come.
+  // Drawn at the end, the tickets of a launch whose workgroups finish together queue up, 11 ns each.
+  if (P.num_splits == 1) {
+    asm volatile("" ::"s"(n_pages), "s"(r));
+    __builtin_amdgcn_s_barrier();
+    if (tid == 0) my_ticket = atomicAdd(&P.c.tickets[0], 1);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#endif
   OSCAR_STAMP(2);   // first page's key-side loads issued
 
   // this wave's operand tables start as zeros (rows of absent heads stay zero)
@@ -788,10 +944,14 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool valid = p0 + 4 * wave + i < rcount;   // wave-uniform
+        ResTok<M32> tok = rt[i];
+#if OSCAR_MFMA_STEP
+        if (is_new(p0, i)) tok = tok_new;
+#endif
         float kv[8];
-        halves_to_f32(rt[i].k, kv);
-        rt[i].v.widen(vv[i], P.c.cfg.io_dtype);
-        const float nrm = rt[i].norm();
+        halves_to_f32(tok.k, kv);
+        tok.v.widen(vv[i], P.c.cfg.io_dtype);
+        const float nrm = tok.norm();
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
           float acc = qh[s][0] * kv[0];
@@ -1425,6 +1585,16 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     P.ws[rec * WS_STRIDE + D] = M;
     P.ws[rec * WS_STRIDE + D + 1] = L;
   }
+#if OSCAR_MFMA_STEP
+  if (P.num_splits == 1 && wave == 0) {
+    const int total = (int)(gridDim.x * gridDim.y * gridDim.z);
+    if (__builtin_amdgcn_readfirstlane(my_ticket) == total - 1) {
+      for (int bb = lane; bb < P.c.batch; bb += 64)
+        advance_lengths(P.c.seq_lens, P.c.res_lens, bb, P.c.max_pages_per_seq);
+      if (lane == 0) P.c.tickets[0] = 0;
+    }
+  }
+#endif
   OSCAR_STAMP(27);   // split record written
 }
 
@@ -1432,16 +1602,16 @@ template <int BITS, int HP>
 int launch_groups(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, hipEvent_t e0,
                   hipEvent_t e1) {
   const int ngk = P.g.ngk, ngv = P.g.ngv;
-  constexpr bool ZPM = OSCAR_MFMA_ZPMIN != 0, M32 = OSCAR_MFMA_META32 != 0;
+  constexpr bool ZPM = OSCAR_MFMA_ZPMIN != 0, M32 = OSCAR_MFMA_META32 != 0, STEP = OSCAR_MFMA_STEP != 0;
   // the event-carrying launch only when a timer asked for it: the plain launch is what a
   // stream capture records
 #define OSCAR_MFMA_CASE(NK, NV)                                                            \
   if (ngk == NK && ngv == NV) {                                                            \
     if (e0 || e1)                                                                          \
-      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32>), grid,       \
+      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP>), grid,       \
                             dim3(256), 0, st, e0, e1, 0, P, gq);                           \
     else                                                                                   \
-      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32>), grid,          \
+      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP>), grid,          \
                          dim3(256), 0, st, P, gq);                                         \
     return OSCAR_OK;                                                                       \
   }
@@ -1470,14 +1640,18 @@ int launch_this_form(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, h
 
 }  // namespace
 
-// the other three translation units' entries
+// the other translation units' entries
 #define OSCAR_MFMA_FORM(NAME) \
   int NAME(const void* params, int gq, dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 #define OSCAR_MFMA_FORM_DEFINE(NAME)                                                             \
   OSCAR_MFMA_FORM(NAME) {                                                                        \
     return launch_this_form(*reinterpret_cast<const DecodeParams*>(params), gq, grid, st, e0, e1); \
   }
-#if OSCAR_MFMA_META32 && OSCAR_MFMA_ZPMIN
+#if OSCAR_MFMA_STEP && OSCAR_MFMA_ZPMIN
+OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_step_this_zpmin)
+#elif OSCAR_MFMA_STEP
+OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_step_this)
+#elif OSCAR_MFMA_META32 && OSCAR_MFMA_ZPMIN
 OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_meta32_zpmin)
 #elif OSCAR_MFMA_META32
 OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_meta32)
@@ -1487,6 +1661,8 @@ OSCAR_MFMA_FORM_DEFINE(oscar_launch_decode_mfma_zpmin)
 OSCAR_MFMA_FORM(oscar_launch_decode_mfma_zpmin);
 OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32);
 OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32_zpmin);
+OSCAR_MFMA_FORM(oscar_launch_decode_step_this);
+OSCAR_MFMA_FORM(oscar_launch_decode_step_this_zpmin);
 
 #ifdef OSCAR_DECODE_STAMPS
 // [8 workgroup slots][4 waves][32 stamps] of the last stamped launch (integer zero-point variants)
@@ -1504,28 +1680,42 @@ extern "C" int oscar_debug_force_generic_decode(int32_t on) {
   return g_force_generic.exchange(on ? 1 : 0, std::memory_order_relaxed);
 }
 
-// Launches the matrix-core partial pass when the configuration is one it is built for
-// (fp16 or fp32 metadata; group sizes 32, 64 or 128 on either side; keys scaled into [-1, 1];
-// page pools below 2 GiB each); OSCAR_ERR_UNSUPPORTED tells the caller to use the generic kernel.
-int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
-                             hipEvent_t e0, hipEvent_t e1) {
-  const DecodeParams& P = *reinterpret_cast<const DecodeParams*>(params);
+// Whether the matrix-core kernel is built for a configuration: group sizes 32, 64 or 128 on either
+// side, keys scaled into [-1, 1], page pools below 2 GiB each.
+static bool mfma_takes(const DecodeParams& P) {
   // the key operand's fixed exponent assumes Delta_k <= 1, which holds when |K_u| <= 1 (L2 or
   // maximum scaling); the un-scaled and mean-absolute-value ablations go to the generic kernel
-  if (P.c.cfg.scale_mode != OSCAR_SCALE_L2 && P.c.cfg.scale_mode != OSCAR_SCALE_MAX)
-    return OSCAR_ERR_UNSUPPORTED;
-  if (g_force_generic.load(std::memory_order_relaxed)) return OSCAR_ERR_UNSUPPORTED;
+  if (P.c.cfg.scale_mode != OSCAR_SCALE_L2 && P.c.cfg.scale_mode != OSCAR_SCALE_MAX) return false;
+  if (g_force_generic.load(std::memory_order_relaxed)) return false;
   // a page is addressed as a 32-bit scalar offset into its pool
   const unsigned long long units = (unsigned long long)P.c.num_pages * (unsigned long long)P.c.cfg.n_kv_heads;
   int biggest = P.g.k_codes_bytes > P.g.v_meta_bytes ? P.g.k_codes_bytes : P.g.v_meta_bytes;
   if (P.g.k_meta_bytes > biggest) biggest = P.g.k_meta_bytes;
-  if (units * (unsigned long long)biggest > 0x7FFFFFFFull) return OSCAR_ERR_UNSUPPORTED;
+  return units * (unsigned long long)biggest <= 0x7FFFFFFFull;
+}
+
+// Launches the matrix-core partial pass; OSCAR_ERR_UNSUPPORTED tells the caller to use the generic
+// kernel.
+int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
+                             hipEvent_t e0, hipEvent_t e1) {
+  const DecodeParams& P = *reinterpret_cast<const DecodeParams*>(params);
+  if (!mfma_takes(P)) return OSCAR_ERR_UNSUPPORTED;
   const bool zpm = P.c.cfg.zp_mode == OSCAR_ZP_MIN;
   if (P.c.cfg.meta_dtype == OSCAR_F32)
     return zpm ? oscar_launch_decode_mfma_meta32_zpmin(params, gq, grid, st, e0, e1)
                : oscar_launch_decode_mfma_meta32(params, gq, grid, st, e0, e1);
   if (zpm) return oscar_launch_decode_mfma_zpmin(params, gq, grid, st, e0, e1);
   return launch_this_form(P, gq, grid, st, e0, e1);
+}
+
+// The same for a whole decode step (fp16 metadata); OSCAR_ERR_UNSUPPORTED: append and attention as two
+// calls.
+int oscar_launch_decode_step_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
+                                  hipEvent_t e0, hipEvent_t e1) {
+  const DecodeParams& P = *reinterpret_cast<const DecodeParams*>(params);
+  if (!mfma_takes(P) || P.c.cfg.meta_dtype != OSCAR_F16) return OSCAR_ERR_UNSUPPORTED;
+  return P.c.cfg.zp_mode == OSCAR_ZP_MIN ? oscar_launch_decode_step_this_zpmin(params, gq, grid, st, e0, e1)
+                                         : oscar_launch_decode_step_this(params, gq, grid, st, e0, e1);
 }
 
 #endif

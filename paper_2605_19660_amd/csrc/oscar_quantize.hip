@@ -393,11 +393,10 @@ extern "C" int oscar_rotate(const void* x, void* out, void* norms, int64_t n_vec
   return OSCAR_OK;
 }
 
-extern "C" int oscar_quantize_append(const void* k, const void* v, int32_t T,
-                                     const int32_t* new_lens, oscar_cache* cache,
-                                     int32_t max_seq_len_hint, uint32_t flags, void* stream) {
+int oscar_check_append(const void* k, const void* v, int32_t T, const oscar_cache* cache,
+                       int32_t max_seq_len_hint, uint32_t flags) {
   if (!cache) return OSCAR_ERR_INVALID_ARG;
-  int rc = oscar_validate_config(&cache->cfg);
+  const int rc = oscar_validate_config(&cache->cfg);
   if (rc != OSCAR_OK) return rc;
   if (T < 0 || cache->batch <= 0 || cache->max_pages_per_seq <= 0 || cache->num_pages <= 0)
     return OSCAR_ERR_INVALID_ARG;
@@ -413,6 +412,14 @@ extern "C" int oscar_quantize_append(const void* k, const void* v, int32_t T,
     const long long pages = (flags & OSCAR_APPEND_EAGER) ? total / R : (total - 1) / R;
     if (pages > cache->max_pages_per_seq) return OSCAR_ERR_CAPACITY;
   }
+  return OSCAR_OK;
+}
+
+extern "C" int oscar_quantize_append(const void* k, const void* v, int32_t T,
+                                     const int32_t* new_lens, oscar_cache* cache,
+                                     int32_t max_seq_len_hint, uint32_t flags, void* stream) {
+  int rc = oscar_check_append(k, v, T, cache, max_seq_len_hint, flags);
+  if (rc != OSCAR_OK || T == 0) return rc;
   AppendParams P;
   P.k = k;
   P.v = v;

@@ -835,23 +835,16 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // the new token is the window's last; every wave of the workgroup that owns it has it in registers
   // (slot numbers past a wave's tokens are clamped to the slice's last one, which it then is)
   const bool has_new = step_ok && rcount > 0 && t_lo + rcount == r;
+  // (its loads go first here, the work on it waits until everything has been asked for)
   ResTok<M32> tok_new;
+  Raw8rt knew;
   if (has_new && wave_res) {
     IoRsrc kn, vn;
     const size_t e0 = ((size_t)b * Hkv + kvh) * D;
     kn.make(P.k_new, e0, D, P.c.cfg.io_dtype, true);
     vn.make(P.v_new, e0, D, P.c.cfg.io_dtype, true);
-    Raw8rt kraw;
-    kraw.load(kn, 8 * cg);
+    knew.load(kn, 8 * cg);
     tok_new.v.load(vn, 8 * cg);
-    float x[8], nf;
-    kraw.widen(x, P.c.cfg.io_dtype);
-    uint32_t sg[4];
-    butterfly_signs(cg, sg);
-    tok_new.k = key_transform8<__half>(x, sg, nf);
-    tok_new.nrm = half_bits(nf);
-    if (!step_flush && q4 == 0 && wave == (((r - 1 - t_lo) & 15) >> 2))
-      store_new_token(P, ((size_t)b * Hkv + kvh) * R + r - 1, tok_new.k, tok_new.v, tok_new.nrm, cg);
   }
   auto is_new = [&](int p0, int i) { return has_new && res_slot(p0, i) == r - 1; };
 #endif
@@ -934,12 +927,25 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #pragma unroll
       for (int c = 0; c < 8; ++c) ow[s][c] = 0.0f;
     }
+#if OSCAR_MFMA_STEP
+    if (has_new) {
+      float x[8], nf;
+      knew.widen(x, P.c.cfg.io_dtype);
+      tok_new.k = key_transform8<__half>(x, sgn, nf);
+      tok_new.nrm = half_bits(nf);
+      if (!step_flush && q4 == 0 && wave == (((r - 1 - t_lo) & 15) >> 2))
+        store_new_token(P, ((size_t)b * Hkv + kvh) * R + r - 1, tok_new.k, tok_new.v, tok_new.nrm, cg);
+    }
+#endif
     // (the raw norms stay opaque until here: converted where they were loaded, they made the
     // wave wait for the loads, and for the whole first page behind them, before the query rotation)
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rt_first[i].nrm));
-    // one pass: the wave's four tokens of slots p0 .. p0 + 15 of the slice, from registers
+    // one pass: the wave's four tokens of slots p0 .. p0 + 15 of the slice, from registers.  Every
+    // fused multiply-add is written out: left to the compiler, the step form and the attention alone
+    // fused differently and their outputs differed in the last bit.
     auto pass = [&](const ResTok<M32> (&rt)[4], int p0) {
+#pragma clang fp contract(off)
       float sc[HP][4], vv[4][8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -966,13 +972,12 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         const float m_new = fmaxf(fmaxf(mw[s], fmaxf(sc[s][0], sc[s][1])), fmaxf(sc[s][2], sc[s][3]));
         const float alpha = __builtin_amdgcn_exp2f(mw[s] - m_new);
         mw[s] = m_new;
-        lw[s] *= alpha;
 #pragma unroll
         for (int c = 0; c < 8; ++c) ow[s][c] *= alpha;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float pw = __builtin_amdgcn_exp2f(sc[s][i] - m_new);
-          lw[s] += pw;
+          lw[s] = i == 0 ? fmaf(lw[s], alpha, pw) : lw[s] + pw;
 #pragma unroll
           for (int c = 0; c < 8; ++c) ow[s][c] = fmaf(pw, vv[i][c], ow[s][c]);
         }

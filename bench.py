@@ -48,12 +48,13 @@ MEASURED_TRAFFIC = {("llama3-8b-like-b8-s32k", 2, 8): 182_300_126,
 # The same kernel's mean duration over the decode steps in the committed `rocprofv3
 # --kernel-trace` summaries (the dispatch's own begin/end timestamps), for comparison with the
 # figure measured here: an event pair around a launch also holds the queue's hand-over from the
-# event marker to the dispatch and reads 2-3 us more.  Keyed like MEASURED_TRAFFIC.
-PROFILED_KERNEL_US = {("llama3-8b-like-b8-s32k", 2, 8): 33.13,
-                      ("long-b1-s128k", 2, 64): 20.54,
-                      ("omni-b4-g7-s64k", 2, 32): 25.54,
-                      ("highbatch-b64-s8k", 2, 1): 67.12,
-                      ("highbatch-b64-s8k", 4, 1): 117.32}
+# event marker to the dispatch and reads 2-3 us more.  The kernel includes the step's append.  Keyed
+# like MEASURED_TRAFFIC.
+PROFILED_KERNEL_US = {("llama3-8b-like-b8-s32k", 2, 8): 34.27,
+                      ("long-b1-s128k", 2, 64): 21.54,
+                      ("omni-b4-g7-s64k", 2, 32): 25.63,
+                      ("highbatch-b64-s8k", 2, 1): 70.94,
+                      ("highbatch-b64-s8k", 4, 1): 119.06}
 
 
 def profiled(w, splits, cache_bytes):
@@ -61,7 +62,7 @@ def profiled(w, splits, cache_bytes):
     if us is None:
         return None
     return {"avg_kernel_us": us, "frac": cache_bytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBS,
-            "summary": "profiles/decode_mfma_%s%s.txt" % (w.name, "-int4" if w.bits == 4 else ""),
+            "summary": "profiles/decode_step_%s%s.txt" % (w.name, "-int4" if w.bits == 4 else ""),
             "what": "mean over the decode steps of a rocprofv3 kernel trace of this bench (dispatch timestamps)"}
 # The encoder kernel alone on the whole-context prefill, median over the prefill launches in the
 # same kernel trace (the call timed here also holds the length-update kernel behind it).
@@ -578,11 +579,10 @@ def measure(args, w, np, torch, ob, synth):
                    "bits": w.bits, "k_group": w.k_group, "v_group": w.v_group,
                    "io_dtype": w.io_dtype,
                    "norm_scope": "all kv heads" if args.norm_all_heads else "per kv head",
-        "step": "oscar_decode_step: append 1 token/seq (1 launch) + decode attention (partial + reduce launches)",
+        "step": "oscar_decode_step: append 1 token/seq and decode attention in one launch, reduce in a second",
                    "splits": splits, "cache_copies_rotated": n_copies},
         "roofline": {"bound": "hbm",
-                     "kernel": ("oscar_decode_mfma_kernel" if w.meta_dtype == "f16"
-                                else "oscar_decode_partial_kernel") + " (split-K partial pass)",
+                     "kernel": "oscar_decode_mfma_kernel (append and split-K partial pass)",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": MEASURED_TRAFFIC.get((w.name, w.bits, splits)),

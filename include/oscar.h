@@ -235,12 +235,16 @@ int oscar_decode_attn(const void *q, const oscar_cache *cache, void *out, int32_
 
 /* One decoding step of Algorithm "The OScaR algorithm" (OScaR-Inference, decoding phase) in one
  * call: oscar_quantize_append of ONE new token per sequence under the decode rule, then
- * oscar_decode_attn over the updated cache -- the same launches, one trip through the ABI.
+ * oscar_decode_attn over the updated cache, in one trip through the ABI.  With fp16 metadata, the
+ * published method and the norm per head the append happens inside the matrix-core kernel (one
+ * launch less; with a single split that needs cache->tickets); cache bytes, lengths and outputs
+ * are the bits of the two calls either way.
  *   k_new, v_new : device, [batch][1][n_kv_heads][head_dim], io_dtype
  *   q, out, out_dtype, softmax_scale, num_splits, workspace: as in oscar_decode_attn
  *   max_seq_len_hint : upper bound on seq_lens[] AFTER this step's append (>= 1)
  *   partial_timer : NULL, or a timer that receives the duration of the split-K partial kernel
- *                   of this step (measurement aid, see oscar_timer_create)
+ *                   of this step, the append included where it is part of it (measurement aid,
+ *                   see oscar_timer_create)
  * Every argument is checked before anything is enqueued; OSCAR_ERR_CAPACITY as in
  * oscar_quantize_append. */
 typedef struct oscar_timer oscar_timer;

@@ -1275,28 +1275,28 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     }
 
     if constexpr (M32) {
-      // ---- fp32 metadata: P V of this page on its own, exactly, then added to the output ----
-      // sum p*Delta*c and sum p*Delta*z are each many times their difference, the page's share of
-      // the output (c is near z for most channels of a group that holds an outlier), and the
-      // plain-ALU kernel takes the difference code by code.  To lose no more than it does, the
-      // page's sums start from zero accumulators and both come from the same limbs on one grid
-      // (grid_limbs): the high limbs' sums are then exact, in the matrix core as in the vector unit,
-      // and so is their difference.  Limbs rounded to their own exponents lost the low bits of every
-      // small product beside a large one (a matrix instruction aligns its products to the largest
-      // nominal exponent, for codes held as subnormals up to 2^10 above their value): 3e-6 of
-      // sum p*Delta*z where the softmax is peaked, eight times this form's error in the output.
-      // (positive fp32 numbers order like their bit patterns; the exponent field E bounds the
-      // largest step size by 2^(E - 126))
-      uint32_t dm = 0;
-#pragma unroll
-      for (int g = 0; g < NGV; ++g) {
-        const uint4 da = vr.vd[g].a, db = vr.vd[g].b;
-        dm = max(max(max(dm, max(da.x, da.y)), max(da.z, da.w)), max(max(db.x, db.y), max(db.z, db.w)));
-      }
-      const int xv = min(139 - (int)(row16_max_u32(dm) >> 23), 126);   // Delta_v * 2^xv < 2^13
-      const float pscale = ldexpf(1.0f, xv);
-      const int unscale_exp = 24 - slot_bitpos_min(BITS) - xv;
+      // ---- fp32 metadata: P V of this page on its own, then added to the output ----
+      // The plain-ALU kernel forms Delta*(c - z) code by code in fp32; this one has to lose no more.
+      // sum p*Delta*c and sum p*Delta*z are each many times their difference (c is near z for most
+      // channels of a group that holds an outlier), so the page's sums start from zero accumulators
+      // and both come from the same limbs on one grid (grid_limbs): the high limbs' sums are then
+      // exact, in the matrix core as in the vector unit, and so is their difference.  Limbs rounded to
+      // their own exponents lost the low bits of every small product beside a large one (a matrix
+      // instruction aligns its products to the largest nominal exponent, for codes held as subnormals
+      // up to 2^10 above their value): 3e-6 of sum p*Delta*z where the softmax is peaked.
+      // The limbs of a product are off by 2^-24 of the grid's range, so the range is that of the
+      // head's largest p*Delta of this page and value group: such an error is far below that token's
+      // own step, whatever the other tokens, groups and heads hold.  (With one range for the page, set
+      // by its largest step, a group or a softmax peak 2^12 below it was off by 1e-4 .. 1e-3, at 2^30
+      // by 2e-2 and more, and an infinite step cleared the other groups.)
+      // What the limbs multiply is c - zc with an integer zc among the codes; the rest of the
+      // zero-point (a group whose values share a sign lies off zero by any number of steps, a float
+      // zero-point between two) cancels against nothing and is weighted with the probabilities as
+      // they are, in the vector unit.
+      // (The own ranges and the split zero-point cost 1 .. 11 % of the time: attention alone, batch 4 x 8K,
+      // INT2, G_k = 128, G_v = 32, 14.6 -> 15.7 us at GQA 4, 18.9 -> 20.8 at GQA 7.)
       constexpr float kz = 1.0f / (float)(1 << (24 - slot_bitpos_min(BITS)));   // limbs -> accumulator
+      constexpr float qmax = (float)((1 << BITS) - 1);
       if (__any(rescale)) {
 #pragma unroll
         for (int s = 0; s < HP; ++s)
@@ -1305,47 +1305,53 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
       }
 #pragma unroll
       for (int g = 0; g < NGV; ++g) {
-        float vdf[8], vzf[8];
+        float vdf[8], vzf[8], zcw[8], rest[8];   // value = Delta * (c - zc) + rest
         vr.vd[g].floats(vdf);
         vr.vz[g].floats(vzf);
-        // integer zero-point: the limbs carry the slots' weights, the zero-points take them back;
-        // float zero-point: the terms p * zero go on the grid themselves
 #pragma unroll
         for (int T = 0; T < 8; ++T) {
-          vdf[T] = (vdf[T] * pscale) * vsc0[T];
-          vzf[T] = zp_min ? vzf[T] * pscale : vzf[T] * vup[T];
+          float zc;
+          if constexpr (zp_min) {
+            // (any integer will do, so the hardware's reciprocal does)
+            zc = __builtin_amdgcn_fmed3f(rintf(-vzf[T] * __builtin_amdgcn_rcpf(vdf[T])), 0.0f, qmax);
+            rest[T] = fmaf(vdf[T], zc, vzf[T]);
+          } else {
+            zc = __builtin_amdgcn_fmed3f(vzf[T], 0.0f, qmax);
+            rest[T] = vdf[T] * (zc - vzf[T]);
+          }
+          zcw[T] = zc * vup[T];   // (the limbs carry the slots' weights, the zero-points take them back)
         }
         float zh[HP], zl[HP];
+        int unscale_exp[HP];
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
           float t[8], gr[8], re[8];
           uint4 hi, lo;
+          // (positive fp32 numbers order like their bit patterns; the exponent field E bounds the
+          // largest product by 2^(E - 126))
+          uint32_t tm = 0;
+          float sh = 0.0f, sl = 0.0f, sx = 0.0f;
 #pragma unroll
-          for (int T = 0; T < 8; ++T) t[T] = S[s][T] * vdf[T];
+          for (int T = 0; T < 8; ++T) {
+            t[T] = S[s][T] * vdf[T];
+            tm = max(tm, __float_as_uint(t[T]));
+            sx = fmaf(S[s][T], rest[T], sx);
+          }
+          const int xv = 139 - (int)(row16_max_u32(tm) >> 23);   // p * Delta_v * 2^xv < 2^13
+          unscale_exp[s] = 24 - slot_bitpos_min(BITS) - xv;
+#pragma unroll
+          for (int T = 0; T < 8; ++T) t[T] = ldexpf(t[T], xv) * vsc0[T];
           grid_limbs(t, vsc0, gr, re, hi, lo);
           const int h = q4 + 4 * s;
           *reinterpret_cast<uint4*>(&P_tab[row_hi(h)][8 * n]) = hi;
           *reinterpret_cast<uint4*>(&P_tab[row_hi(h) + 1][8 * n]) = lo;
-          float sh = 0.0f, sl = 0.0f;
-          if constexpr (zp_min) {
-#pragma clang fp contract(off)
-            constexpr float magic = 12582912.0f * 4.0f;
 #pragma unroll
-            for (int T = 0; T < 8; ++T) {
-              const float tz = S[s][T] * vzf[T];
-              const float gz = (tz + magic) - magic;
-              sh -= gz;
-              sl -= tz - gz;
-            }
-          } else {
-#pragma unroll
-            for (int T = 0; T < 8; ++T) {
-              sh = fmaf(gr[T], vzf[T], sh);
-              sl = fmaf(re[T], vzf[T], sl);
-            }
+          for (int T = 0; T < 8; ++T) {
+            sh = fmaf(gr[T], zcw[T], sh);
+            sl = fmaf(re[T], zcw[T], sl);
           }
           zh[s] = row16_sum(sh) * kz;
-          zl[s] = row16_sum(sl) * kz;
+          zl[s] = row16_sum(fmaf(sl, kz, -ldexpf(sx, -unscale_exp[s])));
         }
         vr.load_delta(nx, g, lane);
         wave_lds_fence();
@@ -1357,7 +1363,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         auto add_tile = [&](int ct, const float4v& a) {
 #pragma unroll
           for (int s = 0; s < HP; ++s)
-            om[s][ct] += ldexpf((a[2 * s] - zh[s]) + (a[2 * s + 1] - zl[s]), unscale_exp);
+            om[s][ct] += ldexpf((a[2 * s] - zh[s]) + (a[2 * s + 1] - zl[s]), unscale_exp[s]);
           keep_tuple(a);
         };
         float4v prev = (float4v){0.0f, 0.0f, 0.0f, 0.0f};

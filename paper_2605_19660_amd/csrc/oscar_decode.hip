@@ -413,8 +413,11 @@ __global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float*
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const float ws_k = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), wave + 4 * k));
-    acc.x = fmaf(o[k].x, ws_k, acc.x);
-    acc.y = fmaf(o[k].y, ws_k, acc.y);
+    // the places past the last split hold it once more and are cleared: with the weight of 0 alone an
+    // infinite partial became NaN
+    const uint32_t held = wave + 4 * k < num_splits ? ~0u : 0u;
+    acc.x = fmaf(__uint_as_float(__float_as_uint(o[k].x) & held), ws_k, acc.x);
+    acc.y = fmaf(__uint_as_float(__float_as_uint(o[k].y) & held), ws_k, acc.y);
   }
   s_acc[wave][lane] = acc;
   __syncthreads();

@@ -41,3 +41,24 @@ def test_split_counts(splits, out_dt, offset):
     bound = scale * (splits + 8) * 2.0 ** -24 + (np.abs(want) * 2.0 ** -8 if out_dt == "bf16" else 0)
     assert (np.abs(got - want) <= bound + 1e-30).all()
     assert (got[0, 0] == 0).all()
+
+
+@pytest.mark.parametrize("splits", [1, 2, 15, 16, 17, 18, 33, 63, 64, 65, 130])
+@pytest.mark.parametrize("at", ["first", "last"])
+def test_an_infinite_partial_gives_an_infinite_output(splits, at):
+    """A split that holds an infinite value (16-bit window) has an infinite partial in that channel: the
+    weighted sum is infinite there whatever the form does with the places past the last split."""
+    import torch
+    from paper_2605_19660_amd import binding as ob
+    cache = ob.Cache(ob.Config(2, 1), 1, 1)
+    rng = np.random.default_rng(splits)
+    rec = rng.standard_normal((1, 2, splits, 130)).astype(np.float32)
+    rec[..., 129] = np.abs(rec[..., 129]) + 0.1
+    rec[0, 1, 0 if at == "first" else splits - 1, [5, 6]] = [np.inf, -np.inf]
+    ws = torch.from_numpy(rec.reshape(-1)).cuda()
+    out = torch.empty(1, 2, 128, device="cuda")
+    ob.decode_attn_reduce(cache, out, ws.view(torch.uint8), splits)
+    got = out.cpu().numpy()
+    assert got[0, 1, 5] == np.inf and got[0, 1, 6] == -np.inf
+    got[0, 1, [5, 6]] = 0
+    assert np.isfinite(got).all()

@@ -585,7 +585,7 @@ template <bool M32> struct ResRsrc {
 
 // One residual token's share for a lane: 8 channels (channel group cg) of K_u (fp16) and of
 // V (caller's dtype), and the token norm, held raw until the query rotation is done.
-// `tok` is the token's slot in the window, clamped by the caller to a slot that exists.
+// `tok` is the token's slot in the window; slot R is past its end and reads as zeros.
 template <bool M32> struct ResTok {
   uint4 k;
   Raw8rt v;
@@ -829,11 +829,16 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // all eight waves of a CU queue there). ----
   ResRsrc<M32> rres;
   rres.make(P, ((size_t)b * Hkv + kvh) * R, wave_res);
-  // slot of the wave's token i of pass p0, clamped to the slice (masked where it is used)
-  auto res_slot = [&](int p0, int i) { return t_lo + max(0, min(p0 + 4 * wave + i, rcount - 1)); };
+  // slot of the wave's token i of pass p0; past the slice a slot past the window's end, which reads as
+  // zeros (the probability there is 0, and the slice's last token in its place made NaN of 0 times an
+  // infinite value).  (R is a power of two past every slot; written as a choice it cost three registers,
+  // and 8 .. 28 bytes of scratch in the variants that have none to spare.)
+  auto res_slot = [&](int p0, int i) {
+    const int j = p0 + 4 * wave + i;
+    return (t_lo + j) | (((rcount - 1 - j) >> 31) & R);
+  };
 #if OSCAR_MFMA_STEP
   // the new token is the window's last; every wave of the workgroup that owns it has it in registers
-  // (slot numbers past a wave's tokens are clamped to the slice's last one, which it then is)
   const bool has_new = step_ok && rcount > 0 && t_lo + rcount == r;
   // (its loads go first here, the work on it waits until everything has been asked for)
   ResTok<M32> tok_new;
@@ -846,7 +851,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     knew.load(kn, 8 * cg);
     tok_new.v.load(vn, 8 * cg);
   }
-  auto is_new = [&](int p0, int i) { return has_new && res_slot(p0, i) == r - 1; };
+  auto is_new = [&](int p0, int i) { return has_new && p0 + 4 * wave + i == rcount - 1; };
 #endif
   ResTok<M32> rt_first[4];   // the wave's four tokens of the first residual pass
   if (wave_res) {

@@ -254,3 +254,40 @@ def test_published_page_layout_read_back_without_the_library(bits, kg, vg, meta)
     assert np.array_equal(rk[:, :, :nr], o.res_k[:, :, :nr])
     assert np.array_equal(rn[:, :, :nr], o.res_norm[:, :, :nr])
     assert g.seq_lens.tolist() == [w.context] * w.batch and g.res_lens.tolist() == [nr] * w.batch
+
+
+# ------------------------------------------------------- the end of the residual window --
+@pytest.mark.parametrize("meta", ["f16", "f32"])
+@pytest.mark.parametrize("splits", [1, 2, 20])
+@pytest.mark.parametrize("step", [False, True])
+@pytest.mark.parametrize("window", [1, 2, 3, 4, 5, 6, 7, 15, 17, 22, 33, 127])
+def test_an_infinite_last_token_gives_infinities(window, step, splits, meta):
+    """The register slots behind the window's last token are empty: an infinite value in that token
+    (appended before or by the step itself) gives infinite outputs in its channel, and nothing else changes."""
+    import torch
+    from paper_2605_19660_amd import binding as ob
+    cfg = ob.Config(4, 2, io_dtype=ob.BF16, meta_dtype=ob.F32 if meta == "f32" else ob.F16)
+    n = 128 + window
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(window)
+    x = torch.randn(2, 1, n, 2, 128, device="cuda", generator=gen).bfloat16()
+    q = torch.randn(1, 4, 128, device="cuda", generator=gen).bfloat16()
+    outs = []
+    for bad in (False, True):
+        k, v = x[0], x[1].clone()
+        if bad:
+            v[0, -1, 0, 3], v[0, -1, 0, 4] = float("inf"), float("-inf")
+        c = ob.Cache(cfg, 1, 2)
+        out = torch.empty(1, 4, 128, device="cuda")
+        ws = torch.empty(ob.decode_workspace_bytes(cfg, 1, splits), dtype=torch.uint8, device="cuda")
+        if step:
+            ob.quantize_append(c, k[:, :-1].contiguous(), v[:, :-1].contiguous(), eager=True, max_seq_len_hint=0)
+            ob.decode_step(c, k[:, -1:].contiguous(), v[:, -1:].contiguous(), q, out, ws, splits, n)
+        else:
+            ob.quantize_append(c, k, v, eager=True, max_seq_len_hint=0)
+            ob.decode_attn(c, q, out=out, max_seq_len_hint=n, num_splits=splits, workspace=ws)
+        outs.append(out)
+    good, got = outs
+    assert (got[0, :2, 3] == float("inf")).all() and (got[0, :2, 4] == float("-inf")).all()
+    got[0, :2, 3:5] = good[0, :2, 3:5]
+    assert torch.equal(good, got)

@@ -237,8 +237,8 @@ int oscar_decode_attn(const void *q, const oscar_cache *cache, void *out, int32_
  * call: oscar_quantize_append of ONE new token per sequence under the decode rule, then
  * oscar_decode_attn over the updated cache, in one trip through the ABI.  With fp16 metadata, the
  * published method and the norm per head the append happens inside the matrix-core kernel (one
- * launch less; with a single split that needs cache->tickets); cache bytes, lengths and outputs
- * are the bits of the two calls either way.
+ * launch less; with a single split that needs cache->tickets) wherever that is the faster form;
+ * cache bytes, lengths and outputs are the bits of the two calls either way.
  *   k_new, v_new : device, [batch][1][n_kv_heads][head_dim], io_dtype
  *   q, out, out_dtype, softmax_scale, num_splits, workspace: as in oscar_decode_attn
  *   max_seq_len_hint : upper bound on seq_lens[] AFTER this step's append (>= 1)

@@ -117,7 +117,7 @@ extern "C" size_t oscar_decode_workspace_bytes(const oscar_config* cfg, int32_t 
 // Compute units of the current device, asked of the runtime once per device and process
 // (the attribute query is far cheaper than a full property read, and a decode step must not
 // pay either on every call).  256 (one MI355X) if the runtime cannot tell.
-static int compute_units_of_current_device() {
+int oscar_compute_units() {
   constexpr int kMaxDev = 64;
   static std::atomic<int> cached[kMaxDev];
   int dev = 0;
@@ -139,7 +139,7 @@ static int compute_units_of_current_device() {
 extern "C" int32_t oscar_decode_auto_splits(const oscar_config* cfg, int32_t batch,
                                             int32_t max_seq_len) {
   if (!cfg || batch <= 0 || cfg->n_kv_heads <= 0) return 1;
-  const int n_cu = compute_units_of_current_device();
+  const int n_cu = oscar_compute_units();
   const int pages = max_seq_len > 0 ? (max_seq_len + OSCAR_R - 1) / OSCAR_R : 1;
   const int units = batch * cfg->n_kv_heads;
   // two workgroups (8 waves) per CU are resident at a time (one for the register-hungry

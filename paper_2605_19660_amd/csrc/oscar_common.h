@@ -145,6 +145,8 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 
 // Host-side validation shared by the entry points.
 int oscar_validate_config(const oscar_config* cfg);
+// Compute units of the current device (asked for once a device).
+int oscar_compute_units();
 
 // the pair of events behind the measurement-aid entry points
 struct oscar_timer {

@@ -631,7 +631,16 @@ __device__ __forceinline__ int row_hi(int h) { return 4 * (h & 3) + 2 * (h >> 2)
 // 19.8 / 29.3; (4,1,1,4) 14.6 / 15.1, 41.6 / 39.2, 15.4 / 15.4; (4,1,2,4) 15.1 / 16.7, 43.6 / 42.2,
 // 15.8 / 16.5; (4,1,4,1) 14.3 / 14.2, 40.9 / 38.7, 15.4 / 22.6; (4,2,1,4) 16.2 / 22.5, 25.6 / 38.5,
 // 20.5 / 24.3; (4,2,1,1) 13.6 / 14.1, 29.6 / 25.9, 18.1 / 22.5.  Two per CU where no size pays for it.
-__host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv, bool m32) {
+//
+// The step's kernel holds the new token beside all that: five variants that run at two per CU without
+// it (step_one_per_cu) would keep 64 .. 120 bytes of a lane in scratch and run at one; the launcher
+// takes them only where a CU gets no second workgroup anyway (step_form_pays).
+__host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, int ngv) {
+  if (bits == 2) return hp == 2 && ngk == 4 && ngv == 4;
+  return hp == 1 ? ngk == 4 && ngv < 4 : ngk <= 2 && ngv == 1;
+}
+__host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv, bool m32, bool step) {
+  if (step && step_one_per_cu(bits, hp, ngk, ngv)) return 1;
   if (!m32) return oscar_decode_mfma_wgs_per_cu(bits, hp, ngk, ngv);
   if (bits == 2) return (hp == 1 ? ngk < 4 || ngv < 4 : ngk < 4) ? 2 : 1;
   return hp == 1 && (ngk == 1 || (ngk == 2 && ngv <= 2)) ? 2 : 1;
@@ -716,7 +725,7 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& ld
 //    draws the cache's ticket as soon as it has the lengths, so that whoever draws the last one knows
 //    that all have read them, and advances them at its end.
 template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32, bool STEP>
-__global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
+__global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32, STEP))
 void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr int TPG = 8 / NGK;  // token tiles per key group
   constexpr int CPG = 8 / NGV;  // channel tiles per value group
@@ -1724,12 +1733,29 @@ int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t 
   return launch_this_form(P, gq, grid, st, e0, e1);
 }
 
-// The same for a whole decode step (fp16 metadata); OSCAR_ERR_UNSUPPORTED: append and attention as two
-// calls.
+// Whether a step is faster with the append inside the attention kernel than as two calls.  It is in
+// most variants (1.01 .. 1.32 times, device time of 128 steps with one flush a sequence, batch 1 .. 64,
+// 0.5K .. 32K tokens).  Not in these, whose step kernel runs out of registers:
+//  * five run at one workgroup a CU.  A grid of at most a workgroup a CU: 0.98 .. 1.19 times (batch 1 x
+//    32K, 31 splits, 4-bit, G_k = 32, G_v = 64: 15.6 us against 18.0); a larger one: 0.80 .. 1.01 (batch
+//    8 x 8K, 8 splits: 25.9 against 24.6).  At two a CU, out of scratch: 0.85 .. 1.17, below 1 with one
+//    split and with a full round.
+//  * 2-bit, more than four query heads per kv head, G_k = 32 and G_v above 32, at two a CU with 80 bytes
+//    of scratch: 1.02 .. 1.19 with several splits, 0.95 .. 1.00 with one.
+static bool step_form_pays(const DecodeParams& P, int gq, dim3 grid) {
+  const int hp = gq <= 4 ? 1 : 2;
+  if (step_one_per_cu(P.g.bits, hp, P.g.ngk, P.g.ngv))
+    return (unsigned long long)grid.x * grid.y * grid.z <= (unsigned long long)oscar_compute_units();
+  return !(P.g.bits == 2 && hp == 2 && P.g.ngk == 4 && P.num_splits == 1);
+}
+
+// The same launch for a whole decode step (fp16 metadata); OSCAR_ERR_UNSUPPORTED: append and attention
+// as two calls.
 int oscar_launch_decode_step_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
                                   hipEvent_t e0, hipEvent_t e1) {
   const DecodeParams& P = *reinterpret_cast<const DecodeParams*>(params);
-  if (!mfma_takes(P) || P.c.cfg.meta_dtype != OSCAR_F16) return OSCAR_ERR_UNSUPPORTED;
+  if (!mfma_takes(P) || P.c.cfg.meta_dtype != OSCAR_F16 || !step_form_pays(P, gq, grid))
+    return OSCAR_ERR_UNSUPPORTED;
   return P.c.cfg.zp_mode == OSCAR_ZP_MIN ? oscar_launch_decode_step_this_zpmin(params, gq, grid, st, e0, e1)
                                          : oscar_launch_decode_step_this(params, gq, grid, st, e0, e1);
 }

@@ -80,3 +80,91 @@ def test_a_sequence_whose_page_table_is_full_stays_as_it_is(splits):
     c = _run(w, [256, 20], 1, splits, 3)
     assert c.seq_lens.tolist() == [256, 23] and c.res_lens.tolist() == [128, 23]
     assert int(c.dev_status.item()) == _ob().ERR_CAPACITY
+
+
+# ---- which calls take the fused form: the launches of one captured step ------------------------------
+FUSED, TWO_CALLS = "fused", "two calls"
+
+
+def _launches(fn):
+    """Kernel launches of fn() (its graph's nodes, all of them kernels)."""
+    import ctypes as C
+    import torch
+    ob = _ob()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    count, kind = C.c_size_t(0), C.c_int(-1)
+    raw = C.c_void_p(graph.raw_cuda_graph())
+    assert ob.lib().hipGraphGetNodes(raw, None, C.byref(count)) == 0
+    nodes = (C.c_void_p * count.value)()
+    assert ob.lib().hipGraphGetNodes(raw, nodes, C.byref(count)) == 0
+    for node in nodes:
+        assert ob.lib().hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0 and kind.value == 0   # a kernel
+    return count.value
+
+
+def _route(splits, batch=2, gq=4, hkv=2, generic=False, tickets=True, **cfg):
+    import torch
+    ob = _ob()
+    cfg = ob.Config(gq * hkv, hkv, **cfg)
+    c = ob.Cache(cfg, batch, 3, fused=tickets)
+    kv = torch.randn(batch, 1, hkv, 128, device="cuda").bfloat16()
+    q = torch.randn(batch, gq * hkv, 128, device="cuda").bfloat16()
+    out = torch.empty(batch, gq * hkv, 128, device="cuda")
+    ws = torch.empty(ob.decode_workspace_bytes(cfg, batch, splits), dtype=torch.uint8, device="cuda")
+    ob.debug_force_generic_decode(generic)
+    step = lambda: ob.decode_step(c, kv, kv, q, out, ws, splits, 1)
+    step()
+    n = _launches(step)
+    ob.debug_force_generic_decode(False)
+    append = 1 if tickets else 2   # without tickets the length update is its own launch
+    reduce = 1 if splits > 1 or generic else 0
+    if n == 1 + reduce and not generic:
+        return FUSED
+    assert n == append + 1 + reduce, n
+    return TWO_CALLS
+
+
+@pytest.mark.parametrize("splits", [1, 2, 5, 20])
+@pytest.mark.parametrize("bits,kg,vg,gq,zp", [(2, 128, 32, 4, 0), (4, 32, 32, 4, 1), (2, 64, 128, 1, 0),
+                                              (4, 128, 32, 7, 0), (2, 32, 32, 7, 0), (4, 32, 64, 4, 0)])
+def test_the_usual_step_is_fused(bits, kg, vg, gq, zp, splits):
+    assert _route(splits, bits=bits, k_group=kg, v_group=vg, gq=gq, zp_mode=zp) == FUSED
+
+
+def test_steps_outside_the_fused_form():
+    ob = _ob()
+    assert _route(2, meta_dtype=ob.F32) == TWO_CALLS
+    assert _route(2, norm_scope=ob.NORM_ALL_KV_HEADS) == TWO_CALLS
+    assert _route(2, rotation=ob.ROTATION_OFF) == TWO_CALLS
+    assert _route(2, scale_mode=ob.SCALE_MAX) == TWO_CALLS
+    assert _route(2, generic=True) == TWO_CALLS
+    assert _route(1, tickets=False) == TWO_CALLS
+    assert _route(2, tickets=False) == FUSED
+
+
+@pytest.mark.parametrize("bits,kg,vg,gq", [(2, 32, 32, 7), (4, 32, 64, 4), (4, 32, 128, 4), (4, 128, 128, 7),
+                                           (4, 64, 128, 7)])
+def test_variants_without_registers_to_spare_are_fused_up_to_a_workgroup_a_cu(bits, kg, vg, gq):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    at = lambda splits, batch: _route(splits, batch=batch, hkv=1, bits=bits, k_group=kg, v_group=vg, gq=gq)
+    assert at(1, cus) == FUSED and at(2, cus // 2) == FUSED
+    assert at(1, cus + 1) == TWO_CALLS and at(2, cus // 2 + 1) == TWO_CALLS
+
+
+@pytest.mark.parametrize("vg", [64, 128])
+def test_the_variants_that_need_several_splits(vg):
+    assert _route(1, bits=2, k_group=32, v_group=vg, gq=7) == TWO_CALLS
+    assert _route(2, bits=2, k_group=32, v_group=vg, gq=7) == FUSED
+
+
+@pytest.mark.parametrize("splits", [1, 6])
+@pytest.mark.parametrize("bits,kg,vg,gq", [(4, 32, 64, 4), (4, 32, 128, 3), (4, 128, 128, 7), (4, 64, 128, 8),
+                                           (2, 32, 128, 6)])
+def test_bits_of_the_variants_without_registers_to_spare(bits, kg, vg, gq, splits):
+    starts = [0, 126, 128, 384, 511]
+    w = synth.LLAMA8B_32K.replace(batch=5, n_q_heads=gq, n_kv_heads=1, context=511 + 4, bits=bits, k_group=kg,
+                                  v_group=vg)
+    _run(w, starts, 6, splits, 4, zp=splits & 1)

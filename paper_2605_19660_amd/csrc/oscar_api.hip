@@ -144,11 +144,14 @@ extern "C" int32_t oscar_decode_auto_splits(const oscar_config* cfg, int32_t bat
   const int units = batch * cfg->n_kv_heads;
   // two workgroups (8 waves) per CU are resident at a time (one for the register-hungry
   // variants, see oscar_decode_mfma_wgs_per_cu) and every wave wants at least two pages: aim
-  // at one round of workgroups
+  // at one round of workgroups.  (A variant of one a CU cut for two makes two rounds: fp32 metadata,
+  // batch 8 x 16K, 8 / 4 splits, 40.3 / 34.4 us at INT2, G_k = G_v = 32, 41.2 / 34.2 at INT4, GQA 7,
+  // G_k = G_v = 128.)
   const int gq = cfg->n_kv_heads > 0 ? cfg->n_q_heads / cfg->n_kv_heads : 1;
   const int ngk = cfg->k_group > 0 ? OSCAR_R / cfg->k_group : 1;
   const int ngv = cfg->v_group > 0 ? OSCAR_D / cfg->v_group : 1;
-  const int resident = oscar_decode_mfma_wgs_per_cu(cfg->bits, gq > 4 ? 2 : 1, ngk, ngv);
+  const int resident = oscar_decode_mfma_wgs_per_cu(cfg->bits, gq > 4 ? 2 : 1, ngk, ngv,
+                                                    cfg->meta_dtype == OSCAR_F32);
   int splits = (resident * n_cu) / units;
   const int max_by_pages = pages / 8 > 0 ? pages / 8 : 1;
   if (splits > max_by_pages) splits = max_by_pages;

@@ -167,11 +167,23 @@ void oscar_launch_decode_reduce(const float* ws, void* out, int num_splits, int 
 int oscar_check_append(const void* k, const void* v, int32_t T, const oscar_cache* cache,
                        int32_t max_seq_len_hint, uint32_t flags);
 
-// Matrix-core partial pass (params = the decode parameter block); returns
-// OSCAR_ERR_UNSUPPORTED when the configuration must take the generic kernel.
 // Resident workgroups per CU of the matrix-core decode kernel for a variant (bits, head slots,
-// key groups per page, value groups); the launch bounds and the split heuristic share it.
-__host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv) {
+// key groups per page, value groups, fp32 metadata); the launch bounds and the split heuristic share it.
+// Two wherever the registers allow it with little or no scratch memory; the rest run one and their
+// overflow lives in accumulation registers.
+__host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv, bool m32) {
+  if (m32) {
+    // fp32 metadata takes up to 68 registers more for the same page, its page sums fewer than the running
+    // ones.  Measured at one / two per CU, each with its own split count (whole call in us, batch 4 x 8K,
+    // 8 x 16K and 1 x 1K): (2,1,1,4) 16.0 / 15.5, 32.1 / 29.3, 15.4 / 15.3; (2,1,4,4) 17.9 / 21.6,
+    // 34.4 / 38.7, 16.5 / 19.4; (2,2,1,4) 20.8 / 20.2, 41.2 / 35.9, 21.8 / 21.5; (2,2,2,4) 21.7 / 24.3,
+    // 43.6 / 41.4, 22.2 / 23.4; (2,2,4,1) 18.7 / 19.6, 35.7 / 33.3, 20.3 / 27.9; (4,1,1,4) 17.6 / 18.1,
+    // 38.4 / 40.2, 16.5 / 16.3; (4,1,1,1) 16.4 / 16.3, 32.8 / 36.2, 14.5 / 14.2; (4,1,2,4) 20.5 / 22.0,
+    // 41.3 / 46.1, 16.7 / 18.3; (4,1,4,1) 16.9 / 18.1, 37.8 / 41.6, 15.1 / 21.8; (4,2,1,4) 22.6 / 33.6,
+    // 44.1 / 60.0, 22.4 / 24.8; (4,2,1,1) 17.6 / 18.2, 34.2 / 38.4, 18.9 / 22.6.
+    if (bits == 2) return (hp == 1 ? ngk < 4 || ngv < 4 : ngk < 4) ? 2 : 1;
+    return hp == 1 && (ngk == 1 || (ngk == 2 && ngv <= 2)) ? 2 : 1;
+  }
   // (measured, partial pass in us at one / two per CU: (4,1,4,4) 65 / 73 with 13 registers in
   // scratch, (4,2,1,4) 35 / 38, (4,2,2,4) 37 / 43; the other way round (2,2,4,4) 39 / 33,
   // (2,2,2,4) 34 / 30, (4,1,2,4) 62 / 60, (4,1,4,1) 62 / 59, (4,1,4,2) 63 / 61)
@@ -179,6 +191,9 @@ __host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp,
   if (bits == 2) return 2;
   return (ngv == 1 && ngk <= 2) ? 2 : 1;
 }
+
+// Matrix-core partial pass (params = the decode parameter block); returns
+// OSCAR_ERR_UNSUPPORTED when the configuration must take the generic kernel.
 int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t st,
                              hipEvent_t e0, hipEvent_t e1);
 // The same with the step's new token appended on the way (params->k_new, v_new).

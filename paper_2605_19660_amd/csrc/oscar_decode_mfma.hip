@@ -623,27 +623,12 @@ __device__ __forceinline__ int row_hi(int h) { return 4 * (h & 3) + 2 * (h >> 2)
 // (measured: 4-bit, G_k = 32 took 188 us with 65 spilled registers at two per CU, 76 us at
 // one).
 //
-// fp32 metadata takes up to 68 registers more for the same page, the exact page sums fewer than the
-// running ones.  Measured at one / two per CU (attention alone, us, batch 4 x 8K, 8 x 16K and
-// 1 x 1K; the plain-ALU kernel these variants replaced: 54, 210 and 59 at GQA 4, 80, 186 and 85 at
-// GQA 7): (2,1,1,4) 13.4 / 13.0, 28.8 / 27.5, 14.9 / 14.7; (2,1,4,4) 13.9 / 17.0, 38.0 / 37.0,
-// 16.1 / 18.5; (2,2,1,4) 15.1 / 14.6, 33.0 / 24.2, 20.2 / 19.6; (2,2,4,1) 14.9 / 14.6, 31.8 / 23.7,
-// 19.8 / 29.3; (4,1,1,4) 14.6 / 15.1, 41.6 / 39.2, 15.4 / 15.4; (4,1,2,4) 15.1 / 16.7, 43.6 / 42.2,
-// 15.8 / 16.5; (4,1,4,1) 14.3 / 14.2, 40.9 / 38.7, 15.4 / 22.6; (4,2,1,4) 16.2 / 22.5, 25.6 / 38.5,
-// 20.5 / 24.3; (4,2,1,1) 13.6 / 14.1, 29.6 / 25.9, 18.1 / 22.5.  Two per CU where no size pays for it.
-//
 // The step's kernel holds the new token beside all that: five variants that run at two per CU without
 // it (step_one_per_cu) would keep 64 .. 120 bytes of a lane in scratch and run at one; the launcher
 // takes them only where a CU gets no second workgroup anyway (step_form_pays).
 __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, int ngv) {
   if (bits == 2) return hp == 2 && ngk == 4 && ngv == 4;
   return hp == 1 ? ngk == 4 && ngv < 4 : ngk <= 2 && ngv == 1;
-}
-__host__ __device__ constexpr int decode_mfma_wgs_per_cu(int bits, int hp, int ngk, int ngv, bool m32, bool step) {
-  if (step && step_one_per_cu(bits, hp, ngk, ngv)) return 1;
-  if (!m32) return oscar_decode_mfma_wgs_per_cu(bits, hp, ngk, ngv);
-  if (bits == 2) return (hp == 1 ? ngk < 4 || ngv < 4 : ngk < 4) ? 2 : 1;
-  return hp == 1 && (ngk == 1 || (ngk == 2 && ngv <= 2)) ? 2 : 1;
 }
 
 #if OSCAR_MFMA_STEP
@@ -725,7 +710,8 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& ld
 //    draws the cache's ticket as soon as it has the lengths, so that whoever draws the last one knows
 //    that all have read them, and advances them at its end.
 template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32, bool STEP>
-__global__ __launch_bounds__(256, decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32, STEP))
+__global__ __launch_bounds__(256, STEP && step_one_per_cu(BITS, HP, NGK, NGV)
+                                  ? 1 : oscar_decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
 void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr int TPG = 8 / NGK;  // token tiles per key group
   constexpr int CPG = 8 / NGV;  // channel tiles per value group

@@ -75,6 +75,24 @@ def test_null_arguments_are_rejected_before_any_launch():
     assert ob.decode_workspace_bytes(ob.Config(32, 8), 8, 16) == 8 * 32 * 16 * 130 * 4
 
 
+@pytest.mark.parametrize("bits,q_heads,kg,vg", [(2, 32, 32, 32), (2, 56, 32, 32), (2, 56, 32, 64), (2, 56, 32, 128),
+                                                (4, 32, 64, 32), (4, 32, 32, 64), (4, 32, 32, 128),
+                                                (4, 56, 128, 128), (4, 56, 64, 128)])
+def test_fp32_metadata_variants_of_one_workgroup_a_cu_are_cut_for_one(bits, q_heads, kg, vg):
+    """Host only: fp16 metadata runs these at two a CU, fp32 metadata at one (256 CUs assumed without a
+    device, 64 units of work), and one round of workgroups is what the split count aims at."""
+    cfg = lambda meta: ob.Config(q_heads, 8, bits=bits, k_group=kg, v_group=vg, meta_dtype=meta)
+    assert ob.decode_auto_splits(cfg(ob.F16), 8, 32768) == 8
+    assert ob.decode_auto_splits(cfg(ob.F32), 8, 32768) == 4
+    assert ob.decode_auto_splits(cfg(ob.F32), 1, 4096) == 4      # 32 pages / 8, either way
+
+
+def test_fp32_metadata_variants_of_two_workgroups_a_cu_keep_their_splits():
+    for bits, q_heads, kg, vg in ((2, 32, 128, 32), (2, 56, 128, 32), (2, 56, 64, 32), (4, 32, 128, 32), (4, 32, 64, 64)):
+        assert ob.decode_auto_splits(ob.Config(q_heads, 8, bits=bits, k_group=kg, v_group=vg, meta_dtype=ob.F32),
+                                     8, 32768) == 8
+
+
 def test_split_heuristic_and_host_side_argument_checks_of_the_aids():
     """Host logic that needs no GPU: the split count aims at one round of resident workgroups
     (two per CU, one for the register-hungry two-slot variants; 256 CUs assumed without a device)

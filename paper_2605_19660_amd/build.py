@@ -65,9 +65,10 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
     return _link(LIB, objs, verbose)
 
 
-# The same library with phase time stamps in the matrix-core decode kernel (phase_profile.py):
-# only the two translation units of that kernel are compiled again.
-STAMPED = ("oscar_decode_mfma.hip", "oscar_decode_mfma_zpmin.hip")
+# The same library with phase time stamps in the matrix-core decode kernel, attention alone and decode
+# step, fp16 metadata (phase_profile.py): only those translation units are compiled differently.
+STAMPED = ("oscar_decode_mfma.hip", "oscar_decode_mfma_zpmin.hip", "oscar_decode_step.hip",
+           "oscar_decode_step_zpmin.hip")
 LIB_STAMPS = os.path.join(HERE, "liboscar_hip_stamps.so")
 
 

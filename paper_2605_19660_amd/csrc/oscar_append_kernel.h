@@ -4,9 +4,10 @@
 // algorithm"; key transform of App. "Implementation Details ...", "Overall Design";
 // quantizer of Eq. 3-4).
 //
-// Every translation unit that includes this header is compiled with -ffp-contract=off:
-// the encoder is an encoding, and its fp32 operation order is part of the format (codes
-// must not depend on whether a multiply-add was fused).
+// The encoder is an encoding, and its fp32 operation order is part of the format (codes must
+// not depend on whether a multiply-add was fused): its own translation units are compiled with
+// -ffp-contract=off, and for the fused decode step, which is not, the pragma below says the same
+// for everything in this header.
 //
 // Work decomposition: one workgroup of 256 threads per (sequence, kv head, block of
 // R=128 pending tokens).  A thread owns 8 channels (channel group cg) of token

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(128) void oscar_decode_reduce_kernel(const float* w
 // and the partial outputs are dealt to four waves, two channels a lane, so that every load of the
 // block is in flight before the first is waited for; the kernel above reads the statistics twice and
 // then walks the partials four at a time, three rounds of memory latency for what takes one here
-// (in the trace: 64 splits x 32 heads 6.2 -> 4.0 us, 32 splits x 112 heads 5.1 -> 4.0, most of it
+// (in the trace: 64 splits x 32 heads 6.2 -> 4.1 us, 32 splits x 112 heads 5.2 -> 4.6, most of it
 // the launch).
 __global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float* ws, void* out, int num_splits,
                                                                     int out_dtype, StepLens lens) {

@@ -37,7 +37,7 @@
 
 #include "oscar_decode_common.h"
 
-// This file is compiled four times: as it stands for the integer zero-point of Eq. 3-4, and through
+// This file is compiled six times: as it stands for the integer zero-point of Eq. 3-4, and through
 // oscar_decode_mfma_zpmin.hip with OSCAR_MFMA_ZPMIN = 1 for the float zero-point form; the
 // zero-point form is a compile-time constant of the kernel (no branches in the page loop), and
 // the two sets of variants compile side by side.
@@ -1651,6 +1651,20 @@ int launch_this_form(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, h
 
 }  // namespace
 
+#if defined(OSCAR_DECODE_STAMPS) && !OSCAR_MFMA_ZPMIN && !OSCAR_MFMA_META32
+// [8 workgroup slots][4 waves][32 stamps] of the last stamped launch (integer zero-point variants) of the
+// attention alone, and of the decode step
+#if OSCAR_MFMA_STEP
+#define OSCAR_READ_STAMPS oscar_debug_read_step_stamps
+#else
+#define OSCAR_READ_STAMPS oscar_debug_read_stamps
+#endif
+extern "C" int OSCAR_READ_STAMPS(void* dst, size_t bytes) {
+  if (!dst || bytes != sizeof(g_stamps)) return OSCAR_ERR_INVALID_ARG;
+  return hipMemcpyFromSymbol(dst, HIP_SYMBOL(g_stamps), sizeof(g_stamps)) == hipSuccess ? OSCAR_OK : OSCAR_ERR_HIP;
+}
+#endif
+
 // the other translation units' entries
 #define OSCAR_MFMA_FORM(NAME) \
   int NAME(const void* params, int gq, dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
@@ -1674,14 +1688,6 @@ OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32);
 OSCAR_MFMA_FORM(oscar_launch_decode_mfma_meta32_zpmin);
 OSCAR_MFMA_FORM(oscar_launch_decode_step_this);
 OSCAR_MFMA_FORM(oscar_launch_decode_step_this_zpmin);
-
-#ifdef OSCAR_DECODE_STAMPS
-// [8 workgroup slots][4 waves][32 stamps] of the last stamped launch (integer zero-point variants)
-extern "C" int oscar_debug_read_stamps(void* dst, size_t bytes) {
-  if (!dst || bytes != sizeof(g_stamps)) return OSCAR_ERR_INVALID_ARG;
-  return hipMemcpyFromSymbol(dst, HIP_SYMBOL(g_stamps), sizeof(g_stamps)) == hipSuccess ? OSCAR_OK : OSCAR_ERR_HIP;
-}
-#endif
 
 // Test / profiling switch of oscar_debug_force_generic_decode: the only process-wide state of
 // the library besides the cached device properties, one relaxed atomic flag read per launch.

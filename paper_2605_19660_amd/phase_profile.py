@@ -1,6 +1,6 @@
 """Where one launch of the matrix-core decode kernel spends its time, from inside the kernel.
 
-    python -m paper_2605_19660_amd.phase_profile [--workload N] [--reps K]
+    python -m paper_2605_19660_amd.phase_profile [--workload N] [--reps K] [--step]
 
 Runs the library built with phase time stamps (`python -m paper_2605_19660_amd.build --stamps`,
 built here if missing): lane 0 of every wave of the first four and the last four workgroups of the
@@ -9,6 +9,8 @@ kernel's phases.  The script keeps the GPU busy for a while (clocks), launches t
 between two events on a cache copy that is not in the last-level cache, reads the stamps back
 and prints them in microseconds after the earliest entry among the sampled workgroups.  The
 stamps themselves cost a scalar memory instruction and a wait each (about 1 % of the kernel).
+The launch is the attention alone; with --step it is the decode step's kernel, which appends a token
+per sequence on the way.
 """
 from __future__ import annotations
 
@@ -30,6 +32,7 @@ def main() -> None:
     ap.add_argument("--reps", type=int, default=3)
     ap.add_argument("--residual", type=int, default=0,
                     help="tokens appended one call behind the prefill (0..128): they stay in the 16-bit window")
+    ap.add_argument("--step", action="store_true", help="the decode step's kernel instead of the attention alone")
     args = ap.parse_args()
 
     lib_path = os.path.join(HERE, "liboscar_hip_stamps.so")
@@ -65,8 +68,12 @@ def main() -> None:
     splits = ob.decode_auto_splits(cfg, w.batch, w.context + args.residual)
     ws = torch.empty(ob.decode_workspace_bytes(cfg, w.batch, splits), dtype=torch.uint8, device="cuda")
     lib = ob.lib()
-    lib.oscar_debug_read_stamps.argtypes = [C.c_void_p, C.c_size_t]
-    lib.oscar_debug_read_stamps.restype = C.c_int
+    read_stamps = lib.oscar_debug_read_step_stamps if args.step else lib.oscar_debug_read_stamps
+    read_stamps.argtypes = [C.c_void_p, C.c_size_t]
+    read_stamps.restype = C.c_int
+    k1 = torch.randn(w.batch, 1, w.n_kv_heads, w.head_dim, device="cuda").to(ob.torch_dtype(io))
+    v1 = torch.randn_like(k1)
+    hint = w.context + args.residual + args.reps
 
     pages_per_wave = -(-(w.context // w.page_size) // (4 * splits))
     print("# workload %s: batch %d, %d kv heads, context %d, %d-bit; %d splits -> %d workgroups, %d pages per wave"
@@ -84,14 +91,17 @@ def main() -> None:
                 i += 1
             torch.cuda.synchronize()
         tm = ob.Timer()
-        ob.decode_attn_partial(caches[i % n_copies], q, ws, splits, timer=tm)
+        if args.step:
+            ob.decode_step(caches[i % n_copies], k1, v1, q, out, ws, splits, hint, timer=tm)
+        else:
+            ob.decode_attn_partial(caches[i % n_copies], q, ws, splits, timer=tm)
         torch.cuda.synchronize()
         ev_us = tm.elapsed_us()
         tm.close()
         buf = (C.c_ulonglong * (8 * 4 * 32))()
-        rc = lib.oscar_debug_read_stamps(buf, C.sizeof(buf))
+        rc = read_stamps(buf, C.sizeof(buf))
         if rc != 0:
-            sys.exit("oscar_debug_read_stamps failed: %d" % rc)
+            sys.exit("reading the stamps failed: %d" % rc)
         a = np.frombuffer(buf, dtype=np.uint64).reshape(8, 4, 32).astype(np.int64)
         t_first = a[:, :, 0].min()
         print("\n# launch %d: %.2f us between its two events; last stamp %.2f us after the first"

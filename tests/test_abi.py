@@ -180,3 +180,14 @@ def test_time_stamped_variant_exports_the_same_entry_points_and_its_reader():
     lib.oscar_debug_read_stamps.restype = C.c_int
     assert lib.oscar_debug_read_stamps(None, 0) == ob.ERR_INVALID_ARG
     assert not hasattr(ob.lib(), "oscar_debug_read_stamps")
+
+
+def test_the_stamped_build_stamps_the_decode_step_too():
+    path = os.path.join(os.path.dirname(ob.LIB_PATH), "liboscar_hip_stamps.so")
+    if not os.path.exists(path):
+        pytest.skip("liboscar_hip_stamps.so not built (python -m paper_2605_19660_amd.build --stamps)")
+    lib = C.CDLL(path)
+    lib.oscar_debug_read_step_stamps.argtypes = [C.c_void_p, C.c_size_t]
+    lib.oscar_debug_read_step_stamps.restype = C.c_int
+    assert lib.oscar_debug_read_step_stamps(None, 0) == ob.ERR_INVALID_ARG
+    assert not hasattr(ob.lib(), "oscar_debug_read_step_stamps")

@@ -14,9 +14,10 @@ twice the 256 MB last-level cache.
 Prints ONE JSON line: metric / value / unit / step counts / config, plus
   parity             a sampled (sequence, kv head) stream of the workload checked against the CPU
                      oracle before anything is timed (codes bit for bit, decode output in tolerance),
-  roofline           the split-K partial kernel: algorithmic bytes per launch over its mean device
-                     time (HIP events attached to every 5th dispatch of the timed region), against
-                     8 TB/s; `traffic` = HBM bytes per launch from FETCH_SIZE / WRITE_SIZE counter runs,
+  roofline           the split-K partial kernel, with the step's append where that is part of it:
+                     algorithmic bytes per launch over its mean device time (HIP events attached to
+                     every 5th dispatch of the timed region), against 8 TB/s; `traffic` = HBM bytes
+                     per launch from FETCH_SIZE / WRITE_SIZE counter runs,
   stream_read_probe  the same timing method on a loads-only kernel of the same launch shape,
   quantize_append_prefill, bf16_decode (the 16-bit comparator), cpu_baseline (the CPU oracle),
   other_workloads    compact records of the other configurations the benchmark description names
@@ -38,28 +39,57 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0       # MI355X published HBM3E bandwidth
-# HBM bytes per launch of the decode kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs,
-# each scaled by the same counter's reading for a plain 256 MiB copy kernel (summary under
-# profiles/); counters cannot be read from inside this process, so the figure is keyed by
-# the workload it was measured on and reported as null for any other.
-MEASURED_TRAFFIC = {("llama3-8b-like-b8-s32k", 2, 8): 182_300_126,
-                    ("long-b1-s128k", 2, 64): 91_611_048,
-                    ("omni-b4-g7-s64k", 2, 32): 92_713_848}
+# HBM bytes per launch of the step's kernel (append and split-K partial pass) from rocprofv3 --pmc
+# FETCH_SIZE / WRITE_SIZE runs, each scaled by the same counter's reading for a plain 256 MiB copy
+# kernel (summary under profiles/); counters cannot be read from inside this process, so the figure is
+# keyed by the workload it was measured on and reported as null for any other, and for steps whose
+# append is a launch of its own.
+MEASURED_TRAFFIC = {("llama3-8b-like-b8-s32k", 2, 8): 182_524_624,
+                    ("long-b1-s128k", 2, 64): 91_676_686,
+                    ("highbatch-b64-s8k", 2, 1): 364_729_390,
+                    ("omni-b4-g7-s64k", 2, 32): 92_786_727}
 # The same kernel's mean duration over the decode steps in the committed `rocprofv3
 # --kernel-trace` summaries (the dispatch's own begin/end timestamps), for comparison with the
 # figure measured here: an event pair around a launch also holds the queue's hand-over from the
 # event marker to the dispatch and reads 2-3 us more.  The kernel includes the step's append.  Keyed
 # like MEASURED_TRAFFIC.
-PROFILED_KERNEL_US = {("llama3-8b-like-b8-s32k", 2, 8): 34.27,
-                      ("long-b1-s128k", 2, 64): 21.54,
-                      ("omni-b4-g7-s64k", 2, 32): 25.63,
-                      ("highbatch-b64-s8k", 2, 1): 70.94,
-                      ("highbatch-b64-s8k", 4, 1): 119.06}
+PROFILED_KERNEL_US = {("llama3-8b-like-b8-s32k", 2, 8): 34.05,
+                      ("long-b1-s128k", 2, 64): 21.69,
+                      ("omni-b4-g7-s64k", 2, 32): 26.35,
+                      ("highbatch-b64-s8k", 2, 1): 69.44,
+                      ("highbatch-b64-s8k", 4, 1): 117.75}
 
 
-def profiled(w, splits, cache_bytes):
+def step_launches(cache, k_new, v_new, q, out, ws, splits, hint, torch, ob):
+    """Launches of one decode step, counted in a captured graph that is not run."""
+    import ctypes
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        ob.decode_step(cache, k_new, v_new, q, out, ws, splits, hint)
+    n = ctypes.c_size_t(0)
+    if ob.lib().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) != 0:
+        raise RuntimeError("hipGraphGetNodes failed")
+    return n.value
+
+
+def append_in_partial(launches, splits):
+    """Whether those launches are the step's kernel (append and partial pass) and at most a reduce."""
+    return launches == (1 if splits == 1 else 2)
+
+
+def step_text(launches, splits):
+    if append_in_partial(launches, splits):
+        return "append 1 token/seq and decode attention in one launch" + (", reduce in a second" if splits > 1 else "")
+    return "append 1 token/seq, then decode attention (%d launches)" % launches
+
+
+def traffic(w, splits, launches):
+    return MEASURED_TRAFFIC.get((w.name, w.bits, splits)) if append_in_partial(launches, splits) else None
+
+
+def profiled(w, splits, cache_bytes, launches):
     us = PROFILED_KERNEL_US.get((w.name, w.bits, splits))
-    if us is None:
+    if us is None or not append_in_partial(launches, splits):
         return None
     return {"avg_kernel_us": us, "frac": cache_bytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBS,
             "summary": "profiles/decode_step_%s%s.txt" % (w.name, "-int4" if w.bits == 4 else ""),
@@ -307,6 +337,7 @@ def run_steps(args_steps, warmup, w, cfg, caches, q, new_k, new_v, out, ws, spli
     step's partial kernel carries an event pair, whatever the step count."""
     n_copies = len(caches)
     hint = w.context + warmup + args_steps + 1
+    launches = step_launches(caches[0], new_k[0], new_v[0], q, out, ws, splits, hint, torch, ob)
 
     def step(i, ev=None):
         ob.decode_step(caches[i % n_copies], new_k[i], new_v[i], q, out, ws, splits, hint,
@@ -344,7 +375,7 @@ def run_steps(args_steps, warmup, w, cfg, caches, q, new_k, new_v, out, ws, spli
     return {"us_step": wall / args_steps * 1e6, "span_us": g0.elapsed_time(g1) * 1e3 / args_steps,
             "enqueue_us": t_enq / args_steps * 1e6, "k_us": float(np.mean(k_samples)),
             "k_samples": len(k_samples), "k_list": [round(x, 2) for x in k_samples[:64]],
-            "preheat_launches": heat_launches}
+            "preheat_launches": heat_launches, "launches": launches}
 
 
 def step_inputs(w, io, total_steps, torch, ob):
@@ -384,8 +415,9 @@ def compact_record(args, w, np, torch, ob, synth, bf16=False, steps=200, warmup=
            "us_per_step": r["us_step"], "device_span_us_per_step": r["span_us"],
            "partial_us": r["k_us"], "hbm_gbs": gbs, "frac": gbs / HBM_PEAK_GBS,
            "algorithmic_bytes_per_launch": cache_bytes,
-           "traffic": MEASURED_TRAFFIC.get((w.name, w.bits, splits)),
-           "profiled": profiled(w, splits, cache_bytes),
+           "step": step_text(r["launches"], splits),
+           "traffic": traffic(w, splits, r["launches"]),
+           "profiled": profiled(w, splits, cache_bytes, r["launches"]),
            "decode_tokens_per_s": w.batch / (r["us_step"] * 1e-6),
            "resident_cache_bytes": cache_bytes, "cache_bytes_per_token_kv_head": bytes_tok,
            "prefill_tokens": w.batch * w.context, "prefill_us": pre_us,
@@ -579,16 +611,18 @@ def measure(args, w, np, torch, ob, synth):
                    "bits": w.bits, "k_group": w.k_group, "v_group": w.v_group,
                    "io_dtype": w.io_dtype,
                    "norm_scope": "all kv heads" if args.norm_all_heads else "per kv head",
-        "step": "oscar_decode_step: append 1 token/seq and decode attention in one launch, reduce in a second",
+                   "step": "oscar_decode_step: " + step_text(r["launches"], splits),
                    "splits": splits, "cache_copies_rotated": n_copies},
         "roofline": {"bound": "hbm",
-                     "kernel": "oscar_decode_mfma_kernel (append and split-K partial pass)",
+                     "kernel": ("oscar_decode_mfma_kernel (append and split-K partial pass)"
+                                if append_in_partial(r["launches"], splits) else
+                                "oscar_decode_mfma_kernel (split-K partial pass)"),
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": MEASURED_TRAFFIC.get((w.name, w.bits, splits)),
+                     "traffic": traffic(w, splits, r["launches"]),
                      "algorithmic_bytes_per_launch": cache_bytes,
                      "avg_kernel_us": k_us,
-                     "profiled": profiled(w, splits, cache_bytes)},
+                     "profiled": profiled(w, splits, cache_bytes, r["launches"])},
         "paper_context": "the paper reports, end to end on Qwen3-8B with one NVIDIA H20 141 GB (INT2, G=32, "
                          "FP16 residual): up to 3.0x decode speedup at 128K context, 5.3x smaller memory "
                          "footprint and 4.1x throughput against BF16 FlashDecoding-v2; other hardware and an "

@@ -239,8 +239,13 @@ __global__ __launch_bounds__(256) void oscar_rotate_columns_kernel(const IO* __r
 // back, the rows a register stands for simply follow.
 typedef float float4c __attribute__((ext_vector_type(4)));
 // NT: non-temporal accesses, for widths of whole cache lines; where two waves share a line it should
-// stay in the cache for the second (32 heads x 1000 columns: fp32 10.5 -> 9.4, bf16 9.9 -> 9.0 us; the
-// one-column form 9.0 and 17.1).
+// stay in the cache for the second (32 heads x 1000 columns: fp32 10.5 -> 9.4, bf16 9.9 -> 9.0 us).
+// Those two waves are workgroups on different dies, and each writes its part of the line to memory; the
+// one-column form shares a line once in 256 columns.  At such widths this one is taken by bf16, whose
+// one-column form takes 2.5 times as long as fp16's, and by the others up to a wave a CU, where its fewer
+// instructions count (matrices in turn, one-column / this, us: 1024 x 1000 fp16 8.0 / 7.1, fp32 8.8 /
+// 7.0; 2048 x 1000 8.8 / 8.6, 9.8 / 8.9; 4096 x 1000 10.4 / 11.9, 11.6 / 12.8; 4096 x 3300 21.3 / 28.4,
+// 30.7 / 32.9; bf16 23.3 / 7.2, 24.1 / 8.6, 25.5 / 11.9, 36.9 / 27.7).
 template <typename IO> struct Col4;
 template <bool NT, typename T> __device__ __forceinline__ T col_load(const T* p) {
   return NT ? __builtin_nontemporal_load(p) : *p;
@@ -332,10 +337,11 @@ void launch_rotate_columns(const void* w, float* out, long long n_rows, long lon
   const bool aligned = n_cols % 4 == 0 && reinterpret_cast<uintptr_t>(w) % (4 * sizeof(IO)) == 0 &&
                        reinterpret_cast<uintptr_t>(out) % 16 == 0;
   const long long waves = (n_cols + 63) / 64;
+  const bool shared_lines_pay = std::is_same<IO, __hip_bfloat16>::value || waves * blocks <= oscar_compute_units();
   if (aligned && waves <= 0x7FFFFFFF && n_cols % 64 == 0)
     hipLaunchKernelGGL((oscar_rotate_columns4_kernel<IO, true>), dim3((unsigned)waves, blocks), dim3(64), 0, st,
                        wp, out, n_cols);
-  else if (aligned && waves <= 0x7FFFFFFF)
+  else if (aligned && waves <= 0x7FFFFFFF && shared_lines_pay)
     hipLaunchKernelGGL((oscar_rotate_columns4_kernel<IO, false>), dim3((unsigned)waves, blocks), dim3(64), 0, st,
                        wp, out, n_cols);
   else

@@ -32,3 +32,15 @@ def test_widths_and_alignments(cols, offset, io):
     got = ob.rotate_columns(dev).cpu().numpy()
     want = _reference(store[offset:].view(rows, cols).float().numpy())
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("io", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("blocks,cols", [(32, 500), (32, 516), (33, 500), (32, 512), (4, 4100), (3, 4100)])
+def test_both_sides_of_a_wave_a_cu(blocks, cols, io):
+    """Widths that are not whole cache lines change kernels where the grid passes a wave a CU (256)."""
+    import torch
+    from paper_2605_19660_amd import binding as ob
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[io]
+    host = torch.from_numpy(np.random.default_rng(cols).standard_normal((128 * blocks, cols)).astype(np.float32)).to(dt)
+    got = ob.rotate_columns(host.cuda()).cpu().numpy()
+    assert np.array_equal(got, _reference(host.float().numpy()))

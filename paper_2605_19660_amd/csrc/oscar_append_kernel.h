@@ -1068,8 +1068,11 @@ template <typename IO, typename META, int BITS, int XF>
 int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
   // (the ablation switches keep the one form)
   if constexpr (XF != XF_SWITCHED) {
-    // (a one-token append moves a page once in 128 calls; the rest of the time it is one token row)
-    if (P.T > 1 && (size_t)grid.x * grid.y * grid.z <= small_grid_workgroups<IO>())
+    // An append of up to 16 tokens moves a page once in eight calls or fewer; the rest of the time it is
+    // the tail alone, one pass of the 16 token rows of the 256-thread form, whose half of the waves is then
+    // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads
+    // norm 6.5 / 7.7, 16 tokens 7.3 / 8.4; 17 tokens, a second pass, 5.1 / 4.6 and 9.8 / 9.1).
+    if (P.T > 16 && (size_t)grid.x * grid.y * grid.z <= small_grid_workgroups<IO>())
       return launch_np<IO, META, BITS, XF, 4>(P, grid, st);
   }
   return launch_np<IO, META, BITS, XF, 8>(P, grid, st);

@@ -46,3 +46,23 @@ def test_the_two_forms_meet_at_the_launch_size(context):
                        new_lens=torch.from_numpy(lens).cuda())
     o.append(k, v, eager=True, new_lens=lens)
     assert_cache_equal(g, o, w)
+
+
+@pytest.mark.parametrize("eager", [True, False])
+@pytest.mark.parametrize("norm_all", [False, True])
+@pytest.mark.parametrize("io,bits,kg", [("bf16", 2, 128), ("f32", 4, 32)])
+def test_pieces_at_the_choice_of_the_form_by_length(io, bits, kg, norm_all, eager):
+    """16 tokens and fewer take the 256-thread form, 17 and more the 512-thread one, into the same window."""
+    pieces = [16, 17, 15, 64, 17, 16, 2, 16, 110, 18, 16, 17]
+    total = sum(pieces)
+    w = synth.LLAMA8B_32K.replace(batch=2, n_q_heads=4, n_kv_heads=2, context=total, io_dtype=io, bits=bits, k_group=kg)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, total // 128 + 2, norm_scope=1 if norm_all else 0)
+    ob = _ob()
+    at = 0
+    for n in pieces:
+        kp, vp = np.ascontiguousarray(k[:, at:at + n]), np.ascontiguousarray(v[:, at:at + n])
+        ob.quantize_append(g, to_dev(kp, io), to_dev(vp, io), eager=eager, max_seq_len_hint=at)
+        o.append(kp, vp, eager=eager)
+        assert_cache_equal(g, o, w)
+        at += n

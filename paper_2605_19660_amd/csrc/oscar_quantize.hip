@@ -4,12 +4,16 @@
 
 namespace {
 
-// largest grid of a multi-block append whose length update rides on the encoder launch
-// (oscar_quantize_append): the tickets of workgroups that end together are drawn one after the
-// other, about 11 ns each, and the small second kernel takes 4.7 us (whole calls in us with the
-// ticket / the second kernel: 272 workgroups 9.5 / 12.9, 400 13.9 / 13.8, 528 16.1 / 14.9,
-// 784 24.6 / 22.6)
-constexpr size_t kTicketMaxWorkgroups = 448;
+// Largest grid of a multi-block append whose length update rides on the encoder launch
+// (oscar_quantize_append): what is resident at once in the 256-thread form.  The tickets of workgroups
+// that end together are drawn one after the other, about 11 ns each; the small second kernel takes 4.7 us,
+// of which the encoder's last workgroups hide a part.  Whole calls in us with the ticket / the second
+// kernel, bf16 INT2 and fp16 INT4 (G_k = 32), 8 heads: an empty cache's 16 x 512 tokens (640 workgroups)
+// 18.9 / 21.2 and 21.5 / 23.5, 1 x 10000 (632) 19.6 / 21.2 and 22.4 / 23.6, 1 x 14000 (880) 23.4 / 25.0 and
+// 26.9 / 27.9; pieces of 24 x 512 (960) 19.8 / 21.0 and 22.7 / 24.3, of 6 x 2000 (768) 23.5 / 23.6 and
+// 25.7 / 26.4, of 1 x 8192 (520) 15.6 / 15.1 and 18.1 / 17.9.  The other way round where half of the
+// workgroups are idle and draw theirs at once: pieces of 60 x 130 (960) 26.4 / 23.9 and 28.8 / 26.5.
+constexpr size_t kTicketMaxWorkgroups = 1024;
 
 // Stand-alone rotation kernel: 16 vectors of 128 channels per workgroup (one DPP row each).
 // NORMALIZE = false: out = H(x)/sqrt(128) in fp32 (queries).

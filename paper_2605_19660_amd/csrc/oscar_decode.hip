@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void oscar_decode_reduce64_kernel(const float*
     const float ws_k = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), wave + 4 * k));
     // the places past the last split hold it once more and are cleared: with the weight of 0 alone an
     // infinite partial became NaN
-    const uint32_t held = wave + 4 * k < num_splits ? ~0u : 0u;
+    const uint32_t held = k < 4 || wave + 4 * k < num_splits ? ~0u : 0u;   // (the first 16 always are)
     acc.x = fmaf(__uint_as_float(__float_as_uint(o[k].x) & held), ws_k, acc.x);
     acc.y = fmaf(__uint_as_float(__float_as_uint(o[k].y) & held), ws_k, acc.y);
   }

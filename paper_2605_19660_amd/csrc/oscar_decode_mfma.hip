@@ -767,9 +767,9 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   const int pstride = 4 * P.num_splits;
   const int pg_first = 4 * split + wave;
   const int32_t* table = P.c.block_table + (size_t)b * P.c.max_pages_per_seq;
-  // Block-table entries of this wave's pages live in a register, one per lane, 64
-  // iterations at a time: the page loop itself issues no dependent lookups.  Entries past
-  // the sequence's last page are never used for an access.
+  // Block-table entries of this wave's pages live in a register, one per lane, 63 iterations and the
+  // prefetch of the next one at a time: the page loop itself issues no dependent lookups.  Entries
+  // past the sequence's last page are never used for an access.
   auto load_table = [&](int it0) -> int {
     const int idx = pg_first + pstride * (it0 + lane);
     return idx < P.c.max_pages_per_seq ? table[idx] : 0;
@@ -1110,15 +1110,18 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   const int prio_step = max(1, (n_iter + 3) >> 2);
   int prio_next = prio_step, prio_level = 0;
 
-  // Iterations come in chunks of 64 so that the table register is only reloaded between
-  // chunks; tabn (lane 0) is the first entry of the following chunk.
-  for (int it0 = 0; pg_first + pstride * it0 < n_pages; it0 += 64) {
-  if (it0 > 0) tab = load_table(it0);
-  const int tabn = load_table(it0 + 64);
-  const int it_end = min(64, (n_pages - pg_first - pstride * it0 + pstride - 1) / pstride);
-  // touch both registers here, so the wait for these two loads sits outside the page loop
-  // (inside it, it would also wait for every prefetch in flight)
-  asm volatile("" ::"v"(tab), "v"(tabn));
+  // Iterations come in chunks of 63: an iteration asks for the page of the next one, and the 64th entry
+  // of the register is the first of the following chunk.  (A second register for that entry, loaded
+  // behind the first page's loads and waited for in front of the loop, held the first logits back until
+  // the whole page was there, value side included.)
+  for (int it0 = 0; pg_first + pstride * it0 < n_pages; it0 += 63) {
+  if (it0 > 0) {
+    tab = load_table(it0);
+    // touch the register here, so the wait for this load sits outside the page loop (inside it, it would
+    // also wait for every prefetch in flight)
+    asm volatile("" ::"v"(tab));
+  }
+  const int it_end = min(63, (n_pages - pg_first - pstride * it0 + pstride - 1) / pstride);
   for (int iti = 0; iti < it_end; ++iti) {
     const int pg = pg_first + pstride * (it0 + iti);
     OSCAR_STAMP(8 + min(it0 + iti, 15));   // top of page iteration 0..15
@@ -1131,8 +1134,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     }
     const bool has_next = pg + pstride < n_pages;
     // entries past the wave's last page read as 0 (a valid page index) and the load is void
-    const int phys = iti < 63 ? __builtin_amdgcn_readlane(tab, iti + 1)
-                              : __builtin_amdgcn_readlane(tabn, 0);
+    const int phys = __builtin_amdgcn_readlane(tab, iti + 1);
     PageRsrc nx;   // the wave's next page
     nx.make(pools, P, (uint32_t)phys, has_next);
 

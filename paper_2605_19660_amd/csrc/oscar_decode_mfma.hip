@@ -23,9 +23,10 @@
 //    with OSCAR_LIMBS_PACKED = 0).
 //  * Zero-points are subtracted analytically in fp32 (the two right-hand sums above).
 //
-// Work decomposition: grid (split, kv head, sequence); 4 waves per workgroup, every wave
+// Work decomposition: grid (split, kv head, sequence); 4 waves per workgroup (8 in launches that leave
+// compute units to spare, see eight_waves_built), every wave
 // owns whole pages (no barriers in the page loop) and keeps its own online-softmax state;
-// the 4 wave states and the workgroup's slice of the 16-bit residual tokens (plain ALU code,
+// the wave states and the workgroup's slice of the 16-bit residual tokens (plain ALU code,
 // the window is dealt to the splits in multiples of 16 tokens) are merged through LDS at
 // the end.
 // Tile roles: q K^T uses M = query-head limb rows, N = 16 tokens, K = 128 channels;
@@ -84,7 +85,7 @@ __device__ unsigned long long g_stamps[8][4][32];
 }
 #define OSCAR_STAMP(i)                                                                  \
   do {                                                                                  \
-    if (stamp_on && lane == 0) g_stamps[stamp_slot & 7][wave & 3][(i) & 31] = wall_clock64(); \
+    if (stamp_on && wave < 4 && lane == 0) g_stamps[stamp_slot & 7][wave & 3][(i) & 31] = wall_clock64(); \
   } while (0)
 #else
 #define OSCAR_STAMP(i)
@@ -631,6 +632,21 @@ __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, in
   return hp == 1 ? ngk == 4 && ngv < 4 : ngk <= 2 && ngv == 1;
 }
 
+// Workgroups of eight waves, for launches of at most one workgroup a CU: with four, the other half of the
+// SIMDs' two wave slots stays empty while a wave, held to an instruction every five clocks, walks its two
+// pages and its share of the residual window.  Device time of a step over caches that are not in the
+// last-level cache, four / eight waves, us: INT2, G_k = 128, G_v = 32, 8 kv heads, batch 1 x 1000 17.6 / 14.1,
+// 1 x 4000 12.5 / 11.3, 1 x 32000 13.2 / 12.7, 16 x 1000 19.7 / 15.7; seven query heads a kv head, 1 x 1000
+// 23.0 / 18.3, 1 x 16000 16.1 / 14.8; fp32 metadata 1 x 1000 20.9 / 17.4; INT4 1 x 1000 19.1 / 16.5.  At INT4 it
+// is one split only (the window is what gains: with several splits, warm, 1 x 8000 12.8 / 13.6, 1 x 16000
+// 14.7 / 17.5), with fp32 metadata not at all.
+// Built where two workgroups of four fit a CU in both kernels (the step's and the attention alone
+// give the same bits, so they split alike).
+__host__ __device__ constexpr bool eight_waves_built(int bits, int hp, int ngk, int ngv, bool m32) {
+  return oscar_decode_mfma_wgs_per_cu(bits, hp, ngk, ngv, m32) == 2 &&
+         (m32 ? bits == 2 : !step_one_per_cu(bits, hp, ngk, ngv));
+}
+
 #if OSCAR_MFMA_STEP
 // values of the residual window as the encoder's block quantizer takes them
 struct WindowValues {
@@ -655,21 +671,21 @@ __device__ __forceinline__ void store_new_token(const DecodeParams& P, size_t at
 
 // The full window of (b, kvh) into page `page` of the sequence, then the new token into slot 0: what
 // oscar_append_kernel does for this call, by one workgroup.
-template <int BITS, int KG>
-__device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& lds, const DecodeParams& P, int b, int kvh,
+template <int BITS, int KG, int NP>
+__device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, NP>& lds, const DecodeParams& P, int b, int kvh,
                                              int page, int tid, int cg) {
-  const int Hkv = P.c.cfg.n_kv_heads, slot = tid >> 4;
+  const int Hkv = P.c.cfg.n_kv_heads, slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15, grp = NP == 8 ? 0 : tid >> 8;
   const size_t rb = ((size_t)b * Hkv + kvh) * R;
   const int phys = P.c.block_table[(size_t)b * P.c.max_pages_per_seq + page];
   const __half* res_norm = reinterpret_cast<const __half*>(P.c.res_norm) + rb;
   ResRsrc<false> win;
   win.make(P, rb, true);
-  uint4 ku[8];
-  WindowValues vw[8];
-  float nrm[8];
+  uint4 ku[NP];
+  WindowValues vw[NP];
+  float nrm[NP];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const int t = 16 * p + slot;
+  for (int p = 0; p < NP; ++p) {
+    const int t = 16 * (NP == 8 ? p : 2 * p + grp) + slot;
     ku[p] = buf_load16(win.k, (t * D + 8 * cg) * 2);
     vw[p].raw.load(win.v, t * D + 8 * cg);
     vw[p].dt = P.c.cfg.io_dtype;
@@ -690,9 +706,9 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& ld
   // every read of the old window has returned before slot 0 is written
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (slot == 0) store_new_token(P, rb, k, vraw, half_bits(nf), cg);
-  const float nrm_q[2] = {0.0f, 0.0f};
-  quantize_block<__half, BITS, KG, 8>(lds, ku, vw, false, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
+  if (slot == 0 && grp == 0) store_new_token(P, rb, k, vraw, half_bits(nf), cg);
+  const float nrm_q[NP / 4] = {};
+  quantize_block<__half, BITS, KG, NP>(lds, ku, vw, false, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
                                       OSCAR_MFMA_ZPMIN != 0, tid, cg);
 }
 #endif
@@ -709,9 +725,9 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, 8>& ld
 //  * The lengths are advanced by the reduce pass.  With a single split there is none: every workgroup
 //    draws the cache's ticket as soon as it has the lengths, so that whoever draws the last one knows
 //    that all have read them, and advances them at its end.
-template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32, bool STEP>
-__global__ __launch_bounds__(256, STEP && step_one_per_cu(BITS, HP, NGK, NGV)
-                                  ? 1 : oscar_decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
+template <int BITS, int HP, int NGK, int NGV, bool ZPMIN, bool M32, bool STEP, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : STEP && step_one_per_cu(BITS, HP, NGK, NGV)
+                                      ? 1 : oscar_decode_mfma_wgs_per_cu(BITS, HP, NGK, NGV, M32))
 void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   constexpr int TPG = 8 / NGK;  // token tiles per key group
   constexpr int CPG = 8 / NGV;  // channel tiles per value group
@@ -723,25 +739,25 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // rows padded by 16 bytes: the 16-byte operand reads of lanes n = 0..7 hit 8 different banks
 #if OSCAR_MFMA_STEP
   struct Tables {
-    alignas(16) _Float16 A[4][16][TABW], P[4][16][TABW];
-    alignas(16) float o[4][OSCAR_MAX_GQA][D];
+    alignas(16) _Float16 A[NW][16][TABW], P[NW][16][TABW];
+    alignas(16) float o[NW][OSCAR_MAX_GQA][D];
   };
   __shared__ union {   // (the flush is over before the tables are touched)
     Tables t;
-    EncoderLds<__half, BITS, R / NGK, 8> enc;
+    EncoderLds<__half, BITS, R / NGK, NW == 8 ? 4 : 8> enc;
   } s_u;
   auto& s_A = s_u.t.A;
   auto& s_P = s_u.t.P;
   auto& s_o = s_u.t.o;
 #else
-  __shared__ __align__(16) _Float16 s_A[4][16][TABW];   // per wave: (Q_h Delta_k) hi/lo rows
-  __shared__ __align__(16) _Float16 s_P[4][16][TABW];   // per wave: (p Delta_v) hi/lo rows
-  __shared__ __align__(16) float s_o[4][OSCAR_MAX_GQA][D];  // wave results for the merge
+  __shared__ __align__(16) _Float16 s_A[NW][16][TABW];   // per wave: (Q_h Delta_k) hi/lo rows
+  __shared__ __align__(16) _Float16 s_P[NW][16][TABW];   // per wave: (p Delta_v) hi/lo rows
+  __shared__ __align__(16) float s_o[NW][OSCAR_MAX_GQA][D];  // wave results for the merge
 #endif
-  __shared__ float s_wm[4][OSCAR_MAX_GQA], s_wl[4][OSCAR_MAX_GQA];
+  __shared__ float s_wm[NW][OSCAR_MAX_GQA], s_wl[NW][OSCAR_MAX_GQA];
   // two head slots: the rotated queries in operand order wait in LDS between pages instead of
   // registers (16 registers that the second slot's softmax state needs)
-  __shared__ __align__(16) float4 s_qr[HP == 2 ? 4 : 1][HP == 2 ? 2 : 1][2][HP == 2 ? 64 : 1];
+  __shared__ __align__(16) float4 s_qr[HP == 2 ? NW : 1][HP == 2 ? 2 : 1][2][HP == 2 ? 64 : 1];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -761,11 +777,13 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   const int Hkv = P.c.cfg.n_kv_heads, Hq = P.c.cfg.n_q_heads;
   constexpr bool zp_min = ZPMIN;
 
-  // Pages are dealt round-robin: wave w of split s owns pages 4*s + w + 4*S*k.  The page
-  // numbers (and so the block-table addresses) do not depend on the sequence length, which
-  // lets the length, table, query and residual loads all start together.
-  const int pstride = 4 * P.num_splits;
-  const int pg_first = 4 * split + wave;
+  // Pages are dealt round-robin: wave w of split s owns pages 4*s + w + 4*S*k, in the eight-wave form
+  // s + S*w + 8*S*k.  The page numbers (and so the block-table addresses) do not depend on the sequence
+  // length, which lets the length, table, query and residual loads all start together.  (Eight waves
+  // share four SIMDs: a last round of a few pages must not fall on waves of one workgroup.  Batch 1 x 16K,
+  // 125 pages on 120 waves, whole step: 13.1 us with four waves, 13.4 with eight dealt like them, 12.3 so.)
+  const int pstride = NW * P.num_splits;
+  const int pg_first = NW == 8 ? split + P.num_splits * wave : 4 * split + wave;
   const int32_t* table = P.c.block_table + (size_t)b * P.c.max_pages_per_seq;
   // Block-table entries of this wave's pages live in a register, one per lane, 63 iterations and the
   // prefetch of the next one at a time: the page loop itself issues no dependent lookups.  Entries
@@ -798,7 +816,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     step_ok = plan.ok;
     step_flush = plan.ok && plan.flush;
     if (!plan.ok && tid == 0 && split == 0 && kvh == 0 && P.c.dev_status) *P.c.dev_status = OSCAR_ERR_CAPACITY;
-    if (step_flush && split == (plan.packed >> 2) % P.num_splits) {
+    if (step_flush && split == (NW == 8 ? plan.packed : plan.packed >> 2) % P.num_splits) {
       flush_window(s_u.enc, P, b, kvh, plan.packed, tid, cg);
       // the page's stores have reached memory before any wave of this workgroup reads it
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -862,7 +880,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   kr.load(first, lane);
   __builtin_amdgcn_sched_barrier(0);
 #if OSCAR_MFMA_STEP
-  // All four waves have the lengths in registers (the loads above have waited for them) before the
+  // All waves have the lengths in registers (the loads above have waited for them) before the
   // workgroup draws its ticket; the answer is needed at the very end only, by when it has long come.
   // Drawn at the end, the tickets of a launch whose workgroups finish together queue up, 11 ns each.
   if (P.num_splits == 1) {
@@ -933,7 +951,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
       knew.widen(x, P.c.cfg.io_dtype);
       tok_new.k = key_transform8<__half>(x, sgn, nf);
       tok_new.nrm = half_bits(nf);
-      if (!step_flush && q4 == 0 && wave == (((r - 1 - t_lo) & 15) >> 2))
+      if (!step_flush && q4 == 0 && wave == (((r - 1 - t_lo) & (4 * NW - 1)) >> 2))
         store_new_token(P, ((size_t)b * Hkv + kvh) * R + r - 1, tok_new.k, tok_new.v, tok_new.nrm, cg);
     }
 #endif
@@ -989,20 +1007,20 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     // alone, 127 residual tokens 73.4 -> 68.4 us against 60.3 with none; batch 1 x 1K, 104 residual
     // tokens 14.7 -> 13.9.  A third set does not fit the registers of any variant.)
     ResTok<M32> rt_other[4];
-    for (int p0 = 0;; p0 += 32) {
-      const bool second = p0 + 16 + 4 * wave < rcount;
+    for (int p0 = 0;; p0 += 8 * NW) {
+      const bool second = p0 + 4 * NW + 4 * wave < rcount;
       if (second) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rt_other[i].load(rres, res_slot(p0 + 16, i), cg);
+        for (int i = 0; i < 4; ++i) rt_other[i].load(rres, res_slot(p0 + 4 * NW, i), cg);
       }
       pass(rt_first, p0);
       if (!second) break;
-      const bool third = p0 + 32 + 4 * wave < rcount;
+      const bool third = p0 + 8 * NW + 4 * wave < rcount;
       if (third) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rt_first[i].load(rres, res_slot(p0 + 32, i), cg);
+        for (int i = 0; i < 4; ++i) rt_first[i].load(rres, res_slot(p0 + 8 * NW, i), cg);
       }
-      pass(rt_other, p0 + 16);
+      pass(rt_other, p0 + 4 * NW);
       if (!third) break;
     }
     // hand the result over in accumulator layout through the wave's own slice of s_o
@@ -1537,10 +1555,10 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     }
   }
 
-  // ---- merge the 4 wave states and the residual state, write the split's record ----
+  // ---- merge the wave states and the residual state, write the split's record ----
   OSCAR_STAMP(25);   // wave results in LDS
   __syncthreads();
-  OSCAR_STAMP(26);   // all four waves there
+  OSCAR_STAMP(26);   // all waves there
   // a thread owns one channel of every second head (the head parity is wave-uniform, so no
   // lane idles); the reads of a head are independent and go out together
   const int ch = tid & (D - 1), hh = __builtin_amdgcn_readfirstlane(tid >> 7);
@@ -1549,20 +1567,22 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // reduce pass divides them, so both routes give the same bits.
   const bool direct = P.out != nullptr;
 #pragma unroll
-  for (int k = 0; k < OSCAR_MAX_GQA / 2; ++k) {
-    const int h = hh + 2 * k;
+  for (int k = 0; k < OSCAR_MAX_GQA / (NW / 2); ++k) {
+    const int h = hh + NW / 2 * k;
     if (h < gq) {
-      float m[4], o[4];
+      float m[NW], o[NW];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NW; ++w) {
         m[w] = s_wm[w][h];
         o[w] = s_o[w][h][ch];
       }
-      const float M = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+      float M = m[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) M = fmaxf(M, m[w]);
       float acc = 0.0f;
       if (M != -INFINITY) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
+        for (int w = 0; w < NW; ++w)
           if (m[w] != -INFINITY) acc += o[w] * __builtin_amdgcn_exp2f(m[w] - M);
       }
       const size_t unit = (size_t)b * Hq + (size_t)kvh * gq + h;
@@ -1570,7 +1590,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         float L = 0.0f;
         if (M != -INFINITY) {
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
+          for (int w = 0; w < NW; ++w)
             if (m[w] != -INFINITY) L += s_wl[w][h] * __builtin_amdgcn_exp2f(m[w] - M);
         }
         const float res = L > 0.0f ? acc / L : 0.0f;
@@ -1587,11 +1607,11 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     const int h = tid;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_wm[w][h]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_wm[w][h]);
     float L = 0.0f;
     if (M != -INFINITY) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
+      for (int w = 0; w < NW; ++w)
         if (s_wm[w][h] != -INFINITY) L += s_wl[w][h] * __builtin_amdgcn_exp2f(s_wm[w][h] - M);
     }
     const size_t rec = ((size_t)b * Hq + (size_t)kvh * gq + h) * P.num_splits + split;
@@ -1616,16 +1636,29 @@ int launch_groups(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, hipE
                   hipEvent_t e1) {
   const int ngk = P.g.ngk, ngv = P.g.ngv;
   constexpr bool ZPM = OSCAR_MFMA_ZPMIN != 0, M32 = OSCAR_MFMA_META32 != 0, STEP = OSCAR_MFMA_STEP != 0;
+  // (see eight_waves_built)
+  const bool few = (BITS == 2 || P.num_splits == 1) &&
+                   (unsigned long long)grid.x * grid.y * grid.z <= (unsigned long long)oscar_compute_units();
   // the event-carrying launch only when a timer asked for it: the plain launch is what a
   // stream capture records
+#define OSCAR_MFMA_LAUNCH(NK, NV, NW)                                                      \
+  do {                                                                                     \
+    if (e0 || e1)                                                                          \
+      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP, NW>), grid,   \
+                            dim3(64 * NW), 0, st, e0, e1, 0, P, gq);                       \
+    else                                                                                   \
+      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP, NW>), grid,      \
+                         dim3(64 * NW), 0, st, P, gq);                                     \
+  } while (0)
 #define OSCAR_MFMA_CASE(NK, NV)                                                            \
   if (ngk == NK && ngv == NV) {                                                            \
-    if (e0 || e1)                                                                          \
-      hipExtLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP>), grid,       \
-                            dim3(256), 0, st, e0, e1, 0, P, gq);                           \
-    else                                                                                   \
-      hipLaunchKernelGGL((oscar_decode_mfma_kernel<BITS, HP, NK, NV, ZPM, M32, STEP>), grid,          \
-                         dim3(256), 0, st, P, gq);                                         \
+    if constexpr (eight_waves_built(BITS, HP, NK, NV, M32)) {                              \
+      if (few) {                                                                           \
+        OSCAR_MFMA_LAUNCH(NK, NV, 8);                                                      \
+        return OSCAR_OK;                                                                   \
+      }                                                                                    \
+    }                                                                                      \
+    OSCAR_MFMA_LAUNCH(NK, NV, 4);                                                          \
     return OSCAR_OK;                                                                       \
   }
   OSCAR_MFMA_CASE(1, 4)
@@ -1638,6 +1671,7 @@ int launch_groups(const DecodeParams& P, int gq, dim3 grid, hipStream_t st, hipE
   OSCAR_MFMA_CASE(4, 1)
   OSCAR_MFMA_CASE(4, 2)
 #undef OSCAR_MFMA_CASE
+#undef OSCAR_MFMA_LAUNCH
   return OSCAR_ERR_UNSUPPORTED;
 }
 

@@ -143,6 +143,19 @@ template <> __device__ __forceinline__ float round_meta<__half>(float x) {
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
+// One draw from a cache's ticket counter by thread 0 of the workgroup (tid: the thread's number; every
+// thread calls it, the others' access lies outside the resource).  Without a branch around it: at the
+// end of one the compiler waits for the answer, and for every load asked for before it.
+// ticket_answer() is where the answer is waited for.
+__device__ __forceinline__ int draw_ticket(int32_t* counter, bool on, int tid) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(counter, 0, on ? 4 : 0, 0x00020000);
+  return __builtin_amdgcn_raw_ptr_buffer_atomic_add_i32(1, r, 4 * tid, 0, 0);
+}
+__device__ __forceinline__ int ticket_answer(int ticket) {   // thread 0's, in its wave
+  asm volatile("" : "+v"(ticket));
+  return __builtin_amdgcn_readfirstlane(ticket);
+}
+
 // Host-side validation shared by the entry points.
 int oscar_validate_config(const oscar_config* cfg);
 // Compute units of the current device (asked for once a device).

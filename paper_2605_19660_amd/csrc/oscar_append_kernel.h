@@ -37,10 +37,6 @@
 
 #include "oscar_rowops.h"
 
-#ifndef OSCAR_ENC_EARLY_K
-#define OSCAR_ENC_EARLY_K 1
-#endif
-
 struct AppendParams {
   const void* k;
   const void* v;
@@ -390,6 +386,16 @@ __device__ __forceinline__ uint32_t pk_max_f16(uint32_t a, uint32_t b) {
   asm volatile("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+// op over the four 16-lane rows of a wave, four words at once: row j of the result holds word j.  The
+// registers of two words trade rows (16, then 32 lanes apart), so that every lane has work: three swaps
+// and three operations, where each word for itself took eight shuffles through LDS and eight operations
+// (prefill of 131072 tokens INT2 122.5 -> 120.8 us, 8 x 4K INT4 with four key groups a page 43.1 -> 41.9).
+template <typename OP> __device__ __forceinline__ uint32_t rows_reduce(const uint32_t (&w)[4], OP op) {
+  const auto a = __builtin_amdgcn_permlane16_swap(w[0], w[1], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(w[2], w[3], false, false);
+  const auto c = __builtin_amdgcn_permlane32_swap(op(a[0], a[1]), op(b[0], b[1]), false, false);
+  return op(c[0], c[1]);
+}
 __device__ __forceinline__ float half_of(uint32_t w, int hi) {
   return __half2float(__ushort_as_half((unsigned short)(hi ? (w >> 16) : (w & 0xffffu))));
 }
@@ -497,14 +503,14 @@ template <typename META, int BITS, int KG, int NP> struct EncoderLds {
   alignas(16) META norm[R];
 };
 
-// Phases 3 and 4 of the encoder: the block of 128 tokens held in registers (keys as packed fp16 K_u,
-// values raw; register i of a thread is token 16 * pass(i) + slot) goes into page `pg` of the pools
-// (physical page * kv heads + kv head).  The whole workgroup of 2048 / NP threads takes part.
-template <typename META, int BITS, int KG, int NP, typename VRAW>
-__device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s, const uint4 (&ku)[NP],
-                                               const VRAW (&vraw)[NP], bool batched_norms, const float (&nrm)[NP],
-                                               const float (&nrm_q)[NP / 4], const oscar_cache& c, const PageGeom& g,
-                                               size_t pg, bool zp_min, int tid, int cg) {
+// The key side of a page: the block of 128 tokens held in registers as packed fp16 K_u (register i of a
+// thread is token 16 * pass(i) + slot) becomes codes, step sizes, zero-points and norms of page `pg` of
+// the pools (physical page * kv heads + kv head).  The whole workgroup of 2048 / NP threads takes part.
+template <typename META, int BITS, int KG, int NP>
+__device__ __forceinline__ void quantize_keys(EncoderLds<META, BITS, KG, NP>& s, const uint4 (&ku)[NP],
+                                              bool batched_norms, const float (&nrm)[NP],
+                                              const float (&nrm_q)[NP / 4], const oscar_cache& c, const PageGeom& g,
+                                              size_t pg, bool zp_min, int tid, int cg) {
   constexpr int NGK = R / KG;             // key groups per page
   constexpr int RPG = KG / 16 * NP / 8;   // registers (a thread's tokens) per key group
   constexpr int NT = 2048 / NP, NW = NT / 64;
@@ -517,8 +523,6 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
   uint8_t* o_kcodes = reinterpret_cast<uint8_t*>(c.k_codes) + pg * g.k_codes_bytes;
   META* o_kmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.k_meta) + pg * g.k_meta_bytes);
   META* o_knorm = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.k_norms) + pg * g.k_norms_bytes);
-  uint8_t* o_vcodes = reinterpret_cast<uint8_t*>(c.v_codes) + pg * g.v_codes_bytes;
-  META* o_vmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.v_meta) + pg * g.v_meta_bytes);
 
   // keys: per-channel min/max over the tokens of each group: passes, then the 4 token rows
   // of the wave, then (through LDS) the 4 waves
@@ -536,17 +540,10 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
         mx[j] = pk_max_f16(mx[j], w[j]);
       }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 16, 64));
-      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 16, 64));
-      mn[j] = pk_min_f16(mn[j], (uint32_t)__shfl_xor((int)mn[j], 32, 64));
-      mx[j] = pk_max_f16(mx[j], (uint32_t)__shfl_xor((int)mx[j], 32, 64));
-    }
-    if (lane < 16) {
-      s.red[gk][wave][cg].mn = make_uint4(mn[0], mn[1], mn[2], mn[3]);
-      s.red[gk][wave][cg].mx = make_uint4(mx[0], mx[1], mx[2], mx[3]);
-    }
+    // over the wave's four token rows: row j ends with word j
+    const uint32_t rmn = rows_reduce(mn, pk_min_f16), rmx = rows_reduce(mx, pk_max_f16);
+    reinterpret_cast<uint32_t*>(&s.red[gk][wave][cg].mn)[lane >> 4] = rmn;
+    reinterpret_cast<uint32_t*>(&s.red[gk][wave][cg].mx)[lane >> 4] = rmx;
   }
   if (batched_norms) {
     if ((tid & 15) < 4) {   // first quad of the token row: lane j holds the norms of registers j, 4 + j
@@ -624,7 +621,6 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
     }
   }
 
-#if OSCAR_ENC_EARLY_K
   // the key-code image is complete: it leaves now, under the value phase, instead of with
   // everything else at the end of the workgroup (one more barrier)
   __syncthreads();
@@ -635,7 +631,23 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
 #pragma unroll
     for (int i = tid; i < NV; i += NT) kdst[i] = ksrc[i];
   }
-#endif
+  if (tid < R * (int)sizeof(META) / 16)
+    reinterpret_cast<uint4*>(o_knorm)[tid] = reinterpret_cast<const uint4*>(&s.norm[0])[tid];
+}
+
+// The value side of a page: the block's values as they came, same registers, same workgroup.
+template <typename META, int BITS, int KG, int NP, typename VRAW>
+__device__ __forceinline__ void quantize_values(EncoderLds<META, BITS, KG, NP>& s, const VRAW (&vraw)[NP],
+                                                const oscar_cache& c, const PageGeom& g, size_t pg, bool zp_min,
+                                                int tid, int cg) {
+  constexpr int NT = 2048 / NP;
+  constexpr float QMAX = (float)((1 << BITS) - 1);
+  constexpr int IMG = R * D * BITS / 8;
+  const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;
+  const int grp = NP == 8 ? 0 : tid >> 8;
+  auto pass = [&](int i) { return NP == 8 ? i : 2 * i + grp; };
+  uint8_t* o_vcodes = reinterpret_cast<uint8_t*>(c.v_codes) + pg * g.v_codes_bytes;
+  META* o_vmeta = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.v_meta) + pg * g.v_meta_bytes);
 
   // values: per-token min/max over each group of v_group channels (8 registers, then the
   // 4 | 8 | 16 lanes of the group).  The thread's 8 tokens of one channel are the elements
@@ -738,20 +750,12 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
   }
   __syncthreads();
 
-  // ---- phase 4: coalesced page stores ----
   {
     constexpr int NV = IMG / 16;  // uint4 count: 256 (2-bit) or 512 (4-bit)
-    const uint4* ksrc = reinterpret_cast<const uint4*>(&s.kimg[0]);
     const uint4* vsrc = reinterpret_cast<const uint4*>(&s.vimg[0]);
-    uint4* kdst = reinterpret_cast<uint4*>(o_kcodes);
     uint4* vdst = reinterpret_cast<uint4*>(o_vcodes);
 #pragma unroll
-    for (int i = tid; i < NV; i += NT) {
-#if !OSCAR_ENC_EARLY_K
-      kdst[i] = ksrc[i];
-#endif
-      vdst[i] = vsrc[i + (i / (NV / 8)) * 4];   // un-pad: 4 x 16 bytes per eighth
-    }
+    for (int i = tid; i < NV; i += NT) vdst[i] = vsrc[i + (i / (NV / 8)) * 4];   // un-pad: 4 x 16 bytes per eighth
   }
   {
     // value metadata image: Delta[ngv][R] then zero[ngv][R], 16 bytes per thread (each plane of
@@ -762,8 +766,6 @@ __device__ __forceinline__ void quantize_block(EncoderLds<META, BITS, KG, NP>& s
       reinterpret_cast<uint4*>(o_vmeta)[plane * per16 + idx] =
           reinterpret_cast<const uint4*>(&s.vmeta[plane][0][0])[idx];
     }
-    if (tid < R * (int)sizeof(META) / 16)
-      reinterpret_cast<uint4*>(o_knorm)[tid] = reinterpret_cast<const uint4*>(&s.norm[0])[tid];
   }
 }
 
@@ -1005,8 +1007,9 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   }
   if (!do_block) break;
 
-  quantize_block<META, BITS, KG, NP>(s, ku, vraw, batched_norms, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
-                                     zp_min, tid, cg);
+  const size_t pg = (size_t)phys * Hkv + kvh;
+  quantize_keys<META, BITS, KG, NP>(s, ku, batched_norms, nrm, nrm_q, P.c, P.g, pg, zp_min, tid, cg);
+  quantize_values<META, BITS, KG, NP>(s, vraw, P.c, P.g, pg, zp_min, tid, cg);
   } while (false);
 
   // ---- length update, folded in: the last workgroup to finish advances the lengths of all

@@ -708,8 +708,9 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, NP>& l
   __syncthreads();
   if (slot == 0 && grp == 0) store_new_token(P, rb, k, vraw, half_bits(nf), cg);
   const float nrm_q[NP / 4] = {};
-  quantize_block<__half, BITS, KG, NP>(lds, ku, vw, false, nrm, nrm_q, P.c, P.g, (size_t)phys * Hkv + kvh,
-                                      OSCAR_MFMA_ZPMIN != 0, tid, cg);
+  const size_t pg = (size_t)phys * Hkv + kvh;
+  quantize_keys<__half, BITS, KG, NP>(lds, ku, false, nrm, nrm_q, P.c, P.g, pg, OSCAR_MFMA_ZPMIN != 0, tid, cg);
+  quantize_values<__half, BITS, KG, NP>(lds, vw, P.c, P.g, pg, OSCAR_MFMA_ZPMIN != 0, tid, cg);
 }
 #endif
 

@@ -774,14 +774,16 @@ __device__ __forceinline__ void quantize_values(EncoderLds<META, BITS, KG, NP>& 
 // launch_kg): there a workgroup's own latency is the time, and it is issue-bound at one wave a SIMD.
 // A thread of the 512 takes every second pass: thread group 0 the even ones, group 1 the odd ones,
 // which are the two halves of a packed value piece.
-template <typename IO, typename META, int BITS, int KG, int XF, int NP>
+// SPLIT: two workgroups a block, one for the keys and one for the values (they touch different arrays).
+template <typename IO, typename META, int BITS, int KG, int XF, int NP, bool SPLIT>
 __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF == 2 ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
   constexpr bool NORM_ALL = XF == XF_ALL_HEADS;
   constexpr int NT = 2048 / NP, ROWS = NT / 16;   // threads, token rows
   __shared__ EncoderLds<META, BITS, KG, NP> s;
 
   // kv head fastest: the workgroups that share a token block's rows in memory run together
-  const int b = blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
+  const int b = SPLIT ? blockIdx.z >> 1 : blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
+  const bool keys = !SPLIT || (blockIdx.z & 1) == 0, values = !SPLIT || (blockIdx.z & 1) != 0;
   const int tid = threadIdx.x;
   const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;  // token of a pass
   const int grp = NP == 8 ? 0 : tid >> 8;               // thread group
@@ -796,6 +798,24 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   for (int st = 0; st < 4; ++st) sgn[st] = ((cg >> st) & 1) ? 0x80000000u : 0u;
 
   const SeqPlan sp = plan_sequence(P, b);
+  int my_ticket = -1;
+  bool drawn = false, advanced = false;
+  // (small launches) the ticket is drawn in the middle of the workgroup's work and answered later in it
+  constexpr bool EARLY_TICKET = NP == 4;
+  auto advance_all = [&](int first, int threads) {
+    for (int bb = first; bb < P.c.batch; bb += threads) {
+      const SeqPlan q = plan_sequence(P, bb);
+      if (q.n > 0 && q.ok) {
+        P.c.seq_lens[bb] += q.n;
+        P.c.res_lens[bb] = q.tail_len;
+      }
+    }
+    if (first == 0) P.c.tickets[0] = 0;
+  };
+  const int total = (int)(gridDim.x * gridDim.y * gridDim.z);
+  auto advance_if_last = [&]() {
+    if (P.c.tickets && tid < 64 && ticket_answer(my_ticket) == total - 1) advance_all(tid, 64);
+  };
   do {  // one pass; "break" = this workgroup has nothing (more) to do
   if (sp.n <= 0) break;
   if (!sp.ok) {
@@ -840,8 +860,10 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     const IO* kp = knew + (tok0 * Hkv + kvh) * D + cg * 8;
     const IO* vp = vnew + (tok0 * Hkv + kvh) * D + cg * 8;
     const size_t pstride = (size_t)(16 * (8 / NP)) * Hkv * D;
+    if (keys) {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) kraw[p].load(kp + p * pstride);
+      for (int p = 0; p < NP; ++p) kraw[p].load(kp + p * pstride);
+    }
     // The values are not needed before the key codes are done: their loads go out behind the
     // first half of the key transform (held there by the fences), which keeps their 32
     // registers free while the transform is at its widest and spreads the workgroup's requests.
@@ -852,8 +874,9 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       for (int p = 0; p < NP; ++p) vraw[p].load(vp + p * pstride);
       __builtin_amdgcn_sched_barrier(0);
     };
-    if (NP == 4) load_values();
-    if (NORM_ALL) {
+    if (NP == 4 && values) load_values();
+    if (!keys) {
+    } else if (NORM_ALL) {
 #pragma unroll
       for (int p = 0; p < NP; ++p) nrm[p] = to_f32<META>(pre_norm[tok_meta_pos(pass(p) * 16 + slot)]);
 #pragma unroll
@@ -890,20 +913,23 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     for (int p = 0; p < NP; ++p) {
       const int pi = blk * R + pass(p) * 16 + slot;  // index among pending tokens
       if (pi < sp.r0) {
-        kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
-        nrm[p] = to_f32<META>(res_norm[pi]);
-        vraw[p].load(res_v + (size_t)pi * D + cg * 8);
+        if (keys) {
+          kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
+          nrm[p] = to_f32<META>(res_norm[pi]);
+        }
+        if (values) vraw[p].load(res_v + (size_t)pi * D + cg * 8);
       } else {
         const size_t ti = (size_t)(pi - sp.r0);
         const size_t off = (((size_t)b * P.T + ti) * Hkv + kvh) * D + cg * 8;
-        kraw[p].load(knew + off);
-        vraw[p].load(vnew + off);
+        if (keys) kraw[p].load(knew + off);
+        if (values) vraw[p].load(vnew + off);
         nrm[p] = 0.0f;
       }
     }
     // the branch above is uniform per 16-lane token row; every row runs the transform (its
     // result is dropped for tokens that came from the residual, which are K_u already)
-    if (NP == 4 && XF == XF_PUBLISHED) {
+    if (!keys) {
+    } else if (NP == 4 && XF == XF_PUBLISHED) {
       float x[4][8], nq;
       uint4 nu[4];
 #pragma unroll
@@ -961,22 +987,22 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row, ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
-        kin4[j].load(knew + off);
-        vin4[j].load(vnew + off);
+        if (keys) kin4[j].load(knew + off);
+        if (values) vin4[j].load(vnew + off);
       }
       float x[4][8], nq;
       uint4 nu[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
-      key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+      if (keys) key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row;
         if (i < cnt) {
           const int ds = dst0 + i;
-          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
-          vin4[j].store(res_v + (size_t)ds * D + cg * 8);
-          if ((tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
+          if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
+          if (values) vin4[j].store(res_v + (size_t)ds * D + cg * 8);
+          if (keys && (tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
         }
       }
     } else {
@@ -985,12 +1011,13 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
         const int ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
         Raw8<IO> kin, vin;
-        kin.load(knew + off);
-        vin.load(vnew + off);
+        if (keys) kin.load(knew + off);
+        if (values) vin.load(vnew + off);
         float x[8], nn;
         kin.widen(x);
         uint4 nu;
-        if (NORM_ALL) {
+        if (!keys) {
+        } else if (NORM_ALL) {
           nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
           nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
         } else {
@@ -998,43 +1025,45 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
         }
         if (i < cnt) {
           const int ds = dst0 + i;
-          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
-          vin.store(res_v + (size_t)ds * D + cg * 8);
-          if (cg == 0) res_norm[ds] = from_f32<META>(nn);
+          if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
+          if (values) vin.store(res_v + (size_t)ds * D + cg * 8);
+          if (keys && cg == 0) res_norm[ds] = from_f32<META>(nn);
         }
       }
     }
   }
+  // every wave had its plan at the barrier above.  (In front of the tail, the tail's loads came back
+  // behind the answer: 8 x 500 tokens 13.2 -> 15.0 us.)
+  if (EARLY_TICKET) {
+    my_ticket = draw_ticket(P.c.tickets, P.c.tickets != nullptr, tid);
+    drawn = true;
+  }
   if (!do_block) break;
 
   const size_t pg = (size_t)phys * Hkv + kvh;
-  quantize_keys<META, BITS, KG, NP>(s, ku, batched_norms, nrm, nrm_q, P.c, P.g, pg, zp_min, tid, cg);
-  quantize_values<META, BITS, KG, NP>(s, vraw, P.c, P.g, pg, zp_min, tid, cg);
+  if (keys) quantize_keys<META, BITS, KG, NP>(s, ku, batched_norms, nrm, nrm_q, P.c, P.g, pg, zp_min, tid, cg);
+  if (SPLIT) advance_if_last();
+  if (values) quantize_values<META, BITS, KG, NP>(s, vraw, P.c, P.g, pg, zp_min, tid, cg);
+  advanced = SPLIT;
   } while (false);
 
-  // ---- length update, folded in: the last workgroup to finish advances the lengths of all
-  // sequences.  Every other workgroup consumed its loads of seq_lens / res_lens before it
-  // took its ticket, so no fence is needed (an agent-scope fence per workgroup costs a
+  // ---- length update, folded in: the workgroup that draws the last ticket advances the lengths of all
+  // sequences.  Every other workgroup's waves consumed their loads of seq_lens / res_lens before the
+  // barrier in front of its draw, so no fence is needed (an agent-scope fence per workgroup costs a
   // cache write-back each and nearly doubled the prefill time); the new lengths become
   // visible to later kernels at the end of this one. ----
-  if (P.c.tickets) {
+  if constexpr (EARLY_TICKET) {
+    if (!drawn) {
+      __syncthreads();
+      my_ticket = draw_ticket(P.c.tickets, P.c.tickets != nullptr, tid);
+    }
+    if (!advanced) advance_if_last();
+  } else if (P.c.tickets) {
     __shared__ int s_last;
     __syncthreads();
-    if (tid == 0) {
-      const int total = (int)(gridDim.x * gridDim.y * gridDim.z);
-      s_last = (atomicAdd(&P.c.tickets[0], 1) == total - 1) ? 1 : 0;
-    }
+    if (tid == 0) s_last = (atomicAdd(&P.c.tickets[0], 1) == total - 1) ? 1 : 0;
     __syncthreads();
-    if (s_last) {
-      for (int bb = tid; bb < P.c.batch; bb += NT) {
-        const SeqPlan q = plan_sequence(P, bb);
-        if (q.n > 0 && q.ok) {
-          P.c.seq_lens[bb] += q.n;
-          P.c.res_lens[bb] = q.tail_len;
-        }
-      }
-      if (tid == 0) P.c.tickets[0] = 0;
-    }
+    if (s_last) advance_all(tid, NT);
   }
 }
 
@@ -1056,13 +1085,13 @@ __global__ void oscar_update_lens_kernel(AppendParams P) {
 // 22.7 / 28.4; fp32, 2048 tokens (272) 13.1 / 9.8, 3072 (400) 14.3 / 19.4.
 template <typename IO> constexpr size_t small_grid_workgroups() { return sizeof(IO) == 4 ? 256 : 512; }
 
-template <typename IO, typename META, int BITS, int XF, int NP>
+template <typename IO, typename META, int BITS, int XF, int NP, bool SPLIT>
 int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
   const dim3 block(2048 / NP);
   switch (P.g.k_group) {
-    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF, NP>), grid, block, 0, st, P); break;
-    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF, NP>), grid, block, 0, st, P); break;
-    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF, NP>), grid, block, 0, st, P); break;
+    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF, NP, SPLIT>), grid, block, 0, st, P); break;
+    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF, NP, SPLIT>), grid, block, 0, st, P); break;
+    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF, NP, SPLIT>), grid, block, 0, st, P); break;
     default: return OSCAR_ERR_UNSUPPORTED;
   }
   return OSCAR_OK;
@@ -1075,10 +1104,16 @@ int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
     // the tail alone, one pass of the 16 token rows of the 256-thread form, whose half of the waves is then
     // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads
     // norm 6.5 / 7.7, 16 tokens 7.3 / 8.4; 17 tokens, a second pass, 5.1 / 4.6 and 9.8 / 9.1).
-    if (P.T > 16 && (size_t)grid.x * grid.y * grid.z <= small_grid_workgroups<IO>())
-      return launch_np<IO, META, BITS, XF, 4>(P, grid, st);
+    const size_t n = (size_t)grid.x * grid.y * grid.z;
+    // Up to half a workgroup a CU a block's two sides are two workgroups, each with its share of the tail: one
+    // workgroup's chain of loads, transform, key codes and value codes is the launch's time there (whole
+    // call in us, one / two workgroups a block, bf16 INT2, 8 heads: 1 x 128 tokens 11.8 / 8.9 with INT4, 1 x 512
+    // 10.4 / 7.5 with fp32, pieces of 2 x 500 10.3 / 9.4; past it, 8 x 500 in 512 workgroups, 13.1 / 14.6).
+    if (P.T > 16 && 2 * n <= 256)
+      return launch_np<IO, META, BITS, XF, 4, true>(P, dim3(grid.x, grid.y, 2 * grid.z), st);
+    if (P.T > 16 && n <= small_grid_workgroups<IO>()) return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
   }
-  return launch_np<IO, META, BITS, XF, 8>(P, grid, st);
+  return launch_np<IO, META, BITS, XF, 8, false>(P, grid, st);
 }
 
 template <typename IO, typename META, int XF>

@@ -1,5 +1,5 @@
-"""Multi-token appends in the 512-thread form (small launches) and the 256-thread form of the
-encoder: block edges, tails, and blocks that mix the residual window with new tokens, bit for bit
+"""Multi-token appends in the 512-thread forms (small launches; the smallest have two workgroups a block,
+one for the keys and one for the values) and the 256-thread form of the encoder: block edges, tails, and blocks that mix the residual window with new tokens, bit for bit
 against the oracle, at launch sizes on both sides of the choice."""
 import numpy as np
 import pytest
@@ -66,3 +66,25 @@ def test_pieces_at_the_choice_of_the_form_by_length(io, bits, kg, norm_all, eage
         o.append(kp, vp, eager=eager)
         assert_cache_equal(g, o, w)
         at += n
+
+
+@pytest.mark.parametrize("norm_all", [False, True])
+@pytest.mark.parametrize("io,meta,bits,kg", [("bf16", "f16", 2, 128), ("f32", "f32", 4, 32)])
+@pytest.mark.parametrize("hkv", [42, 43, 64, 65])   # three blocks a sequence: 126 and 129 workgroups; two: 128 and 130
+def test_pieces_where_a_block_becomes_one_workgroup(hkv, io, meta, bits, kg, norm_all):
+    pieces = [150, 300, 17, 131, 256]
+    total = sum(pieces)
+    w = synth.LLAMA8B_32K.replace(batch=1, n_q_heads=hkv, n_kv_heads=hkv, context=total, io_dtype=io, meta_dtype=meta,
+                                  bits=bits, k_group=kg)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, total // 128 + 2, norm_scope=1 if norm_all else 0)
+    ob = _ob()
+    at = 0
+    for n in pieces:
+        kp, vp = np.ascontiguousarray(k[:, at:at + n]), np.ascontiguousarray(v[:, at:at + n])
+        ob.quantize_append(g, to_dev(kp, io), to_dev(vp, io), eager=True, max_seq_len_hint=at)
+        o.append(kp, vp, eager=True)
+        at += n
+        if n in (150, 300, 256):
+            assert_cache_equal(g, o, w)
+    assert int(g.tickets.item()) == 0

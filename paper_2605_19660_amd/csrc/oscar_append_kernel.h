@@ -329,6 +329,12 @@ __device__ __forceinline__ uint4 key_transform8_given(float (&x)[8], const uint3
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// Whether oscar_token_norm_kernel runs in front of the encoder for this append: a single token that is not
+// flushed at once never moves into a page, and its norm is the encoder's.
+__host__ __device__ __forceinline__ bool token_norms_ahead(int T, uint32_t flags) {
+  return T > 1 || (flags & OSCAR_APPEND_EAGER) != 0;
+}
+
 // Token-wise norm over all kv heads (App. "Fused Hadamard-Norm Kernel": squared sums
 // accumulated across heads): every head's vector of the token is rotated, its squared sum
 // taken in the same tree order, the sums added in head order, one square root.
@@ -846,8 +852,10 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   bool batched_norms = false;
   float nrm_q[NP / 4] = {};
   // NORM_ALL: the norms of new tokens that end up in a page were written into that page's
-  // norm slots (of every head) by oscar_token_norm_kernel, launched just before this kernel
+  // norm slots (of every head) by oscar_token_norm_kernel, launched just before this kernel,
+  // those of the others into the residual window
   const META* pre_norm = nullptr;
+  const bool norms_ready = NORM_ALL && token_norms_ahead(P.T, P.flags);
   if (NORM_ALL && do_block) {
     const int phys0 = phys;
     pre_norm = reinterpret_cast<const META*>(reinterpret_cast<const uint8_t*>(P.c.k_norms) +
@@ -915,7 +923,8 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       if (pi < sp.r0) {
         if (keys) {
           kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
-          nrm[p] = to_f32<META>(res_norm[pi]);
+          // (a place that the new tail takes holds the tail's norm by now, and the page the old one)
+          nrm[p] = to_f32<META>(norms_ready && pi < sp.tail_len ? pre_norm[tok_meta_pos(pi)] : res_norm[pi]);
         }
         if (values) vraw[p].load(res_v + (size_t)pi * D + cg * 8);
       } else {
@@ -980,21 +989,29 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     // One token after the other, each behind its own loads, it was the longest part of a launch of
     // few workgroups: 500 new tokens took 4 us more than 512.  (The 256-thread form has no registers
     // for it.)
-    constexpr bool BATCHED_TAIL = NP == 4 && XF == XF_PUBLISHED;
+    constexpr bool BATCHED_TAIL = NP == 4 && XF != XF_SWITCHED;
     if (BATCHED_TAIL && cnt > ROWS) {   // (at most 128 = 4 * ROWS tokens)
       Raw8<IO> kin4[4], vin4[4];
+      float given[4];   // (NORM_ALL: this form is taken behind oscar_token_norm_kernel only)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row, ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
         if (keys) kin4[j].load(knew + off);
         if (values) vin4[j].load(vnew + off);
+        if (NORM_ALL && keys) given[j] = to_f32<META>(res_norm[dst0 + ic]);
       }
       float x[4][8], nq;
       uint4 nu[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
-      if (keys) key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+      if (!keys) {
+      } else if (NORM_ALL) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) nu[j] = key_transform8_given<META>(x[j], sgn, given[j], xf.rotate);
+      } else {
+        key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row;
@@ -1002,7 +1019,7 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
           const int ds = dst0 + i;
           if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
           if (values) vin4[j].store(res_v + (size_t)ds * D + cg * 8);
-          if (keys && (tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
+          if (!NORM_ALL && keys && (tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
         }
       }
     } else {
@@ -1010,15 +1027,18 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
         const int i = i0 + row;
         const int ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
+        float x[8], nn;
+        if (NORM_ALL && keys) {   // (worked out in front of the loads below: registers)
+          if (norms_ready) nn = to_f32<META>(res_norm[dst0 + ic]);
+          else nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
+        }
         Raw8<IO> kin, vin;
         if (keys) kin.load(knew + off);
         if (values) vin.load(vnew + off);
-        float x[8], nn;
         kin.widen(x);
         uint4 nu;
         if (!keys) {
         } else if (NORM_ALL) {
-          nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
           nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
         } else {
           nu = key_transform8<META>(x, sgn, nn, xf);
@@ -1027,7 +1047,7 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
           const int ds = dst0 + i;
           if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
           if (values) vin.store(res_v + (size_t)ds * D + cg * 8);
-          if (keys && cg == 0) res_norm[ds] = from_f32<META>(nn);
+          if (keys && cg == 0 && !norms_ready) res_norm[ds] = from_f32<META>(nn);
         }
       }
     }
@@ -1138,11 +1158,15 @@ int launch_meta(const AppendParams& P, dim3 grid, hipStream_t st) {
   return rc;
 }
 
-// Token norms over all kv heads for the new tokens that this call moves into pages
-// (pending index r0 <= pi < nq*R): one 16-lane row per token, 16 tokens per workgroup;
-// the norm goes into the token's slot of the norm plane of every head's page, where the
-// encoder kernel (launched next on the same stream) picks it up.  Tokens that stay in the
-// residual window are left to the encoder kernel itself.
+// Token norms over all kv heads for the new tokens of this call: one 16-lane row per token, 16 tokens
+// per workgroup.  The norm of a token that moves into a page (pending index r0 <= pi < nq*R) goes into
+// its slot of the norm plane of every head's page, the norm of one that stays in the residual window
+// into its place there; the encoder kernel (launched next on the same stream) picks both up.  Where the
+// place still holds the norm of an old residual token, that one moves to its page slot first.
+// (With the window's norms left to the encoder, each of its kv-head workgroups read every head of
+// those tokens once more, 16 tokens at a time.  Whole call in us, 8 heads bf16 INT2: 1000 tokens 25.9 -> 16.7,
+// pieces of 2 x 500 20.1 -> 13.7, 8 x 100 19.7 -> 13.1, 8 x 2000 57.7 -> 40.0; 60 x 16 14.8 -> 15.0, and
+// without tokens in the window 131072 171 -> 172 and 2 x 16384 53.0 -> 53.9.)
 template <typename IO, typename META>
 __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
   const int b = blockIdx.y, tid = threadIdx.x;
@@ -1154,22 +1178,29 @@ __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
   for (int st = 0; st < 4; ++st) sgn[st] = ((cg >> st) & 1) ? 0x80000000u : 0u;
   const SeqPlan sp = plan_sequence(P, b);
   if (sp.n <= 0 || !sp.ok) return;
-  const int t_first = (int)blockIdx.x * 16;         // (signed: n_paged below can be negative)
+  const int t_first = (int)blockIdx.x * 16;
   const int ti = t_first + (tid >> 4);              // new token of this row
-  const int n_paged = sp.nq * R - sp.r0;            // new tokens that go into pages
-  if (t_first >= n_paged) return;                   // whole workgroup idle
-  const int tc = ti < n_paged ? ti : n_paged - 1;   // whole rows stay active for the exchanges
+  if (t_first >= sp.n) return;                      // whole workgroup idle
+  const int tc = ti < sp.n ? ti : sp.n - 1;         // whole rows stay active for the exchanges
   const IO* knew = reinterpret_cast<const IO*>(P.k);
   const float nf = token_norm_all_heads<IO, META>(
       knew + (((size_t)b * P.T + (size_t)tc) * Hkv) * D + cg * 8, Hkv, sgn,
       P.c.cfg.rotation == OSCAR_ROTATION_ON);
-  if (ti < n_paged) {
-    const int pi = sp.r0 + ti;
-    const int phys = P.c.block_table[(size_t)b * P.c.max_pages_per_seq + sp.packed_pages + pi / R];
-    for (int h = row_lane; h < Hkv; h += 16) {
-      META* o = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(P.c.k_norms) +
-                                        ((size_t)phys * Hkv + h) * P.g.k_norms_bytes);
-      o[tok_meta_pos(pi % R)] = from_f32<META>(nf);
+  if (ti >= sp.n) return;
+  const int pi = sp.r0 + ti;                        // index among pending tokens
+  const int place = pi - sp.nq * R;                 // in the new residual window, if not negative
+  auto page_norms = [&](int blk, int h) {
+    const int phys = P.c.block_table[(size_t)b * P.c.max_pages_per_seq + sp.packed_pages + blk];
+    return reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(P.c.k_norms) +
+                                   ((size_t)phys * Hkv + h) * P.g.k_norms_bytes);
+  };
+  for (int h = row_lane; h < Hkv; h += 16) {
+    if (place < 0) {
+      page_norms(pi / R, h)[tok_meta_pos(pi % R)] = from_f32<META>(nf);
+    } else {
+      META* r = reinterpret_cast<META*>(P.c.res_norm) + ((size_t)b * Hkv + h) * R + place;
+      if (place < sp.r0 && sp.nq > 0) page_norms(0, h)[tok_meta_pos(place)] = *r;
+      *r = from_f32<META>(nf);
     }
   }
 }

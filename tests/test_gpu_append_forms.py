@@ -3,6 +3,7 @@ one for the keys and one for the values) and the 256-thread form of the encoder:
 against the oracle, at launch sizes on both sides of the choice."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_19660_amd import synth
 from test_gpu_parity import _ob, make_pair, to_dev, assert_cache_equal
@@ -88,3 +89,31 @@ def test_pieces_where_a_block_becomes_one_workgroup(hkv, io, meta, bits, kg, nor
         if n in (150, 300, 256):
             assert_cache_equal(g, o, w)
     assert int(g.tickets.item()) == 0
+
+
+@pytest.mark.parametrize("eager", [True, False])
+@pytest.mark.parametrize("batch,hkv", [(1, 3), (3, 40), (9, 30)])   # 256 threads for all pieces past 16 in the last
+@pytest.mark.parametrize("io,meta,bits,kg", [("bf16", "f16", 2, 128), ("f32", "f32", 4, 32)])
+def test_window_places_taken_while_their_old_norms_are_needed(io, meta, bits, kg, batch, hkv, eager):
+    """One norm over all heads: a new tail takes the places of old tokens that move into a page in the same
+    call.  Old and new windows of all relations: shorter, longer, equal, full, empty."""
+    pieces = [100, 40, 128, 88, 128, 200, 1, 127, 16, 130, 254]
+    total = sum(pieces)
+    w = synth.LLAMA8B_32K.replace(batch=batch, n_q_heads=hkv, n_kv_heads=hkv, context=total, io_dtype=io,
+                                  meta_dtype=meta, bits=bits, k_group=kg)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, total // 128 + 2, norm_scope=1)
+    ob = _ob()
+    at = 0
+    for i, n in enumerate(pieces):
+        kp, vp = np.ascontiguousarray(k[:, at:at + n]), np.ascontiguousarray(v[:, at:at + n])
+        lens = None
+        if batch > 1 and i == 5:   # one sequence gets nothing, one a token
+            lens = np.full(batch, n, np.int32)
+            lens[0], lens[1] = 0, 1
+        ob.quantize_append(g, to_dev(kp, io), to_dev(vp, io), None if lens is None else torch.from_numpy(lens).cuda(), eager=eager,
+                           max_seq_len_hint=at)
+        o.append(kp, vp, **({} if lens is None else {"new_lens": lens}), eager=eager)
+        at += n
+        if batch == 1 or i in (3, 5, 10):
+            assert_cache_equal(g, o, w)

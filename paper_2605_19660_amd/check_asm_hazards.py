@@ -1,4 +1,4 @@
-"""Static checks of the compiled kernels for two hazards the compiler cannot see.
+"""Static checks of the compiled kernels for hazards the compiler cannot see.
 
     python -m paper_2605_19660_amd.check_asm_hazards          (compiles to assembly, then scans)
 
@@ -36,7 +36,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ("oscar_decode_mfma.hip", "oscar_decode_mfma_zpmin.hip", "oscar_decode_mfma_meta32.hip",
            "oscar_decode_mfma_meta32_zpmin.hip", "oscar_decode_step.hip", "oscar_decode_step_zpmin.hip")
-DPP_SOURCES = SOURCES + ("oscar_quantize.hip",)    # the encoder and the stand-alone rotations
+# the encoders and the stand-alone rotations
+DPP_SOURCES = SOURCES + ("oscar_quantize.hip", "oscar_quantize_allheads.hip", "oscar_quantize_switched.hip")
 
 
 def _regs(tok: str) -> set[int]:
@@ -142,6 +143,37 @@ def scan_dpp(asm_text: str) -> list[tuple]:
     return found
 
 
+def scan_swap(asm_text: str) -> list[tuple]:
+    lines = asm_text.split("\n")
+    found, flag, kernel = [], False, None
+    hist: list[tuple[set[int], int, int, bool]] = []   # (written registers, line number, slots ago, inside asm)
+    for i, l in enumerate(lines):
+        m = re.match(r"^(_Z\S+):", l)
+        if m:
+            kernel, hist = m.group(1), []
+        if "#ASMSTART" in l:
+            flag = True
+        if "#ASMEND" in l:
+            flag = False
+        t = l.strip()
+        if not t or t[0] in ";." or t.endswith(":"):
+            if t.endswith(":") and not t.startswith(";"):
+                hist = []                          # control flow joins: another block's writes
+            continue
+        op = t.split()[0]
+        step = int(t.split()[1]) + 1 if op == "s_nop" else 1
+        ops = _operands(t) if op.startswith("v_") else []
+        swap = op.startswith("v_permlane") and "_swap" in op
+        if swap:
+            for regs, ln, ago, in_asm in hist:
+                if ago < 2 and (in_asm or flag) and regs & (ops[0] | ops[1]):
+                    found.append((kernel, ln + 1, lines[ln].strip(), i + 1, t, ago))
+        hist = [(r, ln, ago + step, a) for r, ln, ago, a in hist if ago + step < 4]
+        if ops and not op.startswith("v_cmp"):
+            hist.append((ops[0] | ops[1] if swap else set(ops[0]), i, 0, flag))   # (a swap writes both)
+    return found
+
+
 def compile_to_asm(source: str) -> str:
     from .build import COMMON, CSRC, SOURCES as BUILD_SOURCES
     with tempfile.TemporaryDirectory() as d:
@@ -155,7 +187,7 @@ def compile_to_asm(source: str) -> str:
 def main() -> int:
     from concurrent.futures import ThreadPoolExecutor
     bad = 0
-    with ThreadPoolExecutor(max_workers=3) as ex:
+    with ThreadPoolExecutor(max_workers=5) as ex:
         texts = list(ex.map(compile_to_asm, DPP_SOURCES))
     for src, text in zip(DPP_SOURCES, texts):
         if src in SOURCES:
@@ -168,6 +200,12 @@ def main() -> int:
         n_dpp = len(re.findall(r"#ASMSTART(?:(?!#ASMEND).)*?_dpp", text, re.S))
         found = scan_dpp(text)
         print("%s: %d asm blocks with DPP instructions, %d DPP reads inside two slots of the write" % (src, n_dpp, len(found)))
+        for k, i, t, j, tj, ago in found[:20]:
+            print("  %s\n    line %d: %s\n    line %d (%d slots later): %s" % (k, i, t, j, ago, tj))
+        bad += len(found)
+        n_swap = len(re.findall(r"v_permlane\d+_swap", text))
+        found = scan_swap(text)
+        print("%s: %d half-register swaps, %d reads inside two slots of an asm write" % (src, n_swap, len(found)))
         for k, i, t, j, tj, ago in found[:20]:
             print("  %s\n    line %d: %s\n    line %d (%d slots later): %s" % (k, i, t, j, ago, tj))
         bad += len(found)

@@ -392,15 +392,28 @@ __device__ __forceinline__ uint32_t pk_max_f16(uint32_t a, uint32_t b) {
   asm volatile("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
-// op over the four 16-lane rows of a wave, four words at once: row j of the result holds word j.  The
-// registers of two words trade rows (16, then 32 lanes apart), so that every lane has work: three swaps
-// and three operations, where each word for itself took eight shuffles through LDS and eight operations
-// (prefill of 131072 tokens INT2 122.5 -> 120.8 us, 8 x 4K INT4 with four key groups a page 43.1 -> 41.9).
-template <typename OP> __device__ __forceinline__ uint32_t rows_reduce(const uint32_t (&w)[4], OP op) {
-  const auto a = __builtin_amdgcn_permlane16_swap(w[0], w[1], false, false);
-  const auto b = __builtin_amdgcn_permlane16_swap(w[2], w[3], false, false);
-  const auto c = __builtin_amdgcn_permlane32_swap(op(a[0], a[1]), op(b[0], b[1]), false, false);
-  return op(c[0], c[1]);
+// Minimum and maximum over the four 16-lane rows of a wave, four words of each at once: row j of the
+// result holds word j.  The registers of two words trade rows (16, then 32 lanes apart), so that every
+// lane has work: three swaps and three operations, where each word for itself took eight shuffles through
+// LDS and eight operations (prefill of 131072 tokens INT2 122.5 -> 120.8 us, 8 x 4K INT4 with four key
+// groups a page 43.1 -> 41.9).
+// A swap must not read a register inside two issue slots of a vector write.  The compiler sees to that
+// behind its own instructions and not behind an asm block, where pk_min / pk_max leave their results: the
+// wait stands here, once for the eight registers of a stage.
+__device__ __forceinline__ void rows_min_max(uint32_t (&mn)[4], uint32_t (&mx)[4], uint32_t& rmn, uint32_t& rmx) {
+  asm volatile("s_nop 1" : "+v"(mn[0]), "+v"(mn[1]), "+v"(mn[2]), "+v"(mn[3]),
+                           "+v"(mx[0]), "+v"(mx[1]), "+v"(mx[2]), "+v"(mx[3]));
+  const auto na = __builtin_amdgcn_permlane16_swap(mn[0], mn[1], false, false);
+  const auto nb = __builtin_amdgcn_permlane16_swap(mn[2], mn[3], false, false);
+  const auto xa = __builtin_amdgcn_permlane16_swap(mx[0], mx[1], false, false);
+  const auto xb = __builtin_amdgcn_permlane16_swap(mx[2], mx[3], false, false);
+  uint32_t n0 = pk_min_f16(na[0], na[1]), n1 = pk_min_f16(nb[0], nb[1]);
+  uint32_t x0 = pk_max_f16(xa[0], xa[1]), x1 = pk_max_f16(xb[0], xb[1]);
+  asm volatile("s_nop 1" : "+v"(n0), "+v"(n1), "+v"(x0), "+v"(x1));
+  const auto nc = __builtin_amdgcn_permlane32_swap(n0, n1, false, false);
+  const auto xc = __builtin_amdgcn_permlane32_swap(x0, x1, false, false);
+  rmn = pk_min_f16(nc[0], nc[1]);
+  rmx = pk_max_f16(xc[0], xc[1]);
 }
 __device__ __forceinline__ float half_of(uint32_t w, int hi) {
   return __half2float(__ushort_as_half((unsigned short)(hi ? (w >> 16) : (w & 0xffffu))));
@@ -547,7 +560,8 @@ __device__ __forceinline__ void quantize_keys(EncoderLds<META, BITS, KG, NP>& s,
       }
     }
     // over the wave's four token rows: row j ends with word j
-    const uint32_t rmn = rows_reduce(mn, pk_min_f16), rmx = rows_reduce(mx, pk_max_f16);
+    uint32_t rmn, rmx;
+    rows_min_max(mn, mx, rmn, rmx);
     reinterpret_cast<uint32_t*>(&s.red[gk][wave][cg].mn)[lane >> 4] = rmn;
     reinterpret_cast<uint32_t*>(&s.red[gk][wave][cg].mx)[lane >> 4] = rmx;
   }

@@ -1,7 +1,8 @@
 """The compiled matrix-core decode kernels hold no asm-block write into the destination of a
-matrix instruction that may still be in flight, and no asm block of the decode kernels or of the
-encoder reads a DPP operand inside two issue slots of its write -- hazards the compiler cannot
-guard (paper_2605_19660_amd/check_asm_hazards.py).  Needs hipcc, no GPU."""
+matrix instruction that may still be in flight, no asm block of the decode kernels or of the
+encoders reads a DPP operand inside two issue slots of its write, and no half-register swap reads
+what an asm block wrote inside two slots -- hazards the compiler cannot guard
+(paper_2605_19660_amd/check_asm_hazards.py).  Needs hipcc, no GPU."""
 import shutil
 
 import pytest
@@ -49,6 +50,28 @@ def test_dpp_scanner_wants_two_slots_between_a_write_and_its_dpp_read():
     assert len(chk.scan_dpp(twice)) == 1
     # the compiler's own DPP instructions are its business
     assert chk.scan_dpp(block("").replace("\t;;#ASMSTART\n", "").replace("\t;;#ASMEND\n", "")) == []
+
+
+def test_swap_scanner_wants_two_slots_behind_an_asm_write():
+    swap = "\tv_permlane32_swap_b32_e32 v41, v42\n"
+    def block(between, write="v_pk_min_f16 v42, v38, v40"):
+        return "_Zkernel:\n\t;;#ASMSTART\n\t" + write + "\n\t;;#ASMEND\n" + between + swap
+    assert len(chk.scan_swap(block(""))) == 1
+    assert len(chk.scan_swap(block("\tv_lshrrev_b32_e32 v39, 4, v0\n"))) == 1     # one slot
+    assert len(chk.scan_swap(block("\ts_nop 0\n"))) == 1
+    assert chk.scan_swap(block("\ts_nop 1\n")) == []
+    assert chk.scan_swap(block("\t;;#ASMSTART\n\ts_nop 1\n\t;;#ASMEND\n")) == []
+    assert chk.scan_swap(block("\tv_mov_b32_e32 v9, v8\n\tv_mov_b32_e32 v10, v8\n")) == []
+    # either register of the swap counts, another one does not
+    assert len(chk.scan_swap(block("", "v_pk_max_f16 v41, v38, v40"))) == 1
+    assert chk.scan_swap(block("", "v_pk_max_f16 v43, v38, v40")) == []
+    # behind the compiler's own writes the compiler waits; a swap inside a block is nobody's business but ours
+    plain = "_Zkernel:\n\tv_add_u32_e32 v42, v1, v2\n"
+    assert chk.scan_swap(plain + swap) == []
+    assert len(chk.scan_swap(plain + "\t;;#ASMSTART\n" + swap + "\t;;#ASMEND\n")) == 1
+    # both registers of a swap are written by it
+    twice = "_Zkernel:\n\t;;#ASMSTART\n\ts_nop 1\n" + swap + "\tv_permlane16_swap_b32_e32 v42, v50\n\t;;#ASMEND\n"
+    assert len(chk.scan_swap(twice)) == 1
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")

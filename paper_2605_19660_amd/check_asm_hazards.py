@@ -27,6 +27,7 @@ counts as n + 1 slots).
 """
 from __future__ import annotations
 
+import functools
 import os
 import re
 import subprocess
@@ -174,6 +175,15 @@ def scan_swap(asm_text: str) -> list[tuple]:
     return found
 
 
+def scratch_bytes(asm_text: str) -> dict[str, int]:
+    """Bytes of scratch memory a lane of each kernel, from the listing's kernel descriptions."""
+    names = re.findall(r"^    \.name: +(\S+)$", asm_text, re.M)
+    sizes = re.findall(r"^    \.private_segment_fixed_size: +(\d+)$", asm_text, re.M)
+    assert len(names) == len(sizes)
+    return {n: int(b) for n, b in zip(names, sizes)}
+
+
+@functools.lru_cache(maxsize=None)
 def compile_to_asm(source: str) -> str:
     from .build import COMMON, CSRC, SOURCES as BUILD_SOURCES
     with tempfile.TemporaryDirectory() as d:

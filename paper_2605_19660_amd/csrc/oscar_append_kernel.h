@@ -52,8 +52,12 @@ struct AppendParams {
 // variants' code):
 //   XF_PUBLISHED  rotation on, L2 norm per (token, kv head): the switches are constants
 //   XF_SWITCHED   rotation and scaling coefficient read from the configuration (the ablations)
-//   XF_ALL_HEADS  one norm over all kv heads, with the norm pre-pass it needs
-constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2;
+//   XF_ALL_HEADS  one norm over all kv heads, behind the norm pre-pass
+//   XF_ALL_HEADS_ONE  the same for a single token that is not flushed at once: it never moves into a page,
+//                 and the encoder works its norm out.  (In one kernel with the form above, chosen by a
+//                 branch, this path kept three registers of the prefill in scratch memory: 2 x 16384 tokens
+//                 53.8 us, without 52.7, 8 x 2000 39.4, 38.7)
+constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2, XF_ALL_HEADS_ONE = 3;
 int oscar_launch_append_switched(const AppendParams& P, dim3 grid, hipStream_t st);
 int oscar_launch_append_all_heads(const AppendParams& P, dim3 grid, hipStream_t st);
 
@@ -327,12 +331,6 @@ __device__ __forceinline__ uint4 key_transform8_given(float (&x)[8], const uint3
   for (int i = 0; i < 4; ++i)
     w[i] = pack_halves(pin_f32(x[2 * i] * inv), pin_f32(x[2 * i + 1] * inv));
   return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// Whether oscar_token_norm_kernel runs in front of the encoder for this append: a single token that is not
-// flushed at once never moves into a page, and its norm is the encoder's.
-__host__ __device__ __forceinline__ bool token_norms_ahead(int T, uint32_t flags) {
-  return T > 1 || (flags & OSCAR_APPEND_EAGER) != 0;
 }
 
 // Token-wise norm over all kv heads (App. "Fused Hadamard-Norm Kernel": squared sums
@@ -796,8 +794,8 @@ __device__ __forceinline__ void quantize_values(EncoderLds<META, BITS, KG, NP>& 
 // which are the two halves of a packed value piece.
 // SPLIT: two workgroups a block, one for the keys and one for the values (they touch different arrays).
 template <typename IO, typename META, int BITS, int KG, int XF, int NP, bool SPLIT>
-__global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF == 2 ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
-  constexpr bool NORM_ALL = XF == XF_ALL_HEADS;
+__global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF >= XF_ALL_HEADS ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
+  constexpr bool NORM_ALL = XF >= XF_ALL_HEADS, norms_ready = XF == XF_ALL_HEADS;
   constexpr int NT = 2048 / NP, ROWS = NT / 16;   // threads, token rows
   __shared__ EncoderLds<META, BITS, KG, NP> s;
 
@@ -832,9 +830,10 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     }
     if (first == 0) P.c.tickets[0] = 0;
   };
-  const int total = (int)(gridDim.x * gridDim.y * gridDim.z);
+  // (worked out where it is asked for: held from here on, the product costs the prefill forms registers)
+  auto is_last = [&](int ticket) { return ticket == (int)(gridDim.x * gridDim.y * gridDim.z) - 1; };
   auto advance_if_last = [&]() {
-    if (P.c.tickets && tid < 64 && ticket_answer(my_ticket) == total - 1) advance_all(tid, 64);
+    if (P.c.tickets && tid < 64 && is_last(ticket_answer(my_ticket))) advance_all(tid, 64);
   };
   do {  // one pass; "break" = this workgroup has nothing (more) to do
   if (sp.n <= 0) break;
@@ -869,13 +868,13 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   // norm slots (of every head) by oscar_token_norm_kernel, launched just before this kernel,
   // those of the others into the residual window
   const META* pre_norm = nullptr;
-  const bool norms_ready = NORM_ALL && token_norms_ahead(P.T, P.flags);
   if (NORM_ALL && do_block) {
     const int phys0 = phys;
     pre_norm = reinterpret_cast<const META*>(reinterpret_cast<const uint8_t*>(P.c.k_norms) +
                                              ((size_t)phys0 * Hkv + kvh) * P.g.k_norms_bytes);
   }
-  if (do_block && blk * R >= sp.r0) {
+  // (a block that a single token completes is the old window)
+  if (XF != XF_ALL_HEADS_ONE && do_block && blk * R >= sp.r0) {
     // the whole block is new tokens (every block of a prefill): straight-line loads
     Raw8<IO> kraw[NP];
     const size_t tok0 = (size_t)b * P.T + (size_t)(blk * R - sp.r0 + slot + 16 * grp);
@@ -1095,7 +1094,7 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   } else if (P.c.tickets) {
     __shared__ int s_last;
     __syncthreads();
-    if (tid == 0) s_last = (atomicAdd(&P.c.tickets[0], 1) == total - 1) ? 1 : 0;
+    if (tid == 0) s_last = is_last(atomicAdd(&P.c.tickets[0], 1)) ? 1 : 0;
     __syncthreads();
     if (s_last) advance_all(tid, NT);
   }
@@ -1132,8 +1131,8 @@ int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
 }
 template <typename IO, typename META, int BITS, int XF>
 int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
-  // (the ablation switches keep the one form)
-  if constexpr (XF != XF_SWITCHED) {
+  // (the ablation switches keep the one form, and a single token has no use for another)
+  if constexpr (XF == XF_PUBLISHED || XF == XF_ALL_HEADS) {
     // An append of up to 16 tokens moves a page once in eight calls or fewer; the rest of the time it is
     // the tail alone, one pass of the 16 token rows of the 256-thread form, whose half of the waves is then
     // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads

@@ -8,13 +8,12 @@
 #include "oscar_append_kernel.h"
 
 int oscar_launch_append_all_heads(const AppendParams& P, dim3 grid, hipStream_t st) {
-  if (token_norms_ahead(P.T, P.flags)) {
-    switch (P.c.cfg.io_dtype) {
-      case OSCAR_F32: launch_token_norms<float>(P, st); break;
-      case OSCAR_BF16: launch_token_norms<__hip_bfloat16>(P, st); break;
-      case OSCAR_F16: launch_token_norms<__half>(P, st); break;
-      default: return OSCAR_ERR_UNSUPPORTED;
-    }
+  if (P.T == 1 && !(P.flags & OSCAR_APPEND_EAGER)) return launch_append<XF_ALL_HEADS_ONE>(P, grid, st);
+  switch (P.c.cfg.io_dtype) {
+    case OSCAR_F32: launch_token_norms<float>(P, st); break;
+    case OSCAR_BF16: launch_token_norms<__hip_bfloat16>(P, st); break;
+    case OSCAR_F16: launch_token_norms<__half>(P, st); break;
+    default: return OSCAR_ERR_UNSUPPORTED;
   }
   return launch_append<XF_ALL_HEADS>(P, grid, st);
 }

@@ -77,3 +77,13 @@ def test_swap_scanner_wants_two_slots_behind_an_asm_write():
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 def test_compiled_kernels_are_clean():
     assert chk.main() == 0
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+@pytest.mark.parametrize("source", ["oscar_quantize.hip", "oscar_quantize_allheads.hip"])
+def test_encoders_keep_nothing_in_scratch_memory(source):
+    """The prefill forms sit at the last register of four waves a SIMD; the ablations' encoder, which is
+    past it, is not held to this."""
+    used = {k: b for k, b in chk.scratch_bytes(chk.compile_to_asm(source)).items() if "append" in k or "norm" in k}
+    assert len(used) > 50
+    assert {k: b for k, b in used.items() if b} == {}

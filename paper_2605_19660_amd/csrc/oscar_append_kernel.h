@@ -52,12 +52,13 @@ struct AppendParams {
 // variants' code):
 //   XF_PUBLISHED  rotation on, L2 norm per (token, kv head): the switches are constants
 //   XF_SWITCHED   rotation and scaling coefficient read from the configuration (the ablations)
-//   XF_ALL_HEADS  one norm over all kv heads, behind the norm pre-pass
-//   XF_ALL_HEADS_ONE  the same for a single token that is not flushed at once: it never moves into a page,
-//                 and the encoder works its norm out.  (In one kernel with the form above, chosen by a
-//                 branch, this path kept three registers of the prefill in scratch memory: 2 x 16384 tokens
-//                 53.8 us, without 52.7, 8 x 2000 39.4, 38.7)
-constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2, XF_ALL_HEADS_ONE = 3;
+//   XF_ALL_HEADS  one norm over all kv heads, which the norm pre-pass works out
+//   XF_ALL_HEADS_FEW  the same for appends of up to kFewTokens: the encoder works the norms of tokens that
+//                 stay in the window out by itself, and the pre-pass those of tokens that move into a page
+//                 (In one kernel with the form above, chosen by a branch, this path kept three registers of
+//                 the prefill in scratch memory: 2 x 16384 tokens 53.8 us, without 52.7, 8 x 2000 39.4, 38.7)
+constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2, XF_ALL_HEADS_FEW = 3;
+constexpr int kFewTokens = 16;   // one pass of the 256-thread form's token rows
 int oscar_launch_append_switched(const AppendParams& P, dim3 grid, hipStream_t st);
 int oscar_launch_append_all_heads(const AppendParams& P, dim3 grid, hipStream_t st);
 
@@ -866,15 +867,15 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   float nrm_q[NP / 4] = {};
   // NORM_ALL: the norms of new tokens that end up in a page were written into that page's
   // norm slots (of every head) by oscar_token_norm_kernel, launched just before this kernel,
-  // those of the others into the residual window
+  // and, with norms_ready, those of the others into the residual window
   const META* pre_norm = nullptr;
   if (NORM_ALL && do_block) {
     const int phys0 = phys;
     pre_norm = reinterpret_cast<const META*>(reinterpret_cast<const uint8_t*>(P.c.k_norms) +
                                              ((size_t)phys0 * Hkv + kvh) * P.g.k_norms_bytes);
   }
-  // (a block that a single token completes is the old window)
-  if (XF != XF_ALL_HEADS_ONE && do_block && blk * R >= sp.r0) {
+  // (a block that a few tokens complete holds the old window)
+  if (XF != XF_ALL_HEADS_FEW && do_block && blk * R >= sp.r0) {
     // the whole block is new tokens (every block of a prefill): straight-line loads
     Raw8<IO> kraw[NP];
     const size_t tok0 = (size_t)b * P.T + (size_t)(blk * R - sp.r0 + slot + 16 * grp);
@@ -1005,7 +1006,7 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     constexpr bool BATCHED_TAIL = NP == 4 && XF != XF_SWITCHED;
     if (BATCHED_TAIL && cnt > ROWS) {   // (at most 128 = 4 * ROWS tokens)
       Raw8<IO> kin4[4], vin4[4];
-      float given[4];   // (NORM_ALL: this form is taken behind oscar_token_norm_kernel only)
+      float given[4];   // (NORM_ALL: the norms are there in this form)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row, ic = i < cnt ? i : cnt - 1;
@@ -1131,9 +1132,9 @@ int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
 }
 template <typename IO, typename META, int BITS, int XF>
 int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
-  // (the ablation switches keep the one form, and a single token has no use for another)
+  // (the ablation switches keep the one form, and a few tokens have no use for another)
   if constexpr (XF == XF_PUBLISHED || XF == XF_ALL_HEADS) {
-    // An append of up to 16 tokens moves a page once in eight calls or fewer; the rest of the time it is
+    // An append of up to kFewTokens moves a page once in eight calls or fewer; the rest of the time it is
     // the tail alone, one pass of the 16 token rows of the 256-thread form, whose half of the waves is then
     // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads
     // norm 6.5 / 7.7, 16 tokens 7.3 / 8.4; 17 tokens, a second pass, 5.1 / 4.6 and 9.8 / 9.1).
@@ -1142,9 +1143,9 @@ int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
     // workgroup's chain of loads, transform, key codes and value codes is the launch's time there (whole
     // call in us, one / two workgroups a block, bf16 INT2, 8 heads: 1 x 128 tokens 11.8 / 8.9 with INT4, 1 x 512
     // 10.4 / 7.5 with fp32, pieces of 2 x 500 10.3 / 9.4; past it, 8 x 500 in 512 workgroups, 13.1 / 14.6).
-    if (P.T > 16 && 2 * n <= 256)
+    if (P.T > kFewTokens && 2 * n <= 256)
       return launch_np<IO, META, BITS, XF, 4, true>(P, dim3(grid.x, grid.y, 2 * grid.z), st);
-    if (P.T > 16 && n <= small_grid_workgroups<IO>()) return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
+    if (P.T > kFewTokens && n <= small_grid_workgroups<IO>()) return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
   }
   return launch_np<IO, META, BITS, XF, 8, false>(P, grid, st);
 }
@@ -1174,13 +1175,15 @@ int launch_meta(const AppendParams& P, dim3 grid, hipStream_t st) {
 // Token norms over all kv heads for the new tokens of this call: one 16-lane row per token, 16 tokens
 // per workgroup.  The norm of a token that moves into a page (pending index r0 <= pi < nq*R) goes into
 // its slot of the norm plane of every head's page, the norm of one that stays in the residual window
-// into its place there; the encoder kernel (launched next on the same stream) picks both up.  Where the
-// place still holds the norm of an old residual token, that one moves to its page slot first.
-// (With the window's norms left to the encoder, each of its kv-head workgroups read every head of
+// into its place there (WINDOW; otherwise it is left to the encoder); the encoder kernel (launched next on
+// the same stream) picks both up.  Where the place still holds the norm of an old residual token, that one
+// moves to its page slot first.
+// (With the window's norms left to the encoder, each of its kv-head workgroups reads every head of
 // those tokens once more, 16 tokens at a time.  Whole call in us, 8 heads bf16 INT2: 1000 tokens 25.9 -> 16.7,
-// pieces of 2 x 500 20.1 -> 13.7, 8 x 100 19.7 -> 13.1, 8 x 2000 57.7 -> 40.0; 60 x 16 14.8 -> 15.0, and
-// without tokens in the window 131072 171 -> 172 and 2 x 16384 53.0 -> 53.9.)
-template <typename IO, typename META>
+// pieces of 2 x 500 20.1 -> 13.7, 8 x 100 19.7 -> 13.1, 8 x 2000 57.7 -> 40.0.  Up to 16 tokens that is
+// one round of loads in the encoder, and here there is mostly nothing to do: 60 x 16 15.3 with the window's
+// norms from here, 14.8 from the encoder, 60 x 8 14.4 and 13.9, 60 x 2 13.4 and 12.9.)
+template <typename IO, typename META, bool WINDOW>
 __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
   const int b = blockIdx.y, tid = threadIdx.x;
   const int row_lane = tid & 15;
@@ -1191,15 +1194,16 @@ __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
   for (int st = 0; st < 4; ++st) sgn[st] = ((cg >> st) & 1) ? 0x80000000u : 0u;
   const SeqPlan sp = plan_sequence(P, b);
   if (sp.n <= 0 || !sp.ok) return;
-  const int t_first = (int)blockIdx.x * 16;
+  const int t_first = (int)blockIdx.x * 16;         // (signed: n_here can be negative)
   const int ti = t_first + (tid >> 4);              // new token of this row
-  if (t_first >= sp.n) return;                      // whole workgroup idle
-  const int tc = ti < sp.n ? ti : sp.n - 1;         // whole rows stay active for the exchanges
+  const int n_here = WINDOW ? sp.n : sp.nq * R - sp.r0;   // (new tokens that go into pages)
+  if (t_first >= n_here) return;                    // whole workgroup idle
+  const int tc = ti < n_here ? ti : n_here - 1;     // whole rows stay active for the exchanges
   const IO* knew = reinterpret_cast<const IO*>(P.k);
   const float nf = token_norm_all_heads<IO, META>(
       knew + (((size_t)b * P.T + (size_t)tc) * Hkv) * D + cg * 8, Hkv, sgn,
       P.c.cfg.rotation == OSCAR_ROTATION_ON);
-  if (ti >= sp.n) return;
+  if (ti >= n_here) return;
   const int pi = sp.r0 + ti;                        // index among pending tokens
   const int place = pi - sp.nq * R;                 // in the new residual window, if not negative
   auto page_norms = [&](int blk, int h) {
@@ -1208,7 +1212,7 @@ __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
                                    ((size_t)phys * Hkv + h) * P.g.k_norms_bytes);
   };
   for (int h = row_lane; h < Hkv; h += 16) {
-    if (place < 0) {
+    if (!WINDOW || place < 0) {
       page_norms(pi / R, h)[tok_meta_pos(pi % R)] = from_f32<META>(nf);
     } else {
       META* r = reinterpret_cast<META*>(P.c.res_norm) + ((size_t)b * Hkv + h) * R + place;
@@ -1218,13 +1222,13 @@ __global__ __launch_bounds__(256) void oscar_token_norm_kernel(AppendParams P) {
   }
 }
 
-template <typename IO>
+template <typename IO, bool WINDOW>
 int launch_token_norms(const AppendParams& P, hipStream_t st) {
   const dim3 grid((unsigned)((P.T + 15) / 16), (unsigned)P.c.batch);
   if (P.c.cfg.meta_dtype == OSCAR_F16)
-    hipLaunchKernelGGL((oscar_token_norm_kernel<IO, __half>), grid, dim3(256), 0, st, P);
+    hipLaunchKernelGGL((oscar_token_norm_kernel<IO, __half, WINDOW>), grid, dim3(256), 0, st, P);
   else
-    hipLaunchKernelGGL((oscar_token_norm_kernel<IO, float>), grid, dim3(256), 0, st, P);
+    hipLaunchKernelGGL((oscar_token_norm_kernel<IO, float, WINDOW>), grid, dim3(256), 0, st, P);
   return OSCAR_OK;
 }
 

@@ -117,3 +117,25 @@ def test_window_places_taken_while_their_old_norms_are_needed(io, meta, bits, kg
         at += n
         if batch == 1 or i in (3, 5, 10):
             assert_cache_equal(g, o, w)
+
+
+@pytest.mark.parametrize("eager", [True, False])
+@pytest.mark.parametrize("io,meta,bits,kg", [("bf16", "f16", 2, 128), ("f16", "f32", 4, 32), ("f32", "f16", 4, 64)])
+def test_few_tokens_across_a_page_edge_with_one_norm_over_all_heads(io, meta, bits, kg, eager):
+    """Appends of up to 16 tokens: the norms of those that move into a page come from the launch in front, the
+    others' from the encoder.  The edge at every place of an append, sequences of a batch at different ones."""
+    pieces = [120, 16, 111, 1, 1, 127, 16, 112, 15, 1, 114, 14, 128, 16, 16]
+    total = sum(pieces)
+    w = synth.LLAMA8B_32K.replace(batch=5, n_q_heads=6, n_kv_heads=3, context=total, io_dtype=io, meta_dtype=meta,
+                                  bits=bits, k_group=kg)
+    k, v = synth.make_kv_batch(w)
+    g, o = make_pair(w, total // 128 + 2, norm_scope=1)
+    ob = _ob()
+    at = 0
+    for i, n in enumerate(pieces):
+        kp, vp = np.ascontiguousarray(k[:, at:at + n]), np.ascontiguousarray(v[:, at:at + n])
+        lens = np.array([n, max(n - 1, 0), n, (n + 1) // 2, 0 if i % 3 == 1 else n], np.int32)
+        ob.quantize_append(g, to_dev(kp, io), to_dev(vp, io), torch.from_numpy(lens).cuda(), eager=eager, max_seq_len_hint=at)
+        o.append(kp, vp, new_lens=lens, eager=eager)
+        assert_cache_equal(g, o, w)
+        at += n

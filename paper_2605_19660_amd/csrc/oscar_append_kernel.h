@@ -1111,13 +1111,13 @@ __global__ void oscar_update_lens_kernel(AppendParams P) {
   P.c.res_lens[b] = sp.tail_len;
 }
 
-// Largest launch that takes the 512-thread form: what is resident at once on 256 CUs, two workgroups
-// a CU for the 16-bit input types and one for fp32 (registers).  Measured, the whole call in us, 256 / 512
+// Largest launch that takes the 512-thread form, in workgroups a CU: what is resident at once, two
+// for the 16-bit input types and one for fp32 (registers).  Measured, the whole call in us, 256 / 512
 // threads: 2 sequences x 8 heads bf16 INT2, 500 new tokens behind 116 old ones (64 workgroups)
 // 11.4 / 9.1 (13.0 before the batched tail), 3072 tokens (400) 10.9 / 10.8, 4096 (528) 12.9 / 12.6,
 // 6144 (784) 17.0 / 19.2; 8 sequences INT4 G_k = 32, 500 tokens (256) 14.2 / 11.7, 2048 (1088)
 // 22.7 / 28.4; fp32, 2048 tokens (272) 13.1 / 9.8, 3072 (400) 14.3 / 19.4.
-template <typename IO> constexpr size_t small_grid_workgroups() { return sizeof(IO) == 4 ? 256 : 512; }
+template <typename IO> constexpr size_t small_grid_workgroups_per_cu() { return sizeof(IO) == 4 ? 1 : 2; }
 
 template <typename IO, typename META, int BITS, int XF, int NP, bool SPLIT>
 int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
@@ -1138,14 +1138,15 @@ int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
     // the tail alone, one pass of the 16 token rows of the 256-thread form, whose half of the waves is then
     // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads
     // norm 6.5 / 7.7, 16 tokens 7.3 / 8.4; 17 tokens, a second pass, 5.1 / 4.6 and 9.8 / 9.1).
-    const size_t n = (size_t)grid.x * grid.y * grid.z;
+    const size_t n = (size_t)grid.x * grid.y * grid.z, n_cu = (size_t)oscar_compute_units();
     // Up to half a workgroup a CU a block's two sides are two workgroups, each with its share of the tail: one
     // workgroup's chain of loads, transform, key codes and value codes is the launch's time there (whole
     // call in us, one / two workgroups a block, bf16 INT2, 8 heads: 1 x 128 tokens 11.8 / 8.9 with INT4, 1 x 512
     // 10.4 / 7.5 with fp32, pieces of 2 x 500 10.3 / 9.4; past it, 8 x 500 in 512 workgroups, 13.1 / 14.6).
-    if (P.T > kFewTokens && 2 * n <= 256)
+    if (P.T > kFewTokens && 2 * n <= n_cu)
       return launch_np<IO, META, BITS, XF, 4, true>(P, dim3(grid.x, grid.y, 2 * grid.z), st);
-    if (P.T > kFewTokens && n <= small_grid_workgroups<IO>()) return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
+    if (P.T > kFewTokens && n <= small_grid_workgroups_per_cu<IO>() * n_cu)
+      return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
   }
   return launch_np<IO, META, BITS, XF, 8, false>(P, grid, st);
 }

@@ -71,8 +71,9 @@ def test_pieces_at_the_choice_of_the_form_by_length(io, bits, kg, norm_all, eage
 
 @pytest.mark.parametrize("norm_all", [False, True])
 @pytest.mark.parametrize("io,meta,bits,kg", [("bf16", "f16", 2, 128), ("f32", "f32", 4, 32)])
-@pytest.mark.parametrize("hkv", [42, 43, 64, 65])   # three blocks a sequence: 126 and 129 workgroups; two: 128 and 130
-def test_pieces_where_a_block_becomes_one_workgroup(hkv, io, meta, bits, kg, norm_all):
+@pytest.mark.parametrize("blocks,past", [(3, 0), (3, 1), (2, 0), (2, 1)])   # of the longest piece; past half a workgroup a unit
+def test_pieces_where_a_block_becomes_one_workgroup(blocks, past, io, meta, bits, kg, norm_all):
+    hkv = torch.cuda.get_device_properties(0).multi_processor_count // 2 // blocks + past   # 42, 43, 64, 65 of 256
     pieces = [150, 300, 17, 131, 256]
     total = sum(pieces)
     w = synth.LLAMA8B_32K.replace(batch=1, n_q_heads=hkv, n_kv_heads=hkv, context=total, io_dtype=io, meta_dtype=meta,

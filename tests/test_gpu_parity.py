@@ -388,10 +388,11 @@ def test_decode_every_group_size_combination(kg, vg, bits, gq):
 
 @pytest.mark.parametrize("bits", [2, 4])
 def test_decode_long_stream_one_split_crosses_block_table_chunks(bits):
-    """One split over 300 pages: every wave walks 75 pages, more than the 64 block-table entries
-    it keeps in a register, with a shuffled block table; a full (deferred) residual on top."""
+    """One split over 520 pages: every wave of the eight walks 65 pages, more than the 63 it works
+    off the block-table entries in a register, with a shuffled block table; a full (deferred)
+    residual on top."""
     ob = _ob()
-    n_pages = 300
+    n_pages = 520
     w = synth.LLAMA8B_32K.replace(batch=1, n_q_heads=4, n_kv_heads=1, context=128 * n_pages + 128,
                                   bits=bits)
     k, v = synth.make_kv_batch(w)

@@ -10,7 +10,7 @@
 // for everything in this header.
 //
 // Work decomposition: one workgroup of 256 threads per (sequence, kv head, block of
-// R=128 pending tokens).  A thread owns 8 channels (channel group cg) of token
+// R=128 pending tokens); in small launches one or two of 512 (launch_kg).  A thread owns 8 channels (channel group cg) of token
 // 16*pass+slot for pass = 0..7; the 16 lanes of a DPP row share a token, so
 //   - the 128-point Hadamard butterfly runs 3 stages in registers and 4 stages across the
 //     row.  Lanes are labelled so that the partner of every stage is one DPP control
@@ -23,7 +23,7 @@
 //     the square root and the reciprocal of one token instead of four
 //     (key_transform_4tokens),
 //   - per-channel min/max over tokens reduce over passes (packed fp16 registers), over the
-//     4 token slots of a wave and over the 4 waves (LDS); each channel's Eq. 3-4 parameters
+//     4 token slots of a wave and over the waves (LDS); each channel's Eq. 3-4 parameters
 //     are computed once and handed to the 16 token slots through LDS,
 //   - per-token value min/max reduce over 8 registers and 4|8|16 lanes of the row.
 // Rotated keys are held as packed fp16 (that is what they are), values in their input
@@ -543,7 +543,7 @@ __device__ __forceinline__ void quantize_keys(EncoderLds<META, BITS, KG, NP>& s,
   META* o_knorm = reinterpret_cast<META*>(reinterpret_cast<uint8_t*>(c.k_norms) + pg * g.k_norms_bytes);
 
   // keys: per-channel min/max over the tokens of each group: passes, then the 4 token rows
-  // of the wave, then (through LDS) the 4 waves
+  // of the wave, then (through LDS) the waves
 #pragma unroll
   for (int gk = 0; gk < NGK; ++gk) {
     uint32_t mn[4] = {ku[gk * RPG].x, ku[gk * RPG].y, ku[gk * RPG].z, ku[gk * RPG].w};
@@ -1017,14 +1017,15 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       }
       float x[4][8], nq;
       uint4 nu[4];
+      if (keys) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
-      if (!keys) {
-      } else if (NORM_ALL) {
+        for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
+        if (NORM_ALL) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) nu[j] = key_transform8_given<META>(x[j], sgn, given[j], xf.rotate);
-      } else {
-        key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+          for (int j = 0; j < 4; ++j) nu[j] = key_transform8_given<META>(x[j], sgn, given[j], xf.rotate);
+        } else {
+          key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
+        }
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -1049,13 +1050,11 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
         Raw8<IO> kin, vin;
         if (keys) kin.load(knew + off);
         if (values) vin.load(vnew + off);
-        kin.widen(x);
         uint4 nu;
-        if (!keys) {
-        } else if (NORM_ALL) {
-          nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
-        } else {
-          nu = key_transform8<META>(x, sgn, nn, xf);
+        if (keys) {
+          kin.widen(x);
+          if (NORM_ALL) nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
+          else nu = key_transform8<META>(x, sgn, nn, xf);
         }
         if (i < cnt) {
           const int ds = dst0 + i;

@@ -125,9 +125,9 @@ typedef struct oscar_config {
  * dev_status (may be NULL): a device int32 the kernels set to OSCAR_ERR_CAPACITY
  * when a sequence would need more than max_pages_per_seq pages; that append is
  * dropped for that sequence.
- * tickets (may be NULL): a device int32[1], zeroed once by the caller. With it the last
- * workgroup of oscar_quantize_append to finish also advances seq_lens / res_lens (one
- * launch) and leaves the ticket zero again; without it, and for appends of 128 tokens or more
+ * tickets (may be NULL): a device int32[1], zeroed once by the caller. With it the
+ * workgroup of oscar_quantize_append that draws the last ticket (every workgroup draws one once it
+ * has read the lengths) also advances seq_lens / res_lens (one launch) and leaves the ticket zero again; without it, and for appends of 128 tokens or more
  * whose grid exceeds 1024 workgroups (prefills), the length update is a second, tiny launch. */
 typedef struct oscar_cache {
   oscar_config cfg;
@@ -203,8 +203,10 @@ size_t oscar_decode_workspace_bytes(const oscar_config *cfg, int32_t batch, int3
  * their stored fp16 values (no second rotation). A sequence that receives no token
  * (T == 0 or new_lens[b] == 0) is left untouched under either rule.
  * One launch (plus the length-update launch without cache->tickets or for a large grid); with
- * OSCAR_NORM_ALL_KV_HEADS a launch in front computes the norms of the new tokens that
- * move into pages and parks them in those pages' norm slots. */
+ * OSCAR_NORM_ALL_KV_HEADS a launch in front computes the norms of the new tokens and parks those of
+ * tokens that move into pages in those pages' norm slots, those of the others in res_norm (an old norm
+ * in such a place moves to its page first); up to 16 tokens it computes the former only, and for a
+ * single token under the decode rule it is left out. */
 int oscar_quantize_append(const void *k, const void *v, int32_t T, const int32_t *new_lens,
                           oscar_cache *cache, int32_t max_seq_len_hint, uint32_t flags,
                           void *stream);
@@ -221,6 +223,11 @@ int oscar_quantize_append(const void *k, const void *v, int32_t T, const int32_t
  *   num_splits : split-K factor over the sequence (<= 512), 0 = oscar_decode_auto_splits
  *   workspace  : device scratch of at least oscar_decode_workspace_bytes(...)
  * A sequence with seq_lens[b] == 0 yields zeros.
+ * The same call gives the same bits every time.  Which waves take which pages of a sequence depends on
+ * num_splits and on whether the launch, batch * n_kv_heads * num_splits workgroups, is larger than the
+ * device has compute units, so at one split count the last bits of a sequence's output can differ
+ * between batch sizes on either side of that line.  They do not where num_splits * n_kv_heads alone is past it,
+ * nor, with 4-bit codes, with two splits or more.
  * Two launches (split-K partial pass, reduce pass); with a single split the matrix-core kernel
  * writes `out` itself and the reduce launch is left out (same bits: the same sums, divided the
  * same way; the workspace is still required and may then stay untouched).

@@ -639,7 +639,14 @@ __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, in
 // 1 x 4000 12.5 / 11.3, 1 x 32000 13.2 / 12.7, 16 x 1000 19.7 / 15.7; seven query heads a kv head, 1 x 1000
 // 23.0 / 18.3, 1 x 16000 16.1 / 14.8; fp32 metadata 1 x 1000 20.9 / 17.4; INT4 1 x 1000 19.1 / 16.5.  At INT4 it
 // is one split only (the window is what gains: with several splits, warm, 1 x 8000 12.8 / 13.6, 1 x 16000
-// 14.7 / 17.5), with fp32 metadata not at all.
+// 14.7 / 17.5), with fp32 metadata not at all.  With an empty window the attention alone loses there (1 x 1024
+// 9.7 / 10.4, with 104 tokens in it 17.1 / 14.2, with 116 of 500 15.8 / 12.3; the step 11.8 / 11.6, 19.0 / 16.5 and
+// 17.7 / 14.4), and the window is as often full as empty.
+// The step's two-slot forms keep 36 .. 120 bytes a lane in scratch, those of G_k = 32 most, as they do with four
+// waves; eight are faster all the same (warm, 28 heads on 4, 1 x 1016: G_k = 32 with G_v = 128 20.9 / 17.9, with
+// G_v = 64 21.4 / 18.0, G_k = 128 with G_v = 32 19.6 / 16.2).
+// At one split count the two forms deal a sequence's pages to different waves: the last bits of its output
+// differ between launches on either side of the line.
 // Built where two workgroups of four fit a CU in both kernels (the step's and the attention alone
 // give the same bits, so they split alike).
 __host__ __device__ constexpr bool eight_waves_built(int bits, int hp, int ngk, int ngv, bool m32) {
@@ -830,7 +837,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   }
 #endif
   // Residual slice of this split: rs tokens per split (a multiple of 16), handed out from
-  // the last split backwards; inside the workgroup, wave w takes tokens 16*pass + 4*w + j.
+  // the last split backwards; inside the workgroup, wave w takes tokens 4*NW*pass + 4*w + j.
   const int rs = 16 * ((((r + 15) >> 4) + P.num_splits - 1) / P.num_splits);
   const int t_lo = min(r, (P.num_splits - 1 - split) * rs);
   const int rcount = min(r, t_lo + rs) - t_lo;
@@ -963,7 +970,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     // wave wait for the loads, and for the whole first page behind them, before the query rotation)
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rt_first[i].nrm));
-    // one pass: the wave's four tokens of slots p0 .. p0 + 15 of the slice, from registers.  Every
+    // one pass: the wave's four tokens of slots p0 .. p0 + 4*NW - 1 of the slice, from registers.  Every
     // fused multiply-add is written out: left to the compiler, the step form and the attention alone
     // fused differently and their outputs differed in the last bit.
     auto pass = [&](const ResTok<M32> (&rt)[4], int p0) {
@@ -1007,7 +1014,7 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     };
     // Two register sets take turns: the next pass's tokens are on their way while a pass works on
     // its own.  (With one set every pass began by waiting for its loads.  A launch with one split
-    // walks the whole window, up to eight passes, in every workgroup: batch 64 x 8K, attention
+    // walks the whole window, up to eight passes (four waves), in every workgroup: batch 64 x 8K, attention
     // alone, 127 residual tokens 73.4 -> 68.4 us against 60.3 with none; batch 1 x 1K, 104 residual
     // tokens 14.7 -> 13.9.  A third set does not fit the registers of any variant.)
     ResTok<M32> rt_other[4];

@@ -65,3 +65,20 @@ def test_bits_of_the_two_calls_in_the_four_wave_form(io, bits, kg, vg, gq, split
     w = synth.LLAMA8B_32K.replace(batch=len(starts), n_q_heads=gq, n_kv_heads=1, context=300 + 4, io_dtype=io,
                                   bits=bits, k_group=kg, v_group=vg)
     _run(w, starts, 3, splits, 4)
+
+
+@pytest.mark.parametrize("bits,hkv,splits", [(4, 2, 2), (4, 1, 5), (2, 4, 0)])   # 0: past the unit count by itself
+def test_bits_of_a_sequence_where_its_batch_does_not_choose_the_form(bits, hkv, splits):
+    import torch
+    ob = _ob()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    splits = splits or cus // hkv + 1
+    w = synth.LLAMA8B_32K.replace(batch=1, n_q_heads=4 * hkv, n_kv_heads=hkv, context=128 * 9 + 50, bits=bits)
+    k, v = synth.make_kv_batch(w)
+    kd, vd, q = to_dev(k, w.io_dtype), to_dev(v, w.io_dtype), to_dev(synth.make_q(w), w.io_dtype)
+    outs = []
+    for batch in (1, cus // (hkv * min(splits, cus)) + 2):
+        c = ob.Cache(ob.Config(w.n_q_heads, hkv, bits=bits), batch, 10)
+        ob.quantize_append(c, kd.repeat(batch, 1, 1, 1), vd.repeat(batch, 1, 1, 1), eager=True, max_seq_len_hint=0)
+        outs.append(ob.decode_attn(c, q.repeat(batch, 1, 1), max_seq_len_hint=w.context, num_splits=splits))
+    assert torch.equal(outs[0].expand_as(outs[1]), outs[1])

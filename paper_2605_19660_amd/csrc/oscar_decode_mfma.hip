@@ -642,8 +642,8 @@ __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, in
 // 14.7 / 17.5), with fp32 metadata not at all.  With an empty window the attention alone loses there (1 x 1024
 // 9.7 / 10.4, with 104 tokens in it 17.1 / 14.2, with 116 of 500 15.8 / 12.3; the step 11.8 / 11.6, 19.0 / 16.5 and
 // 17.7 / 14.4), and the window is as often full as empty.
-// The step's two-slot forms keep 36 .. 120 bytes a lane in scratch, those of G_k = 32 most, as they do with four
-// waves; eight are faster all the same (warm, 28 heads on 4, 1 x 1016: G_k = 32 with G_v = 128 20.9 / 17.9, with
+// The step's two-slot forms, and INT4 with G_k = 128 and G_v = 32, keep 36 .. 120 bytes a lane in scratch, those of
+// G_k = 32 most, as they do with four waves; eight are faster all the same (warm, 28 heads on 4, 1 x 1016: G_k = 32 with G_v = 128 20.9 / 17.9, with
 // G_v = 64 21.4 / 18.0, G_k = 128 with G_v = 32 19.6 / 16.2).
 // At one split count the two forms deal a sequence's pages to different waves: the last bits of its output
 // differ between launches on either side of the line.

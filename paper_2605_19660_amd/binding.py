@@ -154,14 +154,23 @@ class Config:
                        self.norm_scope, self.rotation, self.scale_mode)
 
 
+_DTYPES: dict = {}   # both ways, filled at the first use (torch is imported late)
+
+
+def _dtypes() -> dict:
+    if not _DTYPES:
+        import torch
+        for code, dt in ((F32, torch.float32), (BF16, torch.bfloat16), (F16, torch.float16)):
+            _DTYPES[code], _DTYPES[dt] = dt, code
+    return _DTYPES
+
+
 def torch_dtype(code: int):
-    import torch
-    return {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16}[code]
+    return (_DTYPES or _dtypes())[code]
 
 
 def dtype_code(dt) -> int:
-    import torch
-    return {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16}[dt]
+    return (_DTYPES or _dtypes())[dt]
 
 
 def cache_sizes(cfg: Config, batch: int, num_pages: int, max_pages_per_seq: int) -> CPoolSizes:
@@ -172,10 +181,27 @@ def cache_sizes(cfg: Config, batch: int, num_pages: int, max_pages_per_seq: int)
     return out
 
 
-def _stream_ptr(stream):
+def _current_stream() -> int:
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
+
+
+_current_raw_stream = None
+
+
+def _stream_ptr(stream) -> int:
+    """The stream's handle; by default the current one of the current device.  torch.cuda.current_stream()
+    makes a Stream object of it first, which is most of what a small call's marshalling cost (a decode step
+    8.8 us on the host, an append 9.5); the handle alone is asked for where this torch has the call."""
+    global _current_raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        import torch
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        torch.cuda.current_stream()   # (initialises torch's side of the device, once)
+        _current_raw_stream = _current_stream if raw is None or device is None else lambda: raw(device())
+    return _current_raw_stream()
 
 
 class Cache:
@@ -285,11 +311,12 @@ class MultiLayerCache:
 def quantize_append(cache: Cache, k, v, new_lens=None, eager: bool = False,
                     max_seq_len_hint: int = -1, stream=None):
     """oscar_quantize_append: k, v device tensors [batch, T, n_kv_heads, d] of the io dtype."""
+    cfg, shape = cache.cfg, k.shape
     assert k.is_cuda and v.is_cuda and k.is_contiguous() and v.is_contiguous()
-    assert k.shape == v.shape and k.dtype == v.dtype == torch_dtype(cache.cfg.io_dtype)
-    assert k.shape[0] == cache.batch and k.shape[2] == cache.cfg.n_kv_heads and k.shape[3] == cache.cfg.head_dim
+    assert shape == v.shape and k.dtype == v.dtype == torch_dtype(cfg.io_dtype)
+    assert shape[0] == cache.batch and shape[2] == cfg.n_kv_heads and shape[3] == cfg.head_dim
     nl = None if new_lens is None else new_lens.data_ptr()
-    rc = lib().oscar_quantize_append(k.data_ptr(), v.data_ptr(), k.shape[1], nl, C.byref(cache.c),
+    rc = lib().oscar_quantize_append(k.data_ptr(), v.data_ptr(), shape[1], nl, C.byref(cache.c),
                                      max_seq_len_hint, APPEND_EAGER if eager else 0,
                                      _stream_ptr(stream))
     _check(rc, "oscar_quantize_append")

@@ -21,6 +21,8 @@ SOURCES = {
     "oscar_quantize.hip": ["-ffp-contract=off"],
     "oscar_quantize_allheads.hip": ["-ffp-contract=off"],
     "oscar_quantize_switched.hip": ["-ffp-contract=off"],
+    "oscar_quantize_sides.hip": ["-ffp-contract=off"],
+    "oscar_quantize_sides_allheads.hip": ["-ffp-contract=off"],
     "oscar_decode.hip": [],
     "oscar_decode_mfma.hip": [],
     "oscar_decode_mfma_zpmin.hip": [],

@@ -38,7 +38,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ("oscar_decode_mfma.hip", "oscar_decode_mfma_zpmin.hip", "oscar_decode_mfma_meta32.hip",
            "oscar_decode_mfma_meta32_zpmin.hip", "oscar_decode_step.hip", "oscar_decode_step_zpmin.hip")
 # the encoders and the stand-alone rotations
-DPP_SOURCES = SOURCES + ("oscar_quantize.hip", "oscar_quantize_allheads.hip", "oscar_quantize_switched.hip")
+DPP_SOURCES = SOURCES + ("oscar_quantize.hip", "oscar_quantize_allheads.hip", "oscar_quantize_switched.hip",
+                         "oscar_quantize_sides.hip", "oscar_quantize_sides_allheads.hip")
 
 
 def _regs(tok: str) -> set[int]:

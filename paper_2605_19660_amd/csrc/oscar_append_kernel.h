@@ -10,7 +10,7 @@
 // for everything in this header.
 //
 // Work decomposition: one workgroup of 256 threads per (sequence, kv head, block of
-// R=128 pending tokens); in small launches one or two of 512 (launch_kg).  A thread owns 8 channels (channel group cg) of token
+// R=128 pending tokens); in small launches one or two of 512 (launch_kg, append_in_sides).  A thread owns 8 channels (channel group cg) of token
 // 16*pass+slot for pass = 0..7; the 16 lanes of a DPP row share a token, so
 //   - the 128-point Hadamard butterfly runs 3 stages in registers and 4 stages across the
 //     row.  Lanes are labelled so that the partner of every stage is one DPP control
@@ -61,6 +61,9 @@ constexpr int XF_PUBLISHED = 0, XF_SWITCHED = 1, XF_ALL_HEADS = 2, XF_ALL_HEADS_
 constexpr int kFewTokens = 16;   // one pass of the 256-thread form's token rows
 int oscar_launch_append_switched(const AppendParams& P, dim3 grid, hipStream_t st);
 int oscar_launch_append_all_heads(const AppendParams& P, dim3 grid, hipStream_t st);
+// The form for the smallest launches (append_in_sides), XF_PUBLISHED and XF_ALL_HEADS; grid as of the others.
+int oscar_launch_append_sides(const AppendParams& P, bool all_heads, dim3 grid, hipStream_t st);
+int oscar_launch_append_sides_all_heads(const AppendParams& P, dim3 grid, hipStream_t st);
 
 // (for the one user that is not compiled with -ffp-contract=off, the fused decode step; it switches
 // contraction back on behind this header)
@@ -77,6 +80,15 @@ __device__ __forceinline__ uint4 load_once(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// the same through a buffer resource: zeros past its end
+__device__ __forceinline__ uint4 load_once(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 2));
+}
+
+__device__ __forceinline__ uint4 operator|(const uint4& x, const uint4& y) {
+  return make_uint4(x.x | y.x, x.y | y.y, x.z | y.z, x.w | y.w);
+}
+
 // Eight consecutive elements of the caller's type, held raw (packed) in registers.
 template <typename IO> struct Raw8;
 template <> struct Raw8<float> {
@@ -84,6 +96,14 @@ template <> struct Raw8<float> {
   __device__ __forceinline__ void load(const float* p) {
     a = load_once(p);
     b = load_once(p + 4);
+  }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+    a = load_once(r, off, soff);
+    b = load_once(r, off + 16, soff);
+  }
+  __device__ __forceinline__ void merge(const Raw8& o) {   // (of two loads of which one is zeros)
+    a = a | o.a;
+    b = b | o.b;
   }
   __device__ __forceinline__ void load_halves(const __half* p) {   // 8 fp16 values, kept in a
     a = *reinterpret_cast<const uint4*>(p);
@@ -111,6 +131,8 @@ __device__ __forceinline__ void widen_halves(const uint4& r, float (&x)[8]) {
 template <> struct Raw8<__half> {
   uint4 a;
   __device__ __forceinline__ void load(const __half* p) { a = load_once(p); }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int off, int soff) { a = load_once(r, off, soff); }
+  __device__ __forceinline__ void merge(const Raw8& o) { a = a | o.a; }
   __device__ __forceinline__ void load_halves(const __half* p) { load(p); }
   __device__ __forceinline__ void store(__half* p) const { *reinterpret_cast<uint4*>(p) = a; }
   __device__ __forceinline__ void widen(float (&x)[8]) const { widen_halves(a, x); }
@@ -118,6 +140,8 @@ template <> struct Raw8<__half> {
 template <> struct Raw8<__hip_bfloat16> {
   uint4 a;
   __device__ __forceinline__ void load(const __hip_bfloat16* p) { a = load_once(p); }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int off, int soff) { a = load_once(r, off, soff); }
+  __device__ __forceinline__ void merge(const Raw8& o) { a = a | o.a; }
   __device__ __forceinline__ void load_halves(const __half* p) {
     a = *reinterpret_cast<const uint4*>(p);
   }
@@ -133,6 +157,36 @@ template <> struct Raw8<__hip_bfloat16> {
     }
   }
 };
+
+// (the metadata type's counterpart of load_once through a resource: one element)
+template <typename META> __device__ __forceinline__ META load_meta_elem(__amdgpu_buffer_rsrc_t r, int elem) {
+  if constexpr (sizeof(META) == 2)
+    return __builtin_bit_cast(META, (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, elem * 2, 0, 0));
+  else
+    return __builtin_bit_cast(META, __builtin_amdgcn_raw_buffer_load_b32(r, elem * 4, 0, 0));
+}
+// `count` tokens of one (sequence, kv head) in K or V from token t0 on, as a buffer resource; void without any
+template <typename IO>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t token_rows(const AppendParams& P, const void* side, int b, int kvh,
+                                                             int t0, int count) {
+  const int Hkv = P.c.cfg.n_kv_heads;
+  const size_t at = (((size_t)b * P.T + (size_t)t0) * Hkv + kvh) * D;
+  const int bytes = count > 0 ? ((count - 1) * Hkv + 1) * D * (int)sizeof(IO) : 0;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<IO*>(reinterpret_cast<const IO*>(side) + at), 0, bytes, 0x00020000);
+}
+// The same for the new tokens of a block.  Block 0 can begin with tokens of the old window: the resource then
+// starts at the first new one, and the old ones' offsets (block_row_offset) wrap and lie past its end: zeros.
+template <typename IO>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rows(const AppendParams& P, const void* side, int b, int kvh,
+                                                             int blk, int r0, bool on) {
+  const int first = blk * R - r0, t0 = first > 0 ? first : 0;
+  return token_rows<IO>(P, side, b, kvh, t0, on ? first + R - t0 : 0);
+}
+template <typename IO>
+__device__ __forceinline__ int block_row_offset(const AppendParams& P, int blk, int r0, int tok, int cg) {
+  const int first = blk * R - r0;
+  return (tok + (first < 0 ? first : 0)) * P.c.cfg.n_kv_heads * D * (int)sizeof(IO) + cg * 8 * (int)sizeof(IO);
+}
 
 // Keeps a value in a VGPR across an empty asm: stops the compiler from folding the
 // fp32 multiply and the fp16 conversion below into one mixed-precision instruction that
@@ -437,11 +491,15 @@ struct SeqPlan {
   bool ok;
 };
 
+// (SCALAR: b is uniform and the loads are scalar ones whatever stands in front of them)
+typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
+template <bool SCALAR = false>
 __device__ __forceinline__ SeqPlan plan_sequence(const AppendParams& P, int b) {
   SeqPlan s;
-  const int seq_len = P.c.seq_lens[b];
-  s.r0 = P.c.res_lens[b];
-  int n = P.new_lens ? P.new_lens[b] : P.T;
+  const int seq_len = SCALAR ? ((ScalarInts)P.c.seq_lens)[b] : P.c.seq_lens[b];
+  s.r0 = SCALAR ? ((ScalarInts)P.c.res_lens)[b] : P.c.res_lens[b];
+  int n = P.T;
+  if (P.new_lens) n = SCALAR ? ((ScalarInts)P.new_lens)[b] : P.new_lens[b];
   n = n < 0 ? 0 : (n > P.T ? P.T : n);
   s.n = n;
   s.packed_pages = (seq_len - s.r0) / R;
@@ -453,6 +511,18 @@ __device__ __forceinline__ SeqPlan plan_sequence(const AppendParams& P, int b) {
   s.tail_len = pending - s.nq * R;
   s.ok = (s.packed_pages + s.nq) <= P.c.max_pages_per_seq;
   return s;
+}
+
+// the lengths behind the call, by `threads` threads of which this is number `first`
+__device__ __forceinline__ void advance_all(const AppendParams& P, int first, int threads) {
+  for (int bb = first; bb < P.c.batch; bb += threads) {
+    const SeqPlan q = plan_sequence(P, bb);
+    if (q.n > 0 && q.ok) {
+      P.c.seq_lens[bb] += q.n;
+      P.c.res_lens[bb] = q.tail_len;
+    }
+  }
+  if (first == 0) P.c.tickets[0] = 0;
 }
 
 template <int BITS> __device__ __forceinline__ constexpr float place_value(int i) {
@@ -793,16 +863,14 @@ __device__ __forceinline__ void quantize_values(EncoderLds<META, BITS, KG, NP>& 
 // launch_kg): there a workgroup's own latency is the time, and it is issue-bound at one wave a SIMD.
 // A thread of the 512 takes every second pass: thread group 0 the even ones, group 1 the odd ones,
 // which are the two halves of a packed value piece.
-// SPLIT: two workgroups a block, one for the keys and one for the values (they touch different arrays).
-template <typename IO, typename META, int BITS, int KG, int XF, int NP, bool SPLIT>
+template <typename IO, typename META, int BITS, int KG, int XF, int NP>
 __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeof(IO) == 4 ? (XF >= XF_ALL_HEADS ? 2 : 3) : 4))) void oscar_append_kernel(AppendParams P) {
   constexpr bool NORM_ALL = XF >= XF_ALL_HEADS, norms_ready = XF == XF_ALL_HEADS;
   constexpr int NT = 2048 / NP, ROWS = NT / 16;   // threads, token rows
   __shared__ EncoderLds<META, BITS, KG, NP> s;
 
   // kv head fastest: the workgroups that share a token block's rows in memory run together
-  const int b = SPLIT ? blockIdx.z >> 1 : blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
-  const bool keys = !SPLIT || (blockIdx.z & 1) == 0, values = !SPLIT || (blockIdx.z & 1) != 0;
+  const int b = blockIdx.z, kvh = blockIdx.x, blk = blockIdx.y;
   const int tid = threadIdx.x;
   const int slot = NP == 8 ? tid >> 4 : (tid >> 4) & 15;  // token of a pass
   const int grp = NP == 8 ? 0 : tid >> 8;               // thread group
@@ -818,23 +886,13 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
 
   const SeqPlan sp = plan_sequence(P, b);
   int my_ticket = -1;
-  bool drawn = false, advanced = false;
+  bool drawn = false;
   // (small launches) the ticket is drawn in the middle of the workgroup's work and answered later in it
   constexpr bool EARLY_TICKET = NP == 4;
-  auto advance_all = [&](int first, int threads) {
-    for (int bb = first; bb < P.c.batch; bb += threads) {
-      const SeqPlan q = plan_sequence(P, bb);
-      if (q.n > 0 && q.ok) {
-        P.c.seq_lens[bb] += q.n;
-        P.c.res_lens[bb] = q.tail_len;
-      }
-    }
-    if (first == 0) P.c.tickets[0] = 0;
-  };
   // (worked out where it is asked for: held from here on, the product costs the prefill forms registers)
   auto is_last = [&](int ticket) { return ticket == (int)(gridDim.x * gridDim.y * gridDim.z) - 1; };
   auto advance_if_last = [&]() {
-    if (P.c.tickets && tid < 64 && is_last(ticket_answer(my_ticket))) advance_all(tid, 64);
+    if (P.c.tickets && tid < 64 && is_last(ticket_answer(my_ticket))) advance_all(P, tid, 64);
   };
   do {  // one pass; "break" = this workgroup has nothing (more) to do
   if (sp.n <= 0) break;
@@ -882,10 +940,8 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     const IO* kp = knew + (tok0 * Hkv + kvh) * D + cg * 8;
     const IO* vp = vnew + (tok0 * Hkv + kvh) * D + cg * 8;
     const size_t pstride = (size_t)(16 * (8 / NP)) * Hkv * D;
-    if (keys) {
 #pragma unroll
-      for (int p = 0; p < NP; ++p) kraw[p].load(kp + p * pstride);
-    }
+    for (int p = 0; p < NP; ++p) kraw[p].load(kp + p * pstride);
     // The values are not needed before the key codes are done: their loads go out behind the
     // first half of the key transform (held there by the fences), which keeps their 32
     // registers free while the transform is at its widest and spreads the workgroup's requests.
@@ -896,9 +952,8 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       for (int p = 0; p < NP; ++p) vraw[p].load(vp + p * pstride);
       __builtin_amdgcn_sched_barrier(0);
     };
-    if (NP == 4 && values) load_values();
-    if (!keys) {
-    } else if (NORM_ALL) {
+    if (NP == 4) load_values();
+    if (NORM_ALL) {
 #pragma unroll
       for (int p = 0; p < NP; ++p) nrm[p] = to_f32<META>(pre_norm[tok_meta_pos(pass(p) * 16 + slot)]);
 #pragma unroll
@@ -935,24 +990,21 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
     for (int p = 0; p < NP; ++p) {
       const int pi = blk * R + pass(p) * 16 + slot;  // index among pending tokens
       if (pi < sp.r0) {
-        if (keys) {
-          kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
-          // (a place that the new tail takes holds the tail's norm by now, and the page the old one)
-          nrm[p] = to_f32<META>(norms_ready && pi < sp.tail_len ? pre_norm[tok_meta_pos(pi)] : res_norm[pi]);
-        }
-        if (values) vraw[p].load(res_v + (size_t)pi * D + cg * 8);
+        kraw[p].load_halves(res_k + (size_t)pi * D + cg * 8);
+        // (a place that the new tail takes holds the tail's norm by now, and the page the old one)
+        nrm[p] = to_f32<META>(norms_ready && pi < sp.tail_len ? pre_norm[tok_meta_pos(pi)] : res_norm[pi]);
+        vraw[p].load(res_v + (size_t)pi * D + cg * 8);
       } else {
         const size_t ti = (size_t)(pi - sp.r0);
         const size_t off = (((size_t)b * P.T + ti) * Hkv + kvh) * D + cg * 8;
-        if (keys) kraw[p].load(knew + off);
-        if (values) vraw[p].load(vnew + off);
+        kraw[p].load(knew + off);
+        vraw[p].load(vnew + off);
         nrm[p] = 0.0f;
       }
     }
     // the branch above is uniform per 16-lane token row; every row runs the transform (its
     // result is dropped for tokens that came from the residual, which are K_u already)
-    if (!keys) {
-    } else if (NP == 4 && XF == XF_PUBLISHED) {
+    if (NP == 4 && XF == XF_PUBLISHED) {
       float x[4][8], nq;
       uint4 nu[4];
 #pragma unroll
@@ -1011,30 +1063,28 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row, ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
-        if (keys) kin4[j].load(knew + off);
-        if (values) vin4[j].load(vnew + off);
-        if (NORM_ALL && keys) given[j] = to_f32<META>(res_norm[dst0 + ic]);
+        kin4[j].load(knew + off);
+        vin4[j].load(vnew + off);
+        if (NORM_ALL) given[j] = to_f32<META>(res_norm[dst0 + ic]);
       }
       float x[4][8], nq;
       uint4 nu[4];
-      if (keys) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
-        if (NORM_ALL) {
+      for (int j = 0; j < 4; ++j) kin4[j].widen(x[j]);
+      if (NORM_ALL) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) nu[j] = key_transform8_given<META>(x[j], sgn, given[j], xf.rotate);
-        } else {
-          key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
-        }
+        for (int j = 0; j < 4; ++j) nu[j] = key_transform8_given<META>(x[j], sgn, given[j], xf.rotate);
+      } else {
+        key_transform_4tokens<META>(x, sgn, tid & 3, nq, nu);
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = j * ROWS + row;
         if (i < cnt) {
           const int ds = dst0 + i;
-          if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
-          if (values) vin4[j].store(res_v + (size_t)ds * D + cg * 8);
-          if (!NORM_ALL && keys && (tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
+          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu[j];
+          vin4[j].store(res_v + (size_t)ds * D + cg * 8);
+          if (!NORM_ALL && (tid & 15) == j) res_norm[ds] = from_f32<META>(nq);   // lane j of the first quad has norm j
         }
       }
     } else {
@@ -1043,24 +1093,22 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
         const int ic = i < cnt ? i : cnt - 1;
         const size_t off = (((size_t)b * P.T + (size_t)(src0 + ic)) * Hkv + kvh) * D + cg * 8;
         float x[8], nn;
-        if (NORM_ALL && keys) {   // (worked out in front of the loads below: registers)
+        if (NORM_ALL) {   // (worked out in front of the loads below: registers)
           if (norms_ready) nn = to_f32<META>(res_norm[dst0 + ic]);
           else nn = token_norm_all_heads<IO, META>(knew + off - (size_t)kvh * D, Hkv, sgn, xf.rotate);
         }
         Raw8<IO> kin, vin;
-        if (keys) kin.load(knew + off);
-        if (values) vin.load(vnew + off);
+        kin.load(knew + off);
+        vin.load(vnew + off);
         uint4 nu;
-        if (keys) {
-          kin.widen(x);
-          if (NORM_ALL) nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
-          else nu = key_transform8<META>(x, sgn, nn, xf);
-        }
+        kin.widen(x);
+        if (NORM_ALL) nu = key_transform8_given<META>(x, sgn, nn, xf.rotate);
+        else nu = key_transform8<META>(x, sgn, nn, xf);
         if (i < cnt) {
           const int ds = dst0 + i;
-          if (keys) *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
-          if (values) vin.store(res_v + (size_t)ds * D + cg * 8);
-          if (keys && cg == 0 && !norms_ready) res_norm[ds] = from_f32<META>(nn);
+          *reinterpret_cast<uint4*>(res_k + (size_t)ds * D + cg * 8) = nu;
+          vin.store(res_v + (size_t)ds * D + cg * 8);
+          if (cg == 0 && !norms_ready) res_norm[ds] = from_f32<META>(nn);
         }
       }
     }
@@ -1074,10 +1122,8 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
   if (!do_block) break;
 
   const size_t pg = (size_t)phys * Hkv + kvh;
-  if (keys) quantize_keys<META, BITS, KG, NP>(s, ku, batched_norms, nrm, nrm_q, P.c, P.g, pg, zp_min, tid, cg);
-  if (SPLIT) advance_if_last();
-  if (values) quantize_values<META, BITS, KG, NP>(s, vraw, P.c, P.g, pg, zp_min, tid, cg);
-  advanced = SPLIT;
+  quantize_keys<META, BITS, KG, NP>(s, ku, batched_norms, nrm, nrm_q, P.c, P.g, pg, zp_min, tid, cg);
+  quantize_values<META, BITS, KG, NP>(s, vraw, P.c, P.g, pg, zp_min, tid, cg);
   } while (false);
 
   // ---- length update, folded in: the workgroup that draws the last ticket advances the lengths of all
@@ -1090,17 +1136,16 @@ __global__ __launch_bounds__(2048 / NP) __attribute__((amdgpu_waves_per_eu(sizeo
       __syncthreads();
       my_ticket = draw_ticket(P.c.tickets, P.c.tickets != nullptr, tid);
     }
-    if (!advanced) advance_if_last();
+    advance_if_last();
   } else if (P.c.tickets) {
     __shared__ int s_last;
     __syncthreads();
     if (tid == 0) s_last = is_last(atomicAdd(&P.c.tickets[0], 1)) ? 1 : 0;
     __syncthreads();
-    if (s_last) advance_all(tid, NT);
+    if (s_last) advance_all(P, tid, NT);
   }
 }
 
-template <typename META>
 __global__ void oscar_update_lens_kernel(AppendParams P) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= P.c.batch) return;
@@ -1118,13 +1163,21 @@ __global__ void oscar_update_lens_kernel(AppendParams P) {
 // 22.7 / 28.4; fp32, 2048 tokens (272) 13.1 / 9.8, 3072 (400) 14.3 / 19.4.
 template <typename IO> constexpr size_t small_grid_workgroups_per_cu() { return sizeof(IO) == 4 ? 1 : 2; }
 
-template <typename IO, typename META, int BITS, int XF, int NP, bool SPLIT>
+// Up to half a workgroup a CU a block's two sides are two workgroups, each with its share of the tail
+// (oscar_append_sides.h): one workgroup's chain of loads, transform, key codes and value codes is the launch's
+// time there (whole call in us, one / two workgroups a block, bf16 INT2, 8 heads: 1 x 128 tokens 11.8 / 8.9 with
+// INT4, 1 x 512 10.4 / 7.5 with fp32, pieces of 2 x 500 10.3 / 9.4; past it, 8 x 500 in 512 workgroups, 13.1 / 14.6).
+inline bool append_in_sides(const AppendParams& P, dim3 grid) {
+  return P.T > kFewTokens && 2 * (size_t)grid.x * grid.y * grid.z <= (size_t)oscar_compute_units();
+}
+
+template <typename IO, typename META, int BITS, int XF, int NP>
 int launch_np(const AppendParams& P, dim3 grid, hipStream_t st) {
   const dim3 block(2048 / NP);
   switch (P.g.k_group) {
-    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF, NP, SPLIT>), grid, block, 0, st, P); break;
-    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF, NP, SPLIT>), grid, block, 0, st, P); break;
-    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF, NP, SPLIT>), grid, block, 0, st, P); break;
+    case 32: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 32, XF, NP>), grid, block, 0, st, P); break;
+    case 64: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 64, XF, NP>), grid, block, 0, st, P); break;
+    case 128: hipLaunchKernelGGL((oscar_append_kernel<IO, META, BITS, 128, XF, NP>), grid, block, 0, st, P); break;
     default: return OSCAR_ERR_UNSUPPORTED;
   }
   return OSCAR_OK;
@@ -1138,16 +1191,10 @@ int launch_kg(const AppendParams& P, dim3 grid, hipStream_t st) {
     // idle in the other one (us, 256 / 512 threads, bf16, 8 heads: 2 tokens 3.5 / 3.7, with the all-heads
     // norm 6.5 / 7.7, 16 tokens 7.3 / 8.4; 17 tokens, a second pass, 5.1 / 4.6 and 9.8 / 9.1).
     const size_t n = (size_t)grid.x * grid.y * grid.z, n_cu = (size_t)oscar_compute_units();
-    // Up to half a workgroup a CU a block's two sides are two workgroups, each with its share of the tail: one
-    // workgroup's chain of loads, transform, key codes and value codes is the launch's time there (whole
-    // call in us, one / two workgroups a block, bf16 INT2, 8 heads: 1 x 128 tokens 11.8 / 8.9 with INT4, 1 x 512
-    // 10.4 / 7.5 with fp32, pieces of 2 x 500 10.3 / 9.4; past it, 8 x 500 in 512 workgroups, 13.1 / 14.6).
-    if (P.T > kFewTokens && 2 * n <= n_cu)
-      return launch_np<IO, META, BITS, XF, 4, true>(P, dim3(grid.x, grid.y, 2 * grid.z), st);
     if (P.T > kFewTokens && n <= small_grid_workgroups_per_cu<IO>() * n_cu)
-      return launch_np<IO, META, BITS, XF, 4, false>(P, grid, st);
+      return launch_np<IO, META, BITS, XF, 4>(P, grid, st);
   }
-  return launch_np<IO, META, BITS, XF, 8, false>(P, grid, st);
+  return launch_np<IO, META, BITS, XF, 8>(P, grid, st);
 }
 
 template <typename IO, typename META, int XF>
@@ -1159,16 +1206,12 @@ int launch_bits(const AppendParams& P, dim3 grid, hipStream_t st) {
 
 template <typename IO, int XF>
 int launch_meta(const AppendParams& P, dim3 grid, hipStream_t st) {
-  int rc;
-  if (P.c.cfg.meta_dtype == OSCAR_F16) {
-    rc = launch_bits<IO, __half, XF>(P, grid, st);
-    if (rc == OSCAR_OK && !P.c.tickets)
-      hipLaunchKernelGGL((oscar_update_lens_kernel<__half>), dim3((P.c.batch + 63) / 64), dim3(64), 0, st, P);
-  } else {
-    rc = launch_bits<IO, float, XF>(P, grid, st);
-    if (rc == OSCAR_OK && !P.c.tickets)
-      hipLaunchKernelGGL((oscar_update_lens_kernel<float>), dim3((P.c.batch + 63) / 64), dim3(64), 0, st, P);
-  }
+  constexpr bool HAS_SIDES = XF == XF_PUBLISHED || XF == XF_ALL_HEADS;
+  const int rc = HAS_SIDES && append_in_sides(P, grid) ? oscar_launch_append_sides(P, XF == XF_ALL_HEADS, grid, st)
+                 : P.c.cfg.meta_dtype == OSCAR_F16     ? launch_bits<IO, __half, XF>(P, grid, st)
+                                                       : launch_bits<IO, float, XF>(P, grid, st);
+  if (rc == OSCAR_OK && !P.c.tickets)
+    hipLaunchKernelGGL(oscar_update_lens_kernel, dim3((P.c.batch + 63) / 64), dim3(64), 0, st, P);
   return rc;
 }
 

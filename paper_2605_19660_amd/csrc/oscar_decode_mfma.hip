@@ -38,6 +38,8 @@
 
 #include "oscar_decode_common.h"
 
+#include <type_traits>
+
 // This file is compiled six times: as it stands for the integer zero-point of Eq. 3-4, and through
 // oscar_decode_mfma_zpmin.hip with OSCAR_MFMA_ZPMIN = 1 for the float zero-point form; the
 // zero-point form is a compile-time constant of the kernel (no branches in the page loop), and
@@ -374,6 +376,29 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, int off, u
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, (int)soff, 2));
 }
 
+// 16 bytes a lane from memory straight into LDS, lane after lane from byte `dst` of LDS (uniform) on.  In asm, as
+// are the reads of what it brings (read_staged): the compiler would wait for every load in flight in front of each
+// LDS access that might touch it, the operand tables' in the page loop included.  It does not count this one, so
+// its own waits can only come out longer.  (The wait states: the descriptor may come from vector instructions, and
+// m0 is read a slot after it was written.)
+__device__ __forceinline__ u32x4 lds_load_rsrc(const void* base, uint32_t bytes) {
+  const unsigned long long p = reinterpret_cast<unsigned long long>(base);
+  return (u32x4){(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+__device__ __forceinline__ void load_to_lds(const u32x4& rsrc, uint32_t dst, int off) {
+  asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+               :: "s"(dst), "v"(off), "s"(rsrc) : "memory", "m0");
+}
+// Four times 16 bytes of LDS, 256 bytes apart, and the wait for them.
+__device__ __forceinline__ void read_staged(uint32_t at, u32x4 (&x)[4]) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:256\n\tds_read_b128 %2, %4 offset:512\n\t"
+               "ds_read_b128 %3, %4 offset:768\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]) : "v"(at) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_byte(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+
 // Eight consecutive metadata values (element `elem` of the resource onwards), held as stored.
 template <bool M32> struct Meta8;
 template <> struct Meta8<false> {
@@ -604,18 +629,11 @@ template <bool M32> struct ResRsrc {
 };
 
 // One residual token's share for a lane: 8 channels (channel group cg) of K_u (fp16) and of
-// V (caller's dtype), and the token norm, held raw until the query rotation is done.
-// `tok` is the token's slot in the window; slot R is past its end and reads as zeros.
+// V (caller's dtype), and the token norm, as stored.
 template <bool M32> struct ResTok {
   uint4 k;
   Raw8rt v;
   uint32_t nrm;
-  __device__ __forceinline__ void load(const ResRsrc<M32>& r, int tok, int cg) {
-    k = buf_load16(r.k, (tok * D + 8 * cg) * 2);
-    v.load(r.v, tok * D + 8 * cg);
-    if constexpr (M32) nrm = __builtin_amdgcn_raw_buffer_load_b32(r.n, tok * 4, 0, 0);
-    else nrm = (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r.n, tok * 2, 0, 0);
-  }
   __device__ __forceinline__ float norm() const {
     return M32 ? __uint_as_float(nrm) : __half2float(__ushort_as_half((unsigned short)nrm));
   }
@@ -867,16 +885,11 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
   // over them then runs while the page is still on its way.  Waves without residual tokens skip
   // their loads (a void load still takes its turn in the CU's address unit, and at kernel start
   // all eight waves of a CU queue there). ----
-  ResRsrc<M32> rres;
-  rres.make(P, ((size_t)b * Hkv + kvh) * R, wave_res);
-  // slot of the wave's token i of pass p0; past the slice a slot past the window's end, which reads as
-  // zeros (the probability there is 0, and the slice's last token in its place made NaN of 0 times an
-  // infinite value).  (R is a power of two past every slot; written as a choice it cost three registers,
-  // and 8 .. 28 bytes of scratch in the variants that have none to spare.)
-  auto res_slot = [&](int p0, int i) {
-    const int j = p0 + 4 * wave + i;
-    return (t_lo + j) | (((rcount - 1 - j) >> 31) & R);
-  };
+  constexpr int NORM_BYTES = M32 ? 4 : 2;
+  const auto res_norms = __builtin_amdgcn_make_buffer_rsrc(
+      static_cast<uint8_t*>(P.c.res_norm) + ((size_t)b * Hkv + kvh) * R * NORM_BYTES, 0, R * NORM_BYTES, 0x00020000);
+  // slot of the wave's token i of pass p0
+  auto res_slot = [&](int p0, int i) { return t_lo + p0 + 4 * wave + i; };
 #if OSCAR_MFMA_STEP
   // the new token is the window's last; every wave of the workgroup that owns it has it in registers
   const bool has_new = step_ok && rcount > 0 && t_lo + rcount == r;
@@ -891,13 +904,46 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     knew.load(kn, 8 * cg);
     tok_new.v.load(vn, 8 * cg);
   }
-  auto is_new = [&](int p0, int i) { return has_new && p0 + 4 * wave + i == rcount - 1; };
 #endif
-  ResTok<M32> rt_first[4];   // the wave's four tokens of the first residual pass
+  // The window's tokens go straight into LDS, into the wave's own operand tables, which the page loop is the
+  // first to need: four passes of 16-bit values at a time (two of fp32), K_u in one table, V in the other, a
+  // token a row of lanes and its channels as the lanes hold them.  A place past the slice is some other token
+  // of the window, which the pass masks out.
+  // Through registers two passes were on their way at a time, the values' type was asked for at every token, and
+  // in a launch with one split, which walks the whole window in every workgroup, a pass of 32 tokens cost 1.0 us.
+  // Now all of the first passes arrive together, the registers are free, there is one loop a type, and the new
+  // token of a step is put where the others are instead of being chosen in their place: 0.7 us (attention alone,
+  // 1 x 1K with 126 tokens in the window 12.25 -> 11.1 us, with none 7.8; 64 x 8K INT4 109.3 -> 105.8, 94.4; steps
+  // of 1 x 1000 12.5 -> 11.8, of 16 ragged sequences of 4K 19.9 -> 19.0, of 64 x 8K INT4 106.0 -> 103.2).
+  const bool wide = P.c.cfg.io_dtype == OSCAR_F32;
+  const int depth = wide ? 2 : 4;
+  const uint32_t k_stage = lds_byte(&s_A[wave][0][0]), v_stage = lds_byte(&s_P[wave][0][0]);
+  const u32x4 k_win = lds_load_rsrc(static_cast<const uint8_t*>(P.c.res_k) + ((size_t)b * Hkv + kvh) * R * D * 2, R * D * 2);
+  const uint32_t v_bytes = wide ? 4 : 2;
+  const u32x4 v_win = lds_load_rsrc(static_cast<const uint8_t*>(P.c.res_v) + ((size_t)b * Hkv + kvh) * R * D * v_bytes,
+                                    R * D * v_bytes);
+  auto in_window = [&](int p) { return 4 * (NW * p + wave) < rcount; };   // wave-uniform, as p is
+  auto stage = [&](int p) {
+    const int at = p & (depth - 1), elem = (res_slot(4 * NW * p, q4) & (R - 1)) * D + 8 * cg;
+    load_to_lds(k_win, k_stage + 1024 * at, elem * 2);
+    load_to_lds(v_win, v_stage + (wide ? 2048 : 1024) * at, elem * (int)v_bytes);
+    if (wide) load_to_lds(v_win, v_stage + 2048 * at + 1024, elem * 4 + 16);
+  };
+  // lane 4*p + i: the norm of token i of pass p, as stored.  Loads come back in order, so when this one is there
+  // everything staged in front of it is.
+  auto load_norms = [&]() {
+    const int t = (t_lo + 4 * (NW * (lane >> 2) + wave) + (lane & 3)) & (R - 1);
+    if constexpr (M32) return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(res_norms, t * 4, 0, 0);
+    else return (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(res_norms, t * 2, 0, 0);
+  };
+  uint32_t win_nrm = 0;
   if (wave_res) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rt_first[i].load(rres, res_slot(0, i), cg);
+    for (int p = 0; p < 4; ++p)
+      if (p < depth && in_window(p)) stage(p);
+    win_nrm = load_norms();
   }
+  __builtin_amdgcn_sched_barrier(0);
   PoolBases pools;
   pools.make(P, kvh);
   KeyRegs<BITS, NGK, M32> kr;
@@ -922,11 +968,6 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
 #endif
   OSCAR_STAMP(2);   // first page's key-side loads issued
 
-  // this wave's operand tables start as zeros (rows of absent heads stay zero)
-  for (int i = lane; i < 16 * TABW / 8; i += 64) {
-    reinterpret_cast<uint4*>(&s_A[wave][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
-    reinterpret_cast<uint4*>(&s_P[wave][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
   // Q_h = H(q)/sqrt(128) * scale*log2(e), every wave for itself (DPP butterflies inside the
   // row, no LDS, no workgroup barrier): qh[s][i] = channel 8*cg + i of head q4 + 4*s
   uint32_t sgn[4];
@@ -985,26 +1026,42 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         store_new_token(P, ((size_t)b * Hkv + kvh) * R + r - 1, tok_new.k, tok_new.v, tok_new.nrm, cg);
     }
 #endif
-    // (the raw norms stay opaque until here: converted where they were loaded, they made the
-    // wave wait for the loads, and for the whole first page behind them, before the query rotation)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rt_first[i].nrm));
-    // one pass: the wave's four tokens of slots p0 .. p0 + 4*NW - 1 of the slice, from registers.  Every
+    // The passes, four of the wave's tokens each, from LDS; IO (a constant here) is the values' type.  Every
     // fused multiply-add is written out: left to the compiler, the step form and the attention alone
     // fused differently and their outputs differed in the last bit.
-    auto pass = [&](const ResTok<M32> (&rt)[4], int p0) {
+    auto run_window = [&](auto io_tag) __attribute__((always_inline)) {
+    constexpr int IO = decltype(io_tag)::value;
+    constexpr bool WIDE = IO == OSCAR_F32;
+    constexpr int DEPTH = WIDE ? 2 : 4, V_PASS = WIDE ? 2048 : 1024;
+    auto pass = [&](int p) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
+      const int p0 = 4 * NW * p, at = p & (DEPTH - 1);
+      u32x4 ks[4], va[4], vb[4];
+      read_staged(k_stage + 1024 * at + 16 * n, ks);
+      read_staged(v_stage + V_PASS * at + 16 * n, va);
+      if constexpr (WIDE) read_staged(v_stage + V_PASS * at + 1024 + 16 * n, vb);
+      // (a value that does not belong to the slice must not meet its probability of 0: an infinite one would
+      // make NaN of it)
+      if (p0 + 4 * wave + 4 > rcount) {
+#pragma unroll
+        for (int i = 1; i < 4; ++i) {
+          const uint32_t held = p0 + 4 * wave + i < rcount ? ~0u : 0u;
+          va[i] &= held;
+          if constexpr (WIDE) vb[i] &= held;
+        }
+      }
       float sc[HP][4], vv[4][8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const bool valid = p0 + 4 * wave + i < rcount;   // wave-uniform
-        ResTok<M32> tok = rt[i];
-#if OSCAR_MFMA_STEP
-        if (is_new(p0, i)) tok = tok_new;
-#endif
+        ResTok<M32> tok;
+        tok.k = __builtin_bit_cast(uint4, ks[i]);
+        tok.v.a = __builtin_bit_cast(uint4, va[i]);
+        tok.v.b = WIDE ? __builtin_bit_cast(uint4, vb[i]) : tok.v.a;
+        tok.nrm = __builtin_amdgcn_readlane(win_nrm, 4 * p + i);
         float kv[8];
         halves_to_f32(tok.k, kv);
-        tok.v.widen(vv[i], P.c.cfg.io_dtype);
+        tok.v.widen(vv[i], IO);
         const float nrm = tok.norm();
 #pragma unroll
         for (int s = 0; s < HP; ++s) {
@@ -1031,28 +1088,37 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
         }
       }
     };
-    // Two register sets take turns: the next pass's tokens are on their way while a pass works on
-    // its own.  (With one set every pass began by waiting for its loads.  A launch with one split
-    // walks the whole window, up to eight passes (four waves), in every workgroup: batch 64 x 8K, attention
-    // alone, 127 residual tokens 73.4 -> 68.4 us against 60.3 with none; batch 1 x 1K, 104 residual
-    // tokens 14.7 -> 13.9.  A third set does not fit the registers of any variant.)
-    ResTok<M32> rt_other[4];
-    for (int p0 = 0;; p0 += 8 * NW) {
-      const bool second = p0 + 4 * NW + 4 * wave < rcount;
-      if (second) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) rt_other[i].load(rres, res_slot(p0 + 4 * NW, i), cg);
+    asm volatile("" : "+v"(win_nrm)::"memory");   // (the staged tokens are there)
+    for (int p = 0;;) {
+      const int end = p + DEPTH;
+#if OSCAR_MFMA_STEP
+      // the new token takes the place of what was read from its slot
+      const int last = rcount - 1, pn = last / (4 * NW), i_new = last & 3;
+      if (has_new && pn >= p && pn < end && wave == (last & (4 * NW - 1)) >> 2) {
+        const int at = pn & (DEPTH - 1);
+        if (q4 == 0) {
+          uint8_t* kd = reinterpret_cast<uint8_t*>(&s_A[wave][0][0]) + 1024 * at + 256 * i_new + 16 * n;
+          uint8_t* vd = reinterpret_cast<uint8_t*>(&s_P[wave][0][0]) + V_PASS * at + 256 * i_new + 16 * n;
+          *reinterpret_cast<uint4*>(kd) = tok_new.k;
+          *reinterpret_cast<uint4*>(vd) = tok_new.v.a;
+          if constexpr (WIDE) *reinterpret_cast<uint4*>(vd + 1024) = tok_new.v.b;
+        }
+        if (lane == 4 * pn + i_new) win_nrm = tok_new.nrm;
+        asm volatile("" ::: "memory");
       }
-      pass(rt_first, p0);
-      if (!second) break;
-      const bool third = p0 + 8 * NW + 4 * wave < rcount;
-      if (third) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) rt_first[i].load(rres, res_slot(p0 + 8 * NW, i), cg);
+#endif
+      for (; p < end && in_window(p); ++p) {
+        pass(p);
+        if (in_window(p + DEPTH)) stage(p + DEPTH);
       }
-      pass(rt_other, p0 + 4 * NW);
-      if (!third) break;
+      if (!in_window(p)) break;
+      uint32_t mark = load_norms();
+      asm volatile("" : "+v"(mark)::"memory");
     }
+    };
+    if (wide) run_window(std::integral_constant<int, OSCAR_F32>());
+    else if (P.c.cfg.io_dtype == OSCAR_BF16) run_window(std::integral_constant<int, OSCAR_BF16>());
+    else run_window(std::integral_constant<int, OSCAR_F16>());
     // hand the result over in accumulator layout through the wave's own slice of s_o
     // (written again only by this wave: for the query hand-off below and at the very end)
 #pragma unroll
@@ -1080,8 +1146,13 @@ void oscar_decode_mfma_kernel(DecodeParams P, int gq) {
     }
     wave_lds_fence();
   }
+  // this wave's operand tables start as zeros (rows of absent heads stay zero), behind the window's stay there
+  for (int i = lane; i < 16 * TABW / 8; i += 64) {
+    reinterpret_cast<uint4*>(&s_A[wave][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+    reinterpret_cast<uint4*>(&s_P[wave][0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   // The first page's value side is asked for only now, behind the query rotation and the
-  // residual window (whose two register sets take the space meanwhile): all waves of the grid
+  // residual window: all waves of the grid
   // ask for their first page at the same moment, and with the key side of every wave ahead of
   // every value side in the memory system's queues the first logits start earlier (about 1 %
   // on the small-batch workloads, nothing on the others).

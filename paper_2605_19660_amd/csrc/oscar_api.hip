@@ -157,6 +157,13 @@ extern "C" int32_t oscar_decode_auto_splits(const oscar_config* cfg, int32_t bat
   if (splits > max_by_pages) splits = max_by_pages;
   if (splits < 1) splits = 1;
   if (splits > 512) splits = 512;
+  // Two workgroups of four waves a CU are the waves of one of eight, which needs no reduce pass.  (Whole step in
+  // us, two splits / one, 8 kv heads: 22 sequences of 4000 tokens 22.8 / 20.8, INT4 29.9 / 27.5, of 16000 55.8 / 53.5;
+  // 28 of 4000 23.0 / 21.3; 32 of 4000 24.2 / 22.5, INT4 32.3 / 32.2; seven query heads on 4 kv heads, 44 of 4000
+  // 29.2 / 26.5, of 16000 70.8 / 69.5; 64 of 4000 29.6 / 28.2.  Three splits / one, 20 of 4000: 19.2 / 20.7.)
+  if (splits == 2 && 2 * units > n_cu && units <= n_cu && cfg->meta_dtype != OSCAR_F32 &&
+      oscar_decode_eight_waves(cfg->bits, gq > 4 ? 2 : 1, ngk, ngv))
+    splits = 1;
   return splits;
 }
 

@@ -1834,6 +1834,8 @@ extern "C" int oscar_debug_force_generic_decode(int32_t on) {
   return g_force_generic.exchange(on ? 1 : 0, std::memory_order_relaxed);
 }
 
+bool oscar_decode_eight_waves(int bits, int hp, int ngk, int ngv) { return eight_waves_built(bits, hp, ngk, ngv, false); }
+
 // Whether the matrix-core kernel is built for a configuration: group sizes 32, 64 or 128 on either
 // side, keys scaled into [-1, 1], page pools below 2 GiB each.
 static bool mfma_takes(const DecodeParams& P) {

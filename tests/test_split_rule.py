@@ -1,0 +1,18 @@
+"""The automatic split count where two splits of four-wave workgroups would fill the chip: one of eight waves instead,
+in the variants that have that form.  (Without a GPU the library counts 256 compute units.)"""
+import pytest
+import torch
+
+from paper_2605_19660_amd import binding as ob
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the numbers are those of 256 compute units")
+def test_two_splits_become_one():
+    rule = ob.decode_auto_splits
+    for bits in (2, 4):
+        cfg = ob.Config(32, 8, bits=bits)
+        assert [rule(cfg, b, 8192) for b in (16, 17, 21, 22, 32, 33)] == [4, 3, 3, 1, 1, 1]
+    assert rule(ob.Config(28, 4), 44, 8192) == 1                              # seven query heads a kv head
+    assert rule(ob.Config(32, 8, meta_dtype=ob.F32), 24, 8192) == 2           # fp32 metadata: as before
+    assert rule(ob.Config(32, 8, bits=4, k_group=32, v_group=64), 24, 8192) == 2   # no eight-wave form
+    assert rule(ob.Config(32, 8), 1, 2048 + 128) == 2                         # two by the pages, not by the chip

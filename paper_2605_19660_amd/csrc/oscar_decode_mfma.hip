@@ -456,14 +456,15 @@ template <> struct TilePair<2> {
     return c;
   }
 };
-// The address unit takes a 16-byte load 16 lanes at a time and spends an access on every cache line these
-// touch.  A lane's 32 bytes as two loads of their halves touch 16 lines each way (the 16 lanes of a quarter
-// are 128 bytes apart), every line four times a load, and by the second load the lines of the first are gone
-// again: 1210 accesses a page and a request to the L2 for every 69 bytes, which kept the address unit busy for
-// 81 % of a launch.  So the 16 lanes of a quarter read 32 bytes of eight places in one load: lane
-// n = m + 8*h of the first load the half h (tile 2*tp + h) of place m, of the second the half 1 - h of place
-// 8 + m.  A register holds the even tile in one half of its lanes and the odd one in the other; three DPP moves
-// a word put both in order where they are used (step of 64 x 8K tokens 118.9 -> 106.0 us, 5.3 -> 6.0 TB/s).
+// A lane's 32 bytes as two loads of their halves ask for every cache line twice: the 16 lanes of a quarter are 128
+// bytes apart, a load takes half of what it touches, and by the second load the lines of the first are gone again
+// (a request to the L2 for every 69 bytes, 9.2 million in a launch over 64 x 8K tokens).  So the 16 lanes of a
+// quarter read 32 bytes of eight places in one load: lane n = m + 8*h of the first load the half h (tile
+// 2*tp + h) of place m, of the second the half 1 - h of place 8 + m: 127 bytes a request, 5.0 million.  A register
+// holds the even tile in one half of its lanes and the odd one in the other; three DPP moves a word put both in
+// order where they are used (step of 64 x 8K tokens 118.9 -> 106.0 us, 5.3 -> 6.0 TB/s).  With the two halves in
+// neighbouring lanes the requests are the same and the accesses inside the CU's cache 0.57 times as many, and
+// nothing is gained by it (104.5 against 103.6 us): memory is the bound.
 template <> struct TilePair<4> {
   uint4 a, b;
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int tp, int lane, uint32_t so) {

@@ -614,21 +614,6 @@ struct Raw8rt {
   }
 };
 
-// The residual window of one (sequence, kv head) as buffer resources: K_u (fp16), V (caller's
-// dtype), token norms (metadata type); void when the wave has no residual token.
-template <bool M32> struct ResRsrc {
-  static constexpr int MB = M32 ? 4 : 2;
-  __amdgpu_buffer_rsrc_t k, n;
-  IoRsrc v;
-  __device__ __forceinline__ void make(const DecodeParams& P, size_t rb, bool valid) {
-    uint8_t* kp = const_cast<uint8_t*>(static_cast<const uint8_t*>(P.c.res_k)) + rb * D * 2;
-    uint8_t* np = const_cast<uint8_t*>(static_cast<const uint8_t*>(P.c.res_norm)) + rb * MB;
-    k = __builtin_amdgcn_make_buffer_rsrc(kp, 0, valid ? R * D * 2 : 0, 0x00020000);
-    n = __builtin_amdgcn_make_buffer_rsrc(np, 0, valid ? R * MB : 0, 0x00020000);
-    v.make(P.c.res_v, rb * D, R * D, P.c.cfg.io_dtype, valid);
-  }
-};
-
 // One residual token's share for a lane: 8 channels (channel group cg) of K_u (fp16) and of
 // V (caller's dtype), and the token norm, as stored.
 template <bool M32> struct ResTok {
@@ -723,16 +708,17 @@ __device__ __forceinline__ void flush_window(EncoderLds<__half, BITS, KG, NP>& l
   const size_t rb = ((size_t)b * Hkv + kvh) * R;
   const int phys = P.c.block_table[(size_t)b * P.c.max_pages_per_seq + page];
   const __half* res_norm = reinterpret_cast<const __half*>(P.c.res_norm) + rb;
-  ResRsrc<false> win;
-  win.make(P, rb, true);
+  const auto win_k = __builtin_amdgcn_make_buffer_rsrc(static_cast<uint8_t*>(P.c.res_k) + rb * D * 2, 0, R * D * 2, 0x00020000);
+  IoRsrc win_v;
+  win_v.make(P.c.res_v, rb * D, R * D, P.c.cfg.io_dtype, true);
   uint4 ku[NP];
   WindowValues vw[NP];
   float nrm[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int t = 16 * (NP == 8 ? p : 2 * p + grp) + slot;
-    ku[p] = buf_load16(win.k, (t * D + 8 * cg) * 2);
-    vw[p].raw.load(win.v, t * D + 8 * cg);
+    ku[p] = buf_load16(win_k, (t * D + 8 * cg) * 2);
+    vw[p].raw.load(win_v, t * D + 8 * cg);
     vw[p].dt = P.c.cfg.io_dtype;
     nrm[p] = __half2float(res_norm[t]);
   }

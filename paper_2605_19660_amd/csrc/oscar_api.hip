@@ -157,12 +157,21 @@ extern "C" int32_t oscar_decode_auto_splits(const oscar_config* cfg, int32_t bat
   if (splits > max_by_pages) splits = max_by_pages;
   if (splits < 1) splits = 1;
   if (splits > 512) splits = 512;
-  // Two workgroups of four waves a CU are the waves of one of eight, which needs no reduce pass.  (Whole step in
-  // us, two splits / one, 8 kv heads: 22 sequences of 4000 tokens 22.8 / 20.8, INT4 29.9 / 27.5, of 16000 55.8 / 53.5;
-  // 28 of 4000 23.0 / 21.3; 32 of 4000 24.2 / 22.5, INT4 32.3 / 32.2; seven query heads on 4 kv heads, 44 of 4000
-  // 29.2 / 26.5, of 16000 70.8 / 69.5; 64 of 4000 29.6 / 28.2.  Three splits / one, 20 of 4000: 19.2 / 20.7.)
+  // Two workgroups of four waves a CU are the waves of one of eight, which needs no reduce pass: in the variants that
+  // have that form and take a whole step with one split.  (Whole step in us, two splits / one, 8 kv heads, 22
+  // sequences: 2200 tokens INT4 22.3 / 20.1, G_k = 32 20.4 / 17.5, 4000 22.1 / 19.8, INT4 29.2 / 27.3, G_k = 32 24.9 /
+  // 23.2, 16000 55.8 / 53.5, INT4 90.6 / 77.9; 32 of 4000 23.3 / 21.3, INT4 31.9 / 31.0, of 16000 INT4 111.8 / 103.5;
+  // seven query heads on 4 kv heads, 44 of 4000 29.0 / 26.1, of 16000 71.0 / 69.5, 64 of 4000 29.5 / 26.3; float
+  // zero-points alike.  Where the pages allow two splits and the chip three: 17 of 2500 19.0 / 15.7, INT4 22.9 / 19.7;
+  // three splits against one, 20 of 4000, 19.2 / 20.7.)
+  // Five to eight query heads with G_k = 32 and G_v above keep two: their step with one is two calls (44 of 4000
+  // 30.8 / 31.9, 64 31.6 / 33.1).  The generic kernel has four waves at any count and a reduce pass behind it, and
+  // one split is less work to merge (attention, 16 heads on 4, 44 of 2500 172 / 157, of 4000 233 / 231, of 16000
+  // 922 / 948; 64 of 4000 237 / 231, of 16000 991 / 979).  A cache without tickets takes a step with one split as two
+  // calls, which costs less than the second split from some length on (22 of 4000 22.2 / 23.2, of 16000 54.9 /
+  // 54.4; 32 of 4000 23.7 / 24.7, of 16000 78.9 / 69.8).
   if (splits == 2 && 2 * units > n_cu && units <= n_cu && cfg->meta_dtype != OSCAR_F32 &&
-      oscar_decode_eight_waves(cfg->bits, gq > 4 ? 2 : 1, ngk, ngv))
+      oscar_decode_one_split_of_eight_waves(cfg->bits, gq > 4 ? 2 : 1, ngk, ngv))
     splits = 1;
   return splits;
 }

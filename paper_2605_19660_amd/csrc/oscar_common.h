@@ -205,8 +205,9 @@ __host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp,
   return (ngv == 1 && ngk <= 2) ? 2 : 1;
 }
 
-// Whether a variant (fp16 metadata) has the form of eight waves a workgroup for launches with one split.
-bool oscar_decode_eight_waves(int bits, int hp, int ngk, int ngv);
+// Whether a variant (fp16 metadata) has the form of eight waves a workgroup for launches with one split, and
+// takes a whole step in it.
+bool oscar_decode_one_split_of_eight_waves(int bits, int hp, int ngk, int ngv);
 
 // Matrix-core partial pass (params = the decode parameter block); returns
 // OSCAR_ERR_UNSUPPORTED when the configuration must take the generic kernel.

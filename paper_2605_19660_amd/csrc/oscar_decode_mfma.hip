@@ -1821,7 +1821,12 @@ extern "C" int oscar_debug_force_generic_decode(int32_t on) {
   return g_force_generic.exchange(on ? 1 : 0, std::memory_order_relaxed);
 }
 
-bool oscar_decode_eight_waves(int bits, int hp, int ngk, int ngv) { return eight_waves_built(bits, hp, ngk, ngv, false); }
+// (see step_form_pays)
+static constexpr bool one_split_step_pays(int bits, int hp, int ngk) { return !(bits == 2 && hp == 2 && ngk == 4); }
+
+bool oscar_decode_one_split_of_eight_waves(int bits, int hp, int ngk, int ngv) {
+  return eight_waves_built(bits, hp, ngk, ngv, false) && one_split_step_pays(bits, hp, ngk);
+}
 
 // Whether the matrix-core kernel is built for a configuration: group sizes 32, 64 or 128 on either
 // side, keys scaled into [-1, 1], page pools below 2 GiB each.
@@ -1864,7 +1869,7 @@ static bool step_form_pays(const DecodeParams& P, int gq, dim3 grid) {
   const int hp = gq <= 4 ? 1 : 2;
   if (step_one_per_cu(P.g.bits, hp, P.g.ngk, P.g.ngv))
     return (unsigned long long)grid.x * grid.y * grid.z <= (unsigned long long)oscar_compute_units();
-  return !(P.g.bits == 2 && hp == 2 && P.g.ngk == 4 && P.num_splits == 1);
+  return P.num_splits > 1 || one_split_step_pays(P.g.bits, hp, P.g.ngk);
 }
 
 // The same launch for a whole decode step (fp16 metadata); OSCAR_ERR_UNSUPPORTED: append and attention

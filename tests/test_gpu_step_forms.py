@@ -168,3 +168,13 @@ def test_bits_of_the_variants_without_registers_to_spare(bits, kg, vg, gq, split
     w = synth.LLAMA8B_32K.replace(batch=5, n_q_heads=gq, n_kv_heads=1, context=511 + 4, bits=bits, k_group=kg,
                                   v_group=vg)
     _run(w, starts, 6, splits, 4, zp=splits & 1)
+
+
+@pytest.mark.parametrize("gq,kg,vg,bits", [(4, 128, 32, 2), (4, 128, 32, 4), (7, 64, 64, 2), (7, 32, 64, 2), (7, 32, 128, 2)])
+def test_a_step_of_the_automatic_count_is_fused(gq, kg, vg, bits):
+    """Between half and all of the compute units in (sequence, kv head) pairs, where the rule looks at the variant."""
+    import torch
+    ob = _ob()
+    batch = torch.cuda.get_device_properties(0).multi_processor_count * 11 // 64
+    splits = ob.decode_auto_splits(ob.Config(4 * gq, 4, bits=bits, k_group=kg, v_group=vg), batch, 4000)
+    assert _route(splits, batch=batch, gq=gq, hkv=4, bits=bits, k_group=kg, v_group=vg) == FUSED

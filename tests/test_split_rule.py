@@ -16,3 +16,17 @@ def test_two_splits_become_one():
     assert rule(ob.Config(32, 8, meta_dtype=ob.F32), 24, 8192) == 2           # fp32 metadata: as before
     assert rule(ob.Config(32, 8, bits=4, k_group=32, v_group=64), 24, 8192) == 2   # no eight-wave form
     assert rule(ob.Config(32, 8), 1, 2048 + 128) == 2                         # two by the pages, not by the chip
+
+
+def _units():
+    return torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
+
+
+@pytest.mark.parametrize("share", [0.55, 0.7, 1.0])   # of the compute units, as (sequence, kv head) pairs
+def test_where_one_split_does_not_stand_for_two(share):
+    rule, batch = ob.decode_auto_splits, int(share * _units()) // 4
+    for tokens in (2060, 2900):   # (16 .. 23 pages: two splits at most)
+        at = lambda gq=4, **kw: rule(ob.Config(4 * gq, 4, **kw), batch, tokens)
+        assert at() == 1 and at(gq=7) == 1 and at(bits=4) == 1 and at(k_group=32, v_group=64) == 1
+        # a step with one split is two calls there, with two it is not
+        assert at(gq=7, k_group=32, v_group=64) == 2 and at(gq=7, k_group=32, v_group=128) == 2

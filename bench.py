@@ -427,13 +427,15 @@ def compact_record(args, w, np, torch, ob, synth, bf16=False, steps=200, warmup=
         lens = torch.full((w.batch,), w.context, dtype=torch.int32, device="cuda")
         kh = kd.permute(0, 2, 1, 3).contiguous()
         vh = vd.permute(0, 2, 1, 3).contiguous()
+        bsplits = args.bf16_splits or ob.bf16_auto_splits(w.n_q_heads, w.n_kv_heads, w.batch, w.context)
+        bws = torch.empty(ob.decode_workspace_bytes(cfg, w.batch, bsplits), dtype=torch.uint8, device="cuda")
         for _ in range(3):
-            ob.bf16_decode_attn(q, kh, vh, lens, out=out, num_splits=splits, workspace=ws, stream=stream, head_major=True)
+            ob.bf16_decode_attn(q, kh, vh, lens, out=out, num_splits=bsplits, workspace=bws, stream=stream, head_major=True)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         torch.cuda.synchronize()
         e0.record(stream)
         for _ in range(20):
-            ob.bf16_decode_attn(q, kh, vh, lens, out=out, num_splits=splits, workspace=ws, stream=stream, head_major=True)
+            ob.bf16_decode_attn(q, kh, vh, lens, out=out, num_splits=bsplits, workspace=bws, stream=stream, head_major=True)
         e1.record(stream)
         torch.cuda.synchronize()
         rec["bf16_us"] = e0.elapsed_time(e1) * 1e3 / 20
@@ -522,7 +524,7 @@ def measure(args, w, np, torch, ob, synth):
     bf16 = None
     if not args.no_bf16 and w.io_dtype in ("bf16", "f16"):
         lens = torch.full((w.batch,), w.context, dtype=torch.int32, device="cuda")
-        bsplits = args.bf16_splits or ob.decode_auto_splits(cfg, w.batch, w.context)
+        bsplits = args.bf16_splits or ob.bf16_auto_splits(w.n_q_heads, w.n_kv_heads, w.batch, w.context)
         bws = torch.empty(ob.decode_workspace_bytes(cfg, w.batch, bsplits), dtype=torch.uint8, device="cuda")
         n_rep = max(5, min(50, args.steps // 4))
         b_bytes = w.batch * w.n_kv_heads * w.context * 2 * w.head_dim * 2

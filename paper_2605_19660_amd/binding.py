@@ -471,6 +471,14 @@ def decode_attn_reduce(cache: Cache, out, workspace, num_splits: int, stream=Non
     return out
 
 
+def bf16_auto_splits(n_q_heads: int, n_kv_heads: int, batch: int, max_seq_len: int) -> int:
+    """The comparator's split count.  Its workgroups have four waves whatever their number, so it takes the count of
+    a form that does too (fp32 metadata): with 129 .. 256 (sequence, kv head) pairs two where the packed cache's
+    kernel may take one of eight waves (22 sequences of 4000 tokens, 8 kv heads, two splits / one, 76.6 / 101.0 us,
+    32 of them 88.6 / 101.7)."""
+    return decode_auto_splits(Config(n_q_heads, n_kv_heads, meta_dtype=F32), batch, max_seq_len)
+
+
 def bf16_decode_attn(q, k, v, seq_lens, out=None, scale: float = 0.0, max_seq_len_hint: int = 0,
                      num_splits: int = 0, workspace=None, stream=None, head_major: bool = False):
     """oscar_bf16_decode_attn: comparator on an uncompressed cache, [batch, S, n_kv_heads, d]
@@ -486,7 +494,7 @@ def bf16_decode_attn(q, k, v, seq_lens, out=None, scale: float = 0.0, max_seq_le
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
     if num_splits == 0:
-        num_splits = decode_auto_splits(cfg, B, max_seq_len_hint or S)
+        num_splits = bf16_auto_splits(Hq, Hkv, B, max_seq_len_hint or S)
     if workspace is None:
         workspace = torch.empty(decode_workspace_bytes(cfg, B, num_splits), dtype=torch.uint8,
                                 device=q.device)

@@ -30,3 +30,29 @@ def test_where_one_split_does_not_stand_for_two(share):
         assert at() == 1 and at(gq=7) == 1 and at(bits=4) == 1 and at(k_group=32, v_group=64) == 1
         # a step with one split is two calls there, with two it is not
         assert at(gq=7, k_group=32, v_group=64) == 2 and at(gq=7, k_group=32, v_group=128) == 2
+
+
+@pytest.mark.parametrize("n_q_heads,n_kv_heads", [(32, 8), (28, 4), (8, 8)])
+def test_the_comparator_keeps_the_count_of_four_waves(n_q_heads, n_kv_heads, monkeypatch):
+    """Without a count bf16_decode_attn sizes its workspace for its own one: two splits, not one of eight waves."""
+    batch = int(0.7 * _units()) // n_kv_heads
+    assert ob.decode_auto_splits(ob.Config(n_q_heads, n_kv_heads), batch, 4000) == 1
+
+    class Seen(Exception):
+        pass
+
+    def sized(cfg, b, num_splits):
+        raise Seen(num_splits)
+
+    class Rows:   # what the wrapper asks of a tensor before it needs the device
+        def __init__(self, *shape):
+            self.shape, self.is_cuda, self.device = shape, True, "cpu"
+
+        def is_contiguous(self):
+            return True
+
+    monkeypatch.setattr(ob, "decode_workspace_bytes", sized)
+    kv = Rows(batch, 4000, n_kv_heads, 128)
+    with pytest.raises(Seen) as seen:
+        ob.bf16_decode_attn(Rows(batch, n_q_heads, 128), kv, kv, None, out=kv)
+    assert seen.value.args == (2,)

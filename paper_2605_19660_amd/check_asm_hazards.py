@@ -24,6 +24,9 @@ compiler inserts the wait states for its own DPP instructions and for nothing in
 block.  `scan_dpp` reports every DPP instruction between ASMSTART and ASMEND whose DPP source
 register was written by one of the two vector instructions issued before it (an `s_nop n`
 counts as n + 1 slots).
+
+`scan_swap` holds the half-register swaps to the same distance, and `scan_lengths` looks for what an
+encoder that reads its lengths as constants must not do behind its ticket.
 """
 from __future__ import annotations
 
@@ -176,6 +179,24 @@ def scan_swap(asm_text: str) -> list[tuple]:
     return found
 
 
+def scan_lengths(asm_text: str) -> list[tuple]:
+    """The encoder's form for the smallest launches (oscar_append_sides_kernel) reads its lengths through the constant
+    address space, and its last workgroup, known by the ticket, changes them.  Reported: a kernel without the mark that
+    holds them in registers in front of the draw, and a scalar load behind the draw from anything but the kernel's
+    arguments."""
+    found = []
+    for kernel, body in re.findall(r"^(_Z\S*oscar_append_sides_kernel\S*):.*?\n(.*?)^\ts_endpgm", asm_text, re.M | re.S):
+        draw = body.find("\tbuffer_atomic_add ")
+        mark = body.find("; lengths held in")
+        if not 0 <= mark < draw:
+            found.append((kernel, "lengths not held in front of the ticket"))
+        base = re.search(r"s_load_dword\S* \S+, (s\[\d+:\d+\]),", body)
+        for load, frm in re.findall(r"\t(s_load_dword\S* [^,\n]+, (s\[\d+:\d+\]),[^\n]*)", body[draw:]):
+            if frm != base.group(1):
+                found.append((kernel, load))
+    return found
+
+
 def scratch_bytes(asm_text: str) -> dict[str, int]:
     """Bytes of scratch memory a lane of each kernel, from the listing's kernel descriptions."""
     names = re.findall(r"^    \.name: +(\S+)$", asm_text, re.M)
@@ -220,6 +241,13 @@ def main() -> int:
         for k, i, t, j, tj, ago in found[:20]:
             print("  %s\n    line %d: %s\n    line %d (%d slots later): %s" % (k, i, t, j, ago, tj))
         bad += len(found)
+        n_sides = len(re.findall(r"^_Z\S*oscar_append_sides_kernel\S*:", text, re.M))
+        if n_sides:
+            found = scan_lengths(text)
+            print("%s: %d kernels that hold their lengths, %d lapses" % (src, n_sides, len(found)))
+            for f in found[:20]:
+                print("  %s\n    %s" % f)
+            bad += len(found)
     return 1 if bad else 0
 
 

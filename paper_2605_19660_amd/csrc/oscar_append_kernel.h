@@ -491,15 +491,20 @@ struct SeqPlan {
   bool ok;
 };
 
-// (SCALAR: b is uniform and the loads are scalar ones whatever stands in front of them)
+// (SCALAR: b is uniform and the loads are scalar ones whatever stands in front of them.  They go through the
+// constant address space, which promises the compiler that the lengths never change, and the launch's last
+// workgroup changes them: so that no use behind the ticket is answered by loading them again, they are opaque from
+// here on.  scan_lengths in check_asm_hazards.py looks for this mark in the compiled kernels.)
 typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
 template <bool SCALAR = false>
 __device__ __forceinline__ SeqPlan plan_sequence(const AppendParams& P, int b) {
   SeqPlan s;
-  const int seq_len = SCALAR ? ((ScalarInts)P.c.seq_lens)[b] : P.c.seq_lens[b];
-  s.r0 = SCALAR ? ((ScalarInts)P.c.res_lens)[b] : P.c.res_lens[b];
+  int seq_len = SCALAR ? ((ScalarInts)P.c.seq_lens)[b] : P.c.seq_lens[b];
+  int r0 = SCALAR ? ((ScalarInts)P.c.res_lens)[b] : P.c.res_lens[b];
   int n = P.T;
   if (P.new_lens) n = SCALAR ? ((ScalarInts)P.new_lens)[b] : P.new_lens[b];
+  if constexpr (SCALAR) asm volatile("; lengths held in %0 %1 %2" : "+s"(seq_len), "+s"(r0), "+s"(n));
+  s.r0 = r0;
   n = n < 0 ? 0 : (n > P.T ? P.T : n);
   s.n = n;
   s.packed_pages = (seq_len - s.r0) / R;

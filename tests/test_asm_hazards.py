@@ -87,3 +87,13 @@ def test_encoders_keep_nothing_in_scratch_memory(source):
     used = {k: b for k, b in chk.scratch_bytes(chk.compile_to_asm(source)).items() if "append" in k or "norm" in k}
     assert len(used) > 50
     assert {k: b for k, b in used.items() if b} == {}
+
+
+def test_length_scanner_wants_the_lengths_held_in_front_of_the_ticket():
+    head = "_ZN12_GLOBAL__N_125oscar_append_sides_kernelIfEEv12AppendParams:\n\ts_load_dwordx2 s[4:5], s[0:1], 0x10\n"
+    mark, draw = "\t; lengths held in s6 s7 s8\n", "\tbuffer_atomic_add v1, v2, s[8:11], 0 offen sc0\n"
+    late, end = "\ts_load_dwordx2 s[6:7], s[0:1], 0x20\n", "\ts_endpgm\n"
+    assert chk.scan_lengths(head + mark + draw + late + end) == []
+    assert len(chk.scan_lengths(head + draw + mark + end)) == 1 and len(chk.scan_lengths(head + draw + end)) == 1
+    assert len(chk.scan_lengths(head + mark + draw + "\ts_load_dword s6, s[4:5], 0x0\n" + end)) == 1
+    assert chk.scan_lengths(head.replace("sides_", "") + draw + end) == []

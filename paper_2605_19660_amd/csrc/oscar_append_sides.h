@@ -7,8 +7,7 @@
 //    is not there the offset lies past the resource's end.  The tokens of a block that begins with the old window
 //    came one branch after another before, each behind the whole of the last one's answer, and the tail's behind
 //    the block's transform (whole calls in us, bf16 INT2, 8 heads, the calls' host part alike: pieces of 2 x 500
-//    8.75 -> 7.7, of 1 x 100 7.45 -> 6.9, fp32 8 x 64 6.1 -> 5.8; without an old window nothing: 8 x 384 on 4
-//    heads 6.35 -> 6.45).
+//    8.75 -> 7.7, of 1 x 100 7.45 -> 6.9, fp32 8 x 64 6.1 -> 5.8).
 #pragma once
 #include "oscar_append_kernel.h"
 
@@ -70,41 +69,47 @@ void oscar_append_sides_kernel(AppendParams P) {
       advance_all(P, tid, 64);
   };
 
-  // ---- loads: every one a buffer load without a branch around it, void where there is nothing ----
+  // ---- loads: every one a buffer load without a branch around it, void where there is nothing.  with_old: of a
+  // block that may begin with the old window ----
   struct Keys {
     Raw8<IO> fresh[NP];   // the block's new tokens
     uint4 held[NP];       // its old ones, K_u as it is
     META held_norm[NORM_ALL ? NP : 1], page_norm[NORM_ALL ? NP : 1];
   };
-  auto load_keys = [&](Keys& k) {
+  auto load_keys = [&](Keys& k, auto with_old) {
     const auto rows = block_rows<IO>(P, P.k, b, kvh, blk, sp.r0, do_block);
 #pragma unroll
     for (int j = 0; j < NP; ++j) k.fresh[j].load(rows, block_row_offset<IO>(P, blk, sp.r0, token(j), cg), 0);
     const auto rk = rsrc(res_k, old * D * 2), rn = rsrc(res_norm, old * (int)sizeof(META));
+    if constexpr (with_old) {
 #pragma unroll
-    for (int j = 0; j < NP; ++j) k.held[j] = load_once(rk, (token(j) * D + cg * 8) * 2, 0);
+      for (int j = 0; j < NP; ++j) k.held[j] = load_once(rk, (token(j) * D + cg * 8) * 2, 0);
+    }
     if constexpr (NORM_ALL) {
       // norms of new tokens: the first launch wrote them into the page's slots
-      const auto pn = rsrc(static_cast<uint8_t*>(P.c.k_norms) + page() * P.g.k_norms_bytes, do_block ? R * (int)sizeof(META) : 0);
+      const auto pn = rsrc(static_cast<uint8_t*>(P.c.k_norms) + page() * P.g.k_norms_bytes,
+                           do_block ? R * (int)sizeof(META) : 0);
 #pragma unroll
       for (int j = 0; j < NP; ++j) {
-        k.held_norm[j] = load_meta_elem<META>(rn, token(j));
+        if constexpr (with_old) k.held_norm[j] = load_meta_elem<META>(rn, token(j));
         k.page_norm[j] = load_meta_elem<META>(pn, tok_meta_pos(token(j)));
       }
-    } else {
+    } else if constexpr (with_old) {
       k.held_norm[0] = load_meta_elem<META>(rn, token(qj));   // (of the token whose norm this lane will have)
     }
   };
   struct Values {
     Raw8<IO> fresh[NP], held[NP];
   };
-  auto load_values = [&](Values& v) {
+  auto load_values = [&](Values& v, auto with_old) {
     const auto rows = block_rows<IO>(P, P.v, b, kvh, blk, sp.r0, do_block);
 #pragma unroll
     for (int j = 0; j < NP; ++j) v.fresh[j].load(rows, block_row_offset<IO>(P, blk, sp.r0, token(j), cg), 0);
-    const auto rv = rsrc(res_v, old * D * (int)sizeof(IO));
+    if constexpr (with_old) {
+      const auto rv = rsrc(res_v, old * D * (int)sizeof(IO));
 #pragma unroll
-    for (int j = 0; j < NP; ++j) v.held[j].load(rv, (token(j) * D + cg * 8) * (int)sizeof(IO), 0);
+      for (int j = 0; j < NP; ++j) v.held[j].load(rv, (token(j) * D + cg * 8) * (int)sizeof(IO), 0);
+    }
   };
   // the tail: token i = 32 * j + row of it in register j
   struct Tail {
@@ -123,7 +128,7 @@ void oscar_append_sides_kernel(AppendParams P) {
   };
 
   // ---- the key transform of the block ----
-  auto transform = [&](const Keys& k, uint4 (&ku)[NP], float (&nrm)[NP], float (&nrm_q)[1]) {
+  auto transform = [&](const Keys& k, auto with_old, uint4 (&ku)[NP], float (&nrm)[NP], float (&nrm_q)[1]) {
     uint4 nu[NP];
     if constexpr (NORM_ALL) {
       const int tail_len = sp.tail_len;
@@ -134,17 +139,23 @@ void oscar_append_sides_kernel(AppendParams P) {
         const float pn = to_f32<META>(k.page_norm[j]);
         nu[j] = key_transform8_given<META>(x, sgn, pn, P.c.cfg.rotation == OSCAR_ROTATION_ON);
         // (a window place that the new tail takes holds the tail's norm by now, and the page the old one)
-        nrm[j] = token(j) < old && token(j) >= tail_len ? to_f32<META>(k.held_norm[j]) : pn;
+        if constexpr (with_old) nrm[j] = token(j) < old && token(j) >= tail_len ? to_f32<META>(k.held_norm[j]) : pn;
+        else nrm[j] = pn;
       }
     } else {
       float x[NP][8], nq;
 #pragma unroll
       for (int j = 0; j < NP; ++j) k.fresh[j].widen(x[j]);
       key_transform_4tokens<META>(x, sgn, qj, nq, nu);
-      nrm_q[0] = token(qj) < old ? to_f32<META>(k.held_norm[0]) : nq;
+      if constexpr (with_old) nrm_q[0] = token(qj) < old ? to_f32<META>(k.held_norm[0]) : nq;
+      else nrm_q[0] = nq;
     }
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
+      if constexpr (!with_old) {
+        ku[j] = nu[j];
+        continue;
+      }
       const bool o = token(j) < old;
       ku[j].x = o ? k.held[j].x : nu[j].x;
       ku[j].y = o ? k.held[j].y : nu[j].y;
@@ -197,28 +208,37 @@ void oscar_append_sides_kernel(AppendParams P) {
       if (i < cnt) t.x[j].store(res_v + (size_t)(dst0 + i) * D + cg * 8);
     }
   };
-  auto merged = [&](const Values& v, Raw8<IO> (&vraw)[NP]) {
+  auto merged = [&](const Values& v, auto with_old, Raw8<IO> (&vraw)[NP]) {
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
       vraw[j] = v.fresh[j];
-      vraw[j].merge(v.held[j]);
+      if constexpr (with_old) vraw[j].merge(v.held[j]);
     }
   };
 
-  // (a branch around all of a block's work, not around its loads: those come back where they are used)
+  // Branches around all of a block's work, not around its loads: where branches meet again the compiler waits for
+  // what any of them may have asked for.  Blocks of a sequence without an old window, a first prompt's, leave out
+  // its loads, which take their turns in the CU's address unit also where they bring nothing; not those of a later
+  // block behind one, whose neighbours run the other code: two codes in a launch are fetched twice.  (Whole calls
+  // with two clears in front, us, with the void loads / without: 1 x 128 tokens 9.25 / 9.05, 1 x 1024 9.25 / 9.10, 1 x 1000
+  // 10.65 / 10.42, fp32 2 x 512 9.59 / 9.31; chosen by block, pieces of 2 x 500 behind 60 tokens 10.7 / 10.95.)
+  // The same for the loads of a tail where there is none, in fp32 alone (2 x 512 9.31 / 9.16, INT4 9.51 / 9.33; bf16
+  // 1 x 1024 9.10 / 9.14).
   if ((blockIdx.z & 1) == 0) {
     Tail t;
     uint4 ku[NP];
     float nrm[NP] = {}, nrm_q[1] = {};
-    if (do_block) {
+    auto block = [&](auto with_old, auto with_tail) {
       Keys k;
-      load_keys(k);
-      load_tail(t, P.k, true);
+      load_keys(k, with_old);
+      if constexpr (with_tail) load_tail(t, P.k, true);
       __builtin_amdgcn_sched_barrier(0);
-      transform(k, ku, nrm, nrm_q);
-    } else {
-      load_tail(t, P.k, true);
-    }
+      transform(k, with_old, ku, nrm, nrm_q);
+    };
+    if (do_block && sp.r0 > 0) block(std::true_type(), std::true_type());
+    else if (do_block && (cnt > 0 || sizeof(IO) < 4)) block(std::false_type(), std::true_type());
+    else if (do_block) block(std::false_type(), std::false_type());
+    else load_tail(t, P.k, true);
     __syncthreads();
     draw();
     if (cnt > 0) store_key_tail(t);
@@ -226,15 +246,17 @@ void oscar_append_sides_kernel(AppendParams P) {
   } else {
     Tail t;
     Raw8<IO> vraw[NP];
-    if (do_block) {
+    auto block = [&](auto with_old, auto with_tail) {
       Values v;
-      load_values(v);
-      load_tail(t, P.v, false);
+      load_values(v, with_old);
+      if constexpr (with_tail) load_tail(t, P.v, false);
       __builtin_amdgcn_sched_barrier(0);
-      merged(v, vraw);
-    } else {
-      load_tail(t, P.v, false);
-    }
+      merged(v, with_old, vraw);
+    };
+    if (do_block && sp.r0 > 0) block(std::true_type(), std::true_type());
+    else if (do_block && (cnt > 0 || sizeof(IO) < 4)) block(std::false_type(), std::true_type());
+    else if (do_block) block(std::false_type(), std::false_type());
+    else load_tail(t, P.v, false);
     __syncthreads();
     draw();
     if (cnt > 0) store_value_tail(t);

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_2605_19660_amd import synth
-from test_gpu_parity import DT, _ob, to_dev
+from test_gpu_parity import DT, _ob, assert_decode_close, make_pair, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -178,3 +178,27 @@ def test_a_step_of_the_automatic_count_is_fused(gq, kg, vg, bits):
     batch = torch.cuda.get_device_properties(0).multi_processor_count * 11 // 64
     splits = ob.decode_auto_splits(ob.Config(4 * gq, 4, bits=bits, k_group=kg, v_group=vg), batch, 4000)
     assert _route(splits, batch=batch, gq=gq, hkv=4, bits=bits, k_group=kg, v_group=vg) == FUSED
+
+
+@pytest.mark.parametrize("gq,kg,scale", [(4, 128, "l2"), (7, 32, "l2"), (2, 128, "mean_abs")])
+def test_calls_of_the_automatic_count_against_the_oracle(gq, kg, scale):
+    """The count worked out by the calls themselves, workspace and all, in the same range of pairs."""
+    import torch
+    ob = _ob()
+    batch = torch.cuda.get_device_properties(0).multi_processor_count * 11 // 64
+    n = 2048 + 70   # (16 pages: two splits at most)
+    w = synth.LLAMA8B_32K.replace(batch=batch, n_q_heads=4 * gq, n_kv_heads=4, context=n, k_group=kg, v_group=64)
+    k, v = synth.make_kv_batch(w)
+    q = synth.make_q(w)
+    g, o = make_pair(w, 17, scale=scale)
+    ob.quantize_append(g, to_dev(k, w.io_dtype), to_dev(v, w.io_dtype), eager=True, max_seq_len_hint=0)
+    o.append(k, v, eager=True)
+    qd = to_dev(q, w.io_dtype)
+    assert_decode_close(ob.decode_attn(g, qd, max_seq_len_hint=n).cpu().numpy(), o.decode_attn(q))
+    k1, v1 = np.ascontiguousarray(np.roll(k, 9, 1)[:, :1]), np.ascontiguousarray(np.roll(v, 9, 1)[:, :1])
+    splits = ob.decode_auto_splits(g.cfg, batch, n + 1)
+    work = torch.empty(ob.decode_workspace_bytes(g.cfg, batch, splits), dtype=torch.uint8, device="cuda")
+    out = torch.empty(batch, w.n_q_heads, 128, device="cuda")
+    ob.decode_step(g, to_dev(k1, w.io_dtype), to_dev(v1, w.io_dtype), qd, out, work, 0, max_seq_len_hint=n + 1)
+    o.append(k1, v1, eager=False)
+    assert_decode_close(out.cpu().numpy(), o.decode_attn(q))

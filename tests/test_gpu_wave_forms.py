@@ -57,7 +57,8 @@ def test_both_forms_against_the_oracle(io, meta, bits, kg, vg, gq, zp, splits):
 
 
 @pytest.mark.parametrize("splits", [1, 2])
-@pytest.mark.parametrize("io,bits,kg,vg,gq", [("bf16", 2, 128, 32, 4), ("f16", 4, 64, 32, 3), ("bf16", 2, 64, 64, 7)])
+@pytest.mark.parametrize("io,bits,kg,vg,gq", [("bf16", 2, 128, 32, 4), ("f16", 4, 64, 32, 3), ("bf16", 2, 64, 64, 7),
+                                              ("f32", 2, 128, 32, 4), ("f32", 4, 64, 64, 2), ("f32", 2, 64, 32, 7)])
 def test_bits_of_the_two_calls_in_the_four_wave_form(io, bits, kg, vg, gq, splits):
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count

@@ -1,7 +1,7 @@
 """The residual window in the decode kernels, which read whole passes of it: what lies behind its last token, or
 belongs to another split, must not reach a result.  Windows of all pass remainders, one and several splits, four and
-eight waves, every value type, against the same cache with infinities and NaN in the unused places, and against the
-oracle."""
+eight waves, every value type, attention alone and step (whose new token takes a staged place), against the same cache
+with infinities and NaN in the unused places, and against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -43,6 +43,7 @@ def test_places_behind_the_window(io, meta, bits, gq, hkv):
         o.append(k, v, eager=False, new_lens=new)
         seqs = g.res_lens.tolist()
         before = {name: getattr(g, name).clone() for name in vars(g) if isinstance(getattr(g, name), torch.Tensor)}
+        outs, want = [], o.decode_attn(q)
         for splits in (1, 2, 8):
             work = torch.empty(ob.decode_workspace_bytes(g.cfg, 2, splits), dtype=torch.uint8, device="cuda")
             got = []
@@ -57,5 +58,10 @@ def test_places_behind_the_window(io, meta, bits, gq, hkv):
                                out, work, splits, max_seq_len_hint=max(n) + 1)
                 got.append((attn, out))
             assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (lens, splits)
-            if hkv == 2:
-                assert_decode_close(got[0][0].cpu().numpy(), o.decode_attn(q))
+            outs.append([t.cpu().numpy() for t in got[0]])
+        for attn, _ in outs:
+            assert_decode_close(attn, want)
+        o.append(np.ascontiguousarray(k1), np.ascontiguousarray(v1), eager=False)
+        want = o.decode_attn(q)
+        for _, out in outs:
+            assert_decode_close(out, want)

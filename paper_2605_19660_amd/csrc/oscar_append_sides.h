@@ -169,7 +169,8 @@ void oscar_append_sides_kernel(AppendParams P) {
       float x[8], nn;
       t.x[0].widen(x);
       uint4 u;
-      if constexpr (NORM_ALL) u = key_transform8_given<META>(x, sgn, to_f32<META>(t.norm[0]), P.c.cfg.rotation == OSCAR_ROTATION_ON);
+      if constexpr (NORM_ALL)
+        u = key_transform8_given<META>(x, sgn, to_f32<META>(t.norm[0]), P.c.cfg.rotation == OSCAR_ROTATION_ON);
       else u = key_transform8<META>(x, sgn, nn);
       if (row < cnt) {
         *reinterpret_cast<uint4*>(res_k + (size_t)(dst0 + row) * D + cg * 8) = u;

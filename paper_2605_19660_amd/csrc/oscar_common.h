@@ -199,7 +199,8 @@ __host__ __device__ constexpr int oscar_decode_mfma_wgs_per_cu(int bits, int hp,
   }
   // (measured, partial pass in us at one / two per CU: (4,1,4,4) 65 / 73 with 13 registers in
   // scratch, (4,2,1,4) 35 / 38, (4,2,2,4) 37 / 43; the other way round (2,2,4,4) 39 / 33,
-  // (2,2,2,4) 34 / 30, (4,1,2,4) 62 / 60, (4,1,4,1) 62 / 59, (4,1,4,2) 63 / 61)
+  // (2,2,2,4) 34 / 30, (4,1,2,4) 62 / 60, (4,1,4,1) 62 / 59, (4,1,4,2) 63 / 61; while the residual window went
+  // through registers.  Now (4,2,1,2) and (4,2,4,1) need 252 registers and would fit two: not timed there)
   if (hp == 1) return (bits == 4 && ngk == 4 && ngv == 4) ? 1 : 2;
   if (bits == 2) return 2;
   return (ngv == 1 && ngk <= 2) ? 2 : 1;

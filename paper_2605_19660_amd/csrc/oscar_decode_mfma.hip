@@ -647,9 +647,10 @@ __device__ __forceinline__ int row_hi(int h) { return 4 * (h & 3) + 2 * (h >> 2)
 // (measured: 4-bit, G_k = 32 took 188 us with 65 spilled registers at two per CU, 76 us at
 // one).
 //
-// The step's kernel holds the new token beside all that: five variants that run at two per CU without
-// it (step_one_per_cu) would keep 64 .. 120 bytes of a lane in scratch and run at one; the launcher
-// takes them only where a CU gets no second workgroup anyway (step_form_pays).
+// The step's kernel holds the new token beside all that.  Five variants that run at two per CU without it
+// (step_one_per_cu) are built for one, and taken only where a CU gets no second workgroup anyway
+// (step_form_pays): at two they kept 64 .. 120 bytes of a lane in scratch as long as the residual window went
+// through registers.  At two they would have none today (220 .. 245 registers; (2,2,4,4) 24 bytes).
 __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, int ngv) {
   if (bits == 2) return hp == 2 && ngk == 4 && ngv == 4;
   return hp == 1 ? ngk == 4 && ngv < 4 : ngk <= 2 && ngv == 1;
@@ -665,9 +666,9 @@ __host__ __device__ constexpr bool step_one_per_cu(int bits, int hp, int ngk, in
 // 14.7 / 17.5), with fp32 metadata not at all.  With an empty window the attention alone loses there (1 x 1024
 // 9.7 / 10.4, with 104 tokens in it 17.1 / 14.2, with 116 of 500 15.8 / 12.3; the step 11.8 / 11.6, 19.0 / 16.5 and
 // 17.7 / 14.4), and the window is as often full as empty.
-// The step's two-slot forms, and INT4 with G_k = 128 and G_v = 32, keep 36 .. 120 bytes a lane in scratch, those of
-// G_k = 32 most, as they do with four waves; eight are faster all the same (warm, 28 heads on 4, 1 x 1016: G_k = 32 with G_v = 128 20.9 / 17.9, with
-// G_v = 64 21.4 / 18.0, G_k = 128 with G_v = 32 19.6 / 16.2).
+// (With the residual window straight in LDS, whole step, warm, 1 x 1016, one split: 28 heads on 4, G_k = 128 with
+// G_v = 32 16.9 / 14.9, G_k = G_v = 64 16.6 / 14.8, G_k = 64 with G_v = 32 17.3 / 15.2; 32 on 8, 1 x 1000 12.4 / 11.3,
+// INT4 13.4 / 12.6.  15 splits of 1 x 16000, 28 on 4, 16.6 / 15.4.)
 // At one split count the two forms deal a sequence's pages to different waves: the last bits of its output
 // differ between launches on either side of the line.
 // Built where two workgroups of four fit a CU in both kernels (the step's and the attention alone
@@ -1856,15 +1857,19 @@ int oscar_launch_decode_mfma(const void* params, int gq, dim3 grid, hipStream_t 
   return launch_this_form(P, gq, grid, st, e0, e1);
 }
 
-// Whether a step is faster with the append inside the attention kernel than as two calls.  It is in
-// most variants (1.01 .. 1.32 times, device time of 128 steps with one flush a sequence, batch 1 .. 64,
-// 0.5K .. 32K tokens).  Not in these, whose step kernel runs out of registers:
+// Whether a step takes the append inside the attention kernel or as two calls.  Inside is faster in most variants
+// (1.01 .. 1.32 times, device time of 128 steps with one flush a sequence, batch 1 .. 64, 0.5K .. 32K tokens).  The
+// others ran out of registers while the residual window went through them, and the lines lie where that build
+// put them:
 //  * five run at one workgroup a CU.  A grid of at most a workgroup a CU: 0.98 .. 1.19 times (batch 1 x
-//    32K, 31 splits, 4-bit, G_k = 32, G_v = 64: 15.6 us against 18.0); a larger one: 0.80 .. 1.01 (batch
-//    8 x 8K, 8 splits: 25.9 against 24.6).  At two a CU, out of scratch: 0.85 .. 1.17, below 1 with one
-//    split and with a full round.
-//  * 2-bit, more than four query heads per kv head, G_k = 32 and G_v above 32, at two a CU with 80 bytes
-//    of scratch: 1.02 .. 1.19 with several splits, 0.95 .. 1.00 with one.
+//    32K, 31 splits, 4-bit, G_k = 32, G_v = 64: 15.6 us against 18.0); a larger one: 0.80 .. 1.01.
+//  * 2-bit, more than four query heads per kv head, G_k = 32 and G_v above 32, at two a CU: 1.02 .. 1.19 with
+//    several splits, 0.95 .. 1.00 with one.
+// Of the present kernels the inside form is the faster one beyond both lines (whole step in us, two calls as the
+// rule has it / inside, the five at two workgroups a CU): 2-bit, G_k = 32, G_v = 64, 28 heads on 4, one split,
+// 1 x 1000 17.0 / 15.5, 44 x 4000 31.7 / 28.2, 128 x 1000 31.1 / 26.0; G_k = G_v = 32, 128 x 1000 32.2 / 27.5; 4-bit,
+// G_k = 32, G_v = 64, 32 on 8, 8 x 8000 with 8 splits 23.2 / 20.1, 64 x 4000 62.2 / 57.3; G_k = G_v = 128, 28 on 4,
+// 128 x 1000 30.9 / 25.6.
 static bool step_form_pays(const DecodeParams& P, int gq, dim3 grid) {
   const int hp = gq <= 4 ? 1 : 2;
   if (step_one_per_cu(P.g.bits, hp, P.g.ngk, P.g.ngv))

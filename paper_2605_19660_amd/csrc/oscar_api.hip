@@ -145,8 +145,8 @@ extern "C" int32_t oscar_decode_auto_splits(const oscar_config* cfg, int32_t bat
   // eight waves per CU are resident at a time, as two workgroups of four (one for the register-hungry
   // variants, see oscar_decode_mfma_wgs_per_cu) or, in launches of at most one workgroup a CU, as one of
   // eight: aim at one round of workgroups of eight pages or more, two a wave of the four, one of the eight.  (A
-  // variant of one a CU cut for two makes two rounds: fp32 metadata, batch 8 x 16K, 8 / 4 splits, 40.3 / 34.4 us at INT2, G_k = G_v = 32, 41.2 / 34.2 at INT4, GQA 7,
-  // G_k = G_v = 128.)
+  // variant of one a CU cut for two makes two rounds: fp32 metadata, batch 8 x 16K, 8 / 4 splits, 40.3 / 34.4 us
+  // at INT2, G_k = G_v = 32, 41.2 / 34.2 at INT4, GQA 7, G_k = G_v = 128.)
   const int gq = cfg->n_kv_heads > 0 ? cfg->n_q_heads / cfg->n_kv_heads : 1;
   const int ngk = cfg->k_group > 0 ? OSCAR_R / cfg->k_group : 1;
   const int ngv = cfg->v_group > 0 ? OSCAR_D / cfg->v_group : 1;
